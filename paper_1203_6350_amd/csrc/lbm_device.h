@@ -174,9 +174,18 @@ __device__ __forceinline__ void ref_moments(const CollideParams<C> &p, C mref[9]
 // equal (n = m). That drops the run-time rate test, the relaxation
 // arithmetic of those moments and the second reciprocal; the results are
 // the same bits as without it.
-template <typename C, int VAR, bool DEF = false>
+//
+// FREE = true states that chi is 0 here (outside the absorbing layer; chi is
+// not read). The damping then only adds products with 0, and the form leaves
+// them out: 95 instead of 118 operations (Type II). What such a product does
+// to a value that is not finite is kept (0 * inf is a NaN): the terms 0 * m
+// below stand for the factors that the damped form multiplies by chi, so
+// that a run past its stability limit overflows to the same values in every
+// kernel. Only the sign of a zero may differ.
+template <typename C, int VAR, bool DEF = false, bool FREE = false>
 __device__ __forceinline__ void collide(C g[9], C chi, const CollideParams<C> &p,
                                         const C mref[9]) {
+  constexpr bool DAMPED = VAR == V_I || VAR == V_II || VAR == V_III;
   // ---- dm = M g (Appendix A.1)
   const C ax = g[1] + g[3], ay = g[2] + g[4];
   const C sa = ax + ay;                     // axis populations
@@ -201,7 +210,7 @@ __device__ __forceinline__ void collide(C g[9], C chi, const CollideParams<C> &p
   // the conserved rows needs.
   C dr = dm[0], djx = dm[1], djy = dm[2];
   C d0 = C(0), d1 = C(0), d2 = C(0), inv_n = C(1), inv_m = C(1);
-  if (VAR != V_NONE && VAR != V_VISC) {
+  if (DAMPED && !FREE) {
     d0 = p.dcf0 - dm[0];
     d1 = p.dcf1 - dm[1];
     d2 = p.dcf2 - dm[2];
@@ -232,7 +241,9 @@ __device__ __forceinline__ void collide(C g[9], C chi, const CollideParams<C> &p
       const C sk = p.s[k];
       mc[k] = (DEF || sk == C(0)) ? dm[k] : fmaC(sk, meq[k] - dm[k], dm[k]);
     }
-    if (VAR == V_I) {
+    if (FREE) {
+      // a moment that is not finite makes tr, and with it every result, a NaN
+    } else if (VAR == V_I) {
       // rows 0-2 of m^ref - m are dc^f - dc
       mc[0] = fmaC(chi, d0, mc[0]);
       mc[1] = fmaC(chi, d1, mc[1]);
@@ -257,9 +268,14 @@ __device__ __forceinline__ void collide(C g[9], C chi, const CollideParams<C> &p
 #pragma unroll
     for (int k = 3; k < 9; ++k) {
       C sk = p.s[k];
-      if (VAR == V_VISC) sk = fmaC(C(1) - sk, chi, sk);
+      if (VAR == V_VISC && !FREE) sk = fmaC(C(1) - sk, chi, sk);
       C m = fmaC(sk, meq[k] - dm[k], dm[k]);
-      if (VAR == V_I) {
+      if (FREE) {
+        if (VAR == V_I || (VAR == V_II && k != 5 && k != 6))
+          m = fmaC(C(0), VAR == V_I ? dm[k] : meq[k], m);
+        if ((VAR == V_I || VAR == V_III) && (k == 3 || k == 4))
+          m = fmaC(C(0), dm[k - 2], m);
+      } else if (VAR == V_I) {
         m = fmaC(chi, mref[k] - dm[k], m);
       } else if (VAR == V_II) {
         if (k == 5) m = fmaC(-chi * inv_m, d1, m);
@@ -277,7 +293,22 @@ __device__ __forceinline__ void collide(C g[9], C chi, const CollideParams<C> &p
     C e[9];
 #pragma unroll
     for (int k = 3; k < 9; ++k) e[k] = C(0);
-    if (VAR == V_I) {
+    if (FREE) {
+      if (VAR == V_I) {
+#pragma unroll
+        for (int k = 5; k < 9; ++k) e[k] = C(0) * dm[k];
+        e[3] = fmaC(C(0), dm[1], C(0) * dm[3]);
+        e[4] = fmaC(C(0), dm[2], C(0) * dm[4]);
+      } else if (VAR == V_II) {
+        e[3] = C(0) * meq[3];
+        e[4] = C(0) * meq[4];
+        e[7] = C(0) * meq[7];
+        e[8] = C(0) * meq[8];
+      } else if (VAR == V_III) {
+        e[3] = C(0) * dm[1];
+        e[4] = C(0) * dm[2];
+      }
+    } else if (VAR == V_I) {
       const C c36 = chi * C(DINV[3]), c12 = chi * C(DINV[5]), c4 = chi * C(DINV[7]);
       e[3] = c36 * (mref[3] - dm[3]);
       e[4] = c36 * (mref[4] - dm[4]);
@@ -306,7 +337,7 @@ __device__ __forceinline__ void collide(C g[9], C chi, const CollideParams<C> &p
 #pragma unroll
     for (int k = 3; k < 9; ++k) {
       C sig = p.sig[k], tau = p.tau[k];
-      if (VAR == V_VISC) {
+      if (VAR == V_VISC && !FREE) {
         const C sk = fmaC(C(1) - p.s[k], chi, p.s[k]);
         sig = (C(1) - sk) * C(DINV[k]);
         tau = sk * C(DINV[k]);
@@ -377,6 +408,17 @@ struct Store<__half> {
     *p = __float2half_rn(v * inv_scale);
   }
 };
+
+// A value as it comes back from storage: several steps per launch round every
+// intermediate result through it, as a store and a load would.
+template <typename S>
+__device__ __forceinline__ typename Store<S>::C roundtrip(typename Store<S>::C v,
+                                                          typename Store<S>::C scale,
+                                                          typename Store<S>::C inv_scale) {
+  S t;
+  Store<S>::store(&t, v, inv_scale);
+  return Store<S>::load(&t, scale);
+}
 
 // Sponge strength at a cell.
 template <typename C, int CHI>

@@ -59,10 +59,12 @@ constexpr int CHI_RUNTIME = 4;
 // conserved moments as a running mean, c^f <- c^f + alpha (c - c^f), after
 // each step's collision; a launch reads the field and writes the updated
 // one to a second buffer (strips read their neighbours' entries as halo).
+// V_FREE: chi is 0 in every cell the strip collides (collide's FREE).
 constexpr int V_MASK = 7;
 constexpr int V_DEF = 8;
 constexpr int V_QF = 16;
 constexpr int V_QA = 32;
+constexpr int V_FREE = 64;
 
 template <int K>
 constexpr int strip_width() {
@@ -71,15 +73,6 @@ constexpr int strip_width() {
 template <int M>
 __device__ constexpr int md(int x) {  // x mod M in [0, M)
   return ((x % M) + M) % M;
-}
-
-template <typename S>
-__device__ __forceinline__ typename Store<S>::C roundtrip(typename Store<S>::C v,
-                                                          typename Store<S>::C scale,
-                                                          typename Store<S>::C inv_scale) {
-  S t;
-  Store<S>::store(&t, v, inv_scale);
-  return Store<S>::load(&t, scale);
 }
 
 // DPP wave shifts: wave_shr:1 gives lane l the value of lane l - 1,
@@ -165,6 +158,7 @@ struct StripCtx {
 
   static constexpr bool QF = (VAR & V_QF) != 0;
   static constexpr bool QA = (VAR & V_QA) != 0;
+  static constexpr bool FREE = (VAR & V_FREE) != 0;
 
   __device__ __forceinline__ int wrap_row(int r) const {
     r %= ny;
@@ -262,15 +256,15 @@ struct StripCtx {
         djy = (g[2] - g[4]) + ((g[5] - g[7]) + (g[6] - g[8]));
       }
       C mr[9];
-      if ((VAR & V_MASK) == V_I || (VAR & V_MASK) == V_II) ref_moments(pc, mr);
-      collide<C, VAR & V_MASK, (VAR & V_DEF) != 0>(g, chi, pc, mr);
+      if (!FREE && ((VAR & V_MASK) == V_I || (VAR & V_MASK) == V_II)) ref_moments(pc, mr);
+      collide<C, VAR & V_MASK, (VAR & V_DEF) != 0, FREE>(g, chi, pc, mr);
       if constexpr (QA) {
         st.qraw[md<6>(Q)][0] = fmaC(alpha, dr - pc.dcf0, pc.dcf0);
         st.qraw[md<6>(Q)][1] = fmaC(alpha, djx - pc.dcf1, pc.dcf1);
         st.qraw[md<6>(Q)][2] = fmaC(alpha, djy - pc.dcf2, pc.dcf2);
       }
     } else {
-      collide<C, VAR & V_MASK, (VAR & V_DEF) != 0>(g, chi, p, mref);
+      collide<C, VAR & V_MASK, (VAR & V_DEF) != 0, FREE>(g, chi, p, mref);
     }
   }
   __device__ __forceinline__ C chi_of(C raw) const {
@@ -427,8 +421,31 @@ __device__ __forceinline__ void strip_setup(StripCtx<S, VAR, CHI, K> &c, const S
     c.inv_scale[i] = inv_scale[i];
   }
   c.p = p;
-  if (!StripCtx<S, VAR, CHI, K>::QF && ((VAR & V_MASK) == V_I || (VAR & V_MASK) == V_II))
+  if (!StripCtx<S, VAR, CHI, K>::QF && !StripCtx<S, VAR, CHI, K>::FREE &&
+      ((VAR & V_MASK) == V_I || (VAR & V_MASK) == V_II))
     ref_moments(p, c.mref);
+}
+
+// Whether chi is 0 in every cell that the strip collides over R output rows
+// from Y0 on (rows Y0 - K + 1 .. Y0 + R + K - 2, all 64 lanes), the same
+// answer in all lanes of the wave. A two-dimensional field is taken as not free:
+// looking it over first costs more than the shorter loop gains (1628 x 1610
+// FP32, -4%).
+template <typename S, int VAR, int CHI, int K>
+__device__ __forceinline__ bool strip_is_free(const StripCtx<S, VAR, CHI, K> &c, int R) {
+  typedef typename Store<S>::C C;
+  const int m = c.mode();
+  const int rows = R + 2 * K - 2;
+  bool any = false;
+  if (m == CHI_SEP_MAX || m == CHI_SEP_SUM) {
+    any = c.cx_chi != C(0);
+    // (the same number of rounds in every lane: the loop stays uniform)
+    for (int i = 0; i < rows; i += 64)
+      any |= c.chiy[c.wrap_row(c.Y0 - K + 1 + min(i + (int)(threadIdx.x & 63), rows - 1))] != C(0);
+  } else {
+    any = m == CHI_FIELD;
+  }
+  return __builtin_amdgcn_ballot_w64(any) == 0;  // a scalar: the branch on it is uniform
 }
 
 // The row loop of one strip over R output rows from Y0 on.
@@ -494,6 +511,50 @@ __device__ __forceinline__ void strip_run(const StripCtx<S, VAR, CHI, K> &c, int
 #undef LBM_STRIP_ITER
 }
 
+// One strip, in the form that its part of the layer needs. In FP16 storage,
+// whose strips are bound by VALU issue, a strip clear of the layer (0.90 of the
+// waves of 4096^2 with a 64-cell layer) runs the collision without the
+// damping's products with 0, same values: 4096^2 Type II 210 -> 229 GLUPS (three
+// steps, block 64, rows 32). In FP32 the strips of this width move memory at
+// 4.7 TB/s whether they collide or not (265 us a launch without the collision,
+// 285 with it) and gained 2%; in FP64 the second loop's registers took 9% from
+// batches: these keep the one loop. The choice is made once per strip, so each
+// row loop stays one block; the waves of a workgroup may differ, both loops
+// pass one barrier per row.
+template <typename S, int VAR, int CHI, int K>
+__device__ __forceinline__ void strip_do(const S *src, S *dst, int nx, int ny, int64_t pitch,
+                                         int64_t ps, int strip, bool idle, int Y0, int R, int nw,
+                                         const typename Store<S>::C *chi_field,
+                                         const typename Store<S>::C *chix,
+                                         const typename Store<S>::C *chiy, int chi_mode,
+                                         const typename Store<S>::C scale[9],
+                                         const typename Store<S>::C inv_scale[9],
+                                         const CollideParams<typename Store<S>::C> &p,
+                                         const typename Store<S>::C *qf = nullptr,
+                                         int64_t qps = 0,
+                                         typename Store<S>::C *qf_out = nullptr,
+                                         typename Store<S>::C alpha = 0) {
+  StripCtx<S, VAR, CHI, K> c;
+  strip_setup(c, src, dst, nx, ny, pitch, ps, strip, idle, Y0, nw, chi_field, chix, chiy,
+              chi_mode, scale, inv_scale, p, qf, qps, qf_out, alpha);
+  // (default parameters only, which halves the instances; the undamped scheme
+  // is its own free form)
+  constexpr bool LAYER = sizeof(S) == 2 && (VAR & V_MASK) != V_NONE && (VAR & V_DEF) != 0 &&
+                         CHI != CHI_FIELD;
+  if constexpr (LAYER) {
+    if (CHI == CHI_ZERO || strip_is_free(c, R)) {
+      // a fixed per-cell reference is not read where chi is 0
+      constexpr int FV = ((VAR & V_QA) ? VAR : VAR & ~V_QF) | V_FREE;
+      StripCtx<S, FV, CHI_ZERO, K> f;
+      strip_setup(f, src, dst, nx, ny, pitch, ps, strip, idle, Y0, nw, chi_field, chix, chiy,
+                  CHI_ZERO, scale, inv_scale, p, qf, qps, qf_out, alpha);
+      strip_run(f, R);
+      return;
+    }
+  }
+  if constexpr (!LAYER || CHI != CHI_ZERO) strip_run(c, R);
+}
+
 // Waves per SIMD the single-lattice kernel may run: the FP64 four-step form
 // one (its 253 registers would fit two, but the fitted chunks then halve in
 // height and the extra warm-up rows cost more than the second wave gains:
@@ -524,10 +585,9 @@ void step_multi_strip(
   const bool idle = strip >= nstrips;
   if (idle) strip = nstrips - 1;
   const int Y0 = chunk * rows_per_chunk;
-  StripCtx<S, VAR, CHI, K> c;
-  strip_setup(c, src, dst, L.nx, L.ny, L.pitch, L.ps, strip, idle, Y0, nw, chi_field, chix, chiy,
-              CHI, L.scale, L.inv_scale, p, qf, qps, qf_out, alpha);
-  strip_run(c, min(rows_per_chunk, L.ny - Y0));
+  strip_do<S, VAR, CHI, K>(src, dst, L.nx, L.ny, L.pitch, L.ps, strip, idle, Y0,
+                           min(rows_per_chunk, L.ny - Y0), nw, chi_field, chix, chiy, CHI, L.scale,
+                           L.inv_scale, p, qf, qps, qf_out, alpha);
 }
 
 // Batched form: a persistent grid works through a table of work items
@@ -608,11 +668,10 @@ void batch_multi_strip(const BatchDomain *__restrict__ doms, const int4 *__restr
     set_relax_coeffs(p);
 #define LBM_BATCH_RUN(VAR, QFP)                                                              \
   {                                                                                          \
-    StripCtx<S, VAR | (DEF ? V_DEF : 0), MAXF ? CHI_SEP_MAX : CHI_RUNTIME, K> c;           \
-    strip_setup(c, (const S *)d.lat[par], (S *)d.lat[par ^ 1], d.nx, d.ny, d.pitch, d.ps,   \
-                strip, idle, it.z, nw, (const C *)d.chi_field, (const C *)d.chi_x,           \
-                (const C *)d.chi_y, d.chi_mode, scale, inv_scale, p, QFP, d.qps);            \
-    strip_run(c, it.w);                                                                      \
+    strip_do<S, (VAR) | (DEF ? V_DEF : 0), MAXF ? CHI_SEP_MAX : CHI_RUNTIME, K>(             \
+        (const S *)d.lat[par], (S *)d.lat[par ^ 1], d.nx, d.ny, d.pitch, d.ps, strip, idle,  \
+        it.z, it.w, nw, (const C *)d.chi_field, (const C *)d.chi_x, (const C *)d.chi_y,      \
+        d.chi_mode, scale, inv_scale, p, QFP, d.qps);                                        \
   }
     bool ran = false;
     if constexpr (QF) {
