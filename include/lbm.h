@@ -169,8 +169,9 @@ int lbm_sync(lbm_handle *h);
  * a check kernel reads the stored state on the handle's stream and trips if
  * any cell holds a non-finite population or a deviation |f_i - f_i^base|
  * larger than max_dev: the same condition as lbm_diagnostics reporting
- * out[6] > 0 or out[5] > max_dev. (Launches of the K-step kernels advance K
- * steps, so a check can land up to K - 1 steps after the multiple.) Batch
+ * out[6] > 0 or out[5] > max_dev. (Launches of the K-step kernels of a set
+ * tuning advance K steps, so a check can land up to K - 1 steps after the
+ * multiple; otherwise it lands on it.) Batch
  * ticks check their members the same way at the end of the tick. The first
  * trip keeps the step count at which it was seen; from then on lbm_sync,
  * lbm_moments and lbm_diagnostics complete their work (outputs written)
@@ -256,14 +257,16 @@ int lbm_get_info(lbm_handle *h, lbm_info *info);
  * (rho_f > 0, all finite), copied to the device as the conserved moments
  * (rho^f, rho^f u^f) in the compute precision; it replaces the uniform q_ref
  * of lbm_set_sponge until cleared with three NULL arrays (which also sets
- * the averaging rate back to 0). While a field is set, the K-step kernels
- * of the tuning run only with the default-form parameters (conserved rates
+ * the averaging rate back to 0). While a field is set, the K-step strips
+ * run only with the default-form parameters (conserved rates
  * s0 = s1 = s2 = 0 and shift_n = shift_m; for a running mean also a damped
- * variant I, II or III), lbm_step takes the one-cell-per-thread kernel
- * otherwise (same results either way); the handle cannot join a batch, and
- * the field is not part of lbm_save_state (read it with
- * lbm_get_qref_field). A running mean in the K-step kernels keeps a second
- * field buffer (allocated at the first such step).
+ * variant I, II or III), lbm_step takes the tile kernel or the
+ * one-cell-per-thread kernel otherwise (same results either way); the handle
+ * cannot join a batch, and the field is not part of lbm_save_state (read it
+ * with lbm_get_qref_field). A running mean in the several-step kernels keeps
+ * a second field buffer (allocated at the first such step; a handle whose
+ * shape is not set steps a captured stream with the one-cell kernel, in
+ * place).
  *
  * lbm_set_qref_average: after each step's collision the field follows the
  * cell's pre-collision conserved moments c = (rho, j) as an exponential
@@ -285,7 +288,8 @@ int lbm_get_qref_field(lbm_handle *h, double *rho_f, double *ux_f, double *uy_f)
  * outflow = 1 the column x = nx - 1 holds a copy of column nx - 2 after the
  * collision (zero-gradient outflow). y stays periodic. Needs nx >= 3 and
  * rho0 - |amp| > 0; src = NULL (with outflow = 0) makes x periodic again.
- * While set, lbm_step runs the one-cell-per-thread kernel whatever the
+ * While set, lbm_step runs the tile kernel (up to 14 steps per launch) or
+ * the one-cell-per-thread kernel, whichever suits the size, whatever the
  * tuning, and the handle cannot join a batch or take a reference field. */
 typedef struct lbm_line_source {
   double rho0, amp, freq, phase, ux, uy;
@@ -294,7 +298,15 @@ int lbm_set_line_source(lbm_handle *h, const lbm_line_source *src, int32_t outfl
 
 /* ---- kernel tuning ----------------------------------------------------
  * Launch shape of the step kernel. Every choice computes the same per-cell
- * arithmetic, so results are bit-identical across tunings. */
+ * arithmetic, so results are bit-identical across tunings.
+ * A handle whose shape has not been set (lbm_set_tuning, lbm_autotune) leaves
+ * the choice to lbm_step, by size, storage and number of steps: the tile
+ * kernel on lattices too small to fill the device with strips, else strips of
+ * four steps; lbm_get_tuning then reports the shape of its single steps.
+ * Whatever the kernel, the lattice buffer that is current after a call is the
+ * one that the set shape's own launches (one per step, if none is set) would
+ * have left current, so a captured sequence of an even number of them can be
+ * replayed. */
 typedef struct lbm_tuning {
   int32_t kernel;      /* 0: one cell per thread; 1: 16-byte vector rows
                           (4 cells FP32, 2 FP64, 8 FP16; needs nx % cells == 0,
@@ -313,9 +325,11 @@ typedef struct lbm_tuning {
   int32_t block;       /* threads per block: 64, 128, 256 or 512 (FP64
                           storage with kernel 4: at most 256)               */
   int32_t nontemporal; /* 1: streaming stores (vector kernel only)           */
-  int32_t rows;        /* kernels 2-4: rows per chunk, 1..4096, or 0 for
-                          the height at which all blocks are resident at
-                          once; ignored by kernels 0 and 1                  */
+  int32_t rows;        /* kernels 2-4: rows per chunk, 1..4096, or 0 to fit
+                          the launch to the device: the height at which all
+                          blocks are resident at once, or, on a lattice too
+                          small for that to pay, the tile kernel with up to
+                          14 steps per launch; ignored by kernels 0 and 1    */
 } lbm_tuning;
 
 int lbm_set_tuning(lbm_handle *h, const lbm_tuning *t);

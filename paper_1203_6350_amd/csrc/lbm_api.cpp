@@ -98,6 +98,8 @@ struct lbm_handle {
   int64_t steps = 0;
   size_t lat_bytes = 0;
   int device = 0;
+  int cus = 256;              // compute units of the device
+  bool shape_set = false;     // lbm_set_tuning or lbm_autotune chose the launch shape
   // instability detector (lbm_set_detector)
   int64_t det_every = 0;      // 0: off
   double det_max = 0.0;
@@ -340,6 +342,8 @@ int create_common(const lbm_config *cfg, const double *rho, const double *ux,
   if (!h) return fail(LBM_ENOMEM, "host allocation failed");
   h->user = *cfg;
   h->device = dev;
+  if (hipDeviceGetAttribute(&h->cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess)
+    h->cus = 256;
   h->stream = (hipStream_t)cfg->stream;
   h->q = lbm_qref{cfg->rho_base, cfg->ux_base, cfg->uy_base};
   int64_t pitch, ps;
@@ -390,7 +394,183 @@ int create_common(const lbm_config *cfg, const double *rho, const double *ux,
 }  // namespace
 
 namespace {
-// The second reference-field buffer of the strip kernels' running mean.
+// How lbm_step advances a handle: tiles on regions of `region` cells a side
+// with up to `most` steps per launch, strips of `most` steps with the shape in
+// `cfg`, or one step per launch. `per` is the step count whose multiples (and
+// the call's end) are the moments at which a due detector check is made, and
+// whose number of launches gives the parity that the call leaves: the lattice
+// that is current afterwards does not depend on the kernel that was taken.
+struct StepPlan {
+  enum Kind { ONE, STRIP, TILE } kind = ONE;
+  int region = 0, most = 1, per = 1;
+  lbm::StepConfig cfg;
+};
+struct Launch {
+  int steps;
+  bool check;
+};
+
+// Time of a tile launch in us, as measured back to back on 256 compute units
+// (one entry per region size): first + step * s for s steps where the tiles
+// all run at once, and next + next_step * s for each further round of tiles.
+// Rows: FP64, FP32, FP16.
+struct TileTime {
+  int region;
+  double first, step, next, next_step;
+};
+constexpr TileTime TILE_TIMES[3][4] = {
+    {{24, 6.2, 0.51, 3.4, 0.49}, {32, 7.7, 0.70, 5.8, 0.58}, {0, 0, 0, 0, 0}, {0, 0, 0, 0, 0}},
+    {{24, 4.9, 0.39, 2.0, 0.10}, {32, 6.0, 0.44, 2.4, 0.57}, {40, 8.4, 0.74, 4.9, 0.68}, {48, 10.4, 1.10, 7.2, 0.97}},
+    {{24, 5.0, 0.51, 0.5, 0.38}, {32, 5.5, 0.66, 2.3, 0.68}, {40, 6.9, 1.13, 4.8, 1.00}, {48, 8.9, 1.55, 5.2, 1.70}}};
+
+// The fastest tile launch for up to n steps: region, steps per launch and its
+// time per step (1e300 where there is none). Beyond two rounds of tiles the
+// strips are faster (three rounds, 1023 x 777 FP64: 10.4 against 8.9 us a step;
+// two, 700 x 500: 5.4 against 5.8, in FP32 3.4 against 4.7); where there are
+// none, the alternative is one step per launch and more rounds still pay.
+double best_tiles(const lbm::StepConfig &c, int64_t n, int cus, bool strips, int *region,
+                  int *steps) {
+  double best = 1e300;
+  const double most_rounds = strips ? 2.0 : 8.0;
+  const int ch = c.channel ? 1 : 0;
+  for (const TileTime &t : TILE_TIMES[c.storage]) {
+    for (int s = 2; t.region && s <= lbm::TILE_MAX_STEPS && s <= n; ++s) {
+      const int T = t.region - 2 * (s - 1 + ch);
+      if (T < 4) break;
+      const int64_t tiles = (int64_t)((c.nx + T - 1) / T) * ((c.ny + T - 1) / T);
+      const double rounds = (double)((tiles + cus - 1) / cus);
+      if (rounds > most_rounds) continue;
+      const double us = (t.first + t.step * s + (rounds - 1) * (t.next + t.next_step * s)) / s;
+      if (us < best) {
+        best = us;
+        *region = t.region;
+        *steps = s;
+      }
+    }
+  }
+  return best;
+}
+
+// The time per step in us that the tiles have to beat: the K-step strips' in
+// their fitted shape, from 300^2 to 1400^2 cells a fixed part (a strip's rows run
+// in sequence) and a rate (measured: 512^2 FP32 4.2 and tiles 2.0, 1023 x 777
+// 6.3 and 7.9), or the one-step kernel's where there are no strips.
+double other_time(const lbm::StepConfig &c, bool strips) {
+  const double cells = (double)c.nx * c.ny;
+  static const double fixed[3] = {3.0, 2.6, 2.9}, rate[3] = {7.3e-6, 4.6e-6, 5.5e-6};
+  static const double one_fixed[3] = {3.4, 3.0, 3.0}, one_rate[3] = {2.5e-5, 1.15e-5, 8e-6};
+  return strips ? fixed[c.storage] + rate[c.storage] * cells
+                : one_fixed[c.storage] + one_rate[c.storage] * cells;
+}
+
+// The plan for a call of n steps.
+StepPlan step_plan(const lbm_handle *h, int64_t n) {
+  StepPlan p;
+  const int k = h->cfg.kernel;
+  const bool strips = lbm::multi_step_supports(h->cfg);
+  const bool chosen = h->shape_set && k >= lbm::KERNEL_MULTI_MIN;
+  p.per = chosen && strips ? k : 1;
+  // a channel has no strip form: any shape means the tiles for it
+  if (n >= 2 && (h->channel || !h->shape_set || (chosen && h->cfg.rows == 0)) &&
+      best_tiles(h->cfg, n, h->cus, strips, &p.region, &p.most) <
+          other_time(h->cfg, strips)) {
+    p.kind = StepPlan::TILE;
+    return p;
+  }
+  p.most = 1;
+  if (n < 2 || !strips || (h->shape_set && !chosen)) return p;
+  p.kind = StepPlan::STRIP;
+  p.cfg = h->cfg;
+  if (h->shape_set) {
+    p.most = k;
+    return p;
+  }
+  // as created: the shape that is fastest or within 5% of it from 300^2 to 3000
+  // x 2500 cells (wide workgroups pay once the chunks are tall)
+  p.most = 4;
+  p.cfg.kernel = p.most;
+  p.cfg.rows = 0;
+  p.cfg.block = h->user.storage == LBM_STORAGE_F16              ? 64
+                : (int64_t)h->user.nx * h->user.ny < 3000000 ? (h->user.storage == LBM_STORAGE_F64 ? 128 : 64)
+                                                                : 256;
+  return p;
+}
+
+// The launches of n steps. False where they could not keep the parity (a
+// single step per launch then does).
+bool plan_launches(const lbm_handle *h, int64_t n, const StepPlan &p, std::vector<Launch> &out) {
+  const int64_t before = n / p.per + (n % p.per != 0);
+  const bool own = p.kind == StepPlan::STRIP && p.per == p.most;  // the handle's own strips
+  int64_t next = h->det_every ? h->det_next : 0;
+  for (int64_t k = 0; k < n;) {
+    int64_t seg = n - k;
+    if (h->det_every) {
+      const int64_t due = next - h->steps;  // in steps from the call's start
+      const int64_t at = (due + p.per - 1) / p.per * p.per;
+      if (at < n) seg = std::max<int64_t>(at - k, 1);
+    }
+    const int64_t count = (seg + p.most - 1) / p.most;
+    for (int64_t i = 0; i < count; ++i) {
+      // evenly, except for the handle's own strips: full launches and a rest
+      const int64_t m = own ? std::min<int64_t>(p.most, seg - i * p.most)
+                            : seg / count + (i < seg % count);
+      out.push_back(Launch{(int)m, i + 1 == count});
+    }
+    k += seg;
+    if (h->det_every) next = ((h->steps + k) / h->det_every + 1) * h->det_every;
+  }
+  if (((int64_t)out.size() ^ before) & 1) {
+    size_t i = out.size();
+    while (i > 0 && out[i - 1].steps < 2) --i;
+    if (i == 0) return false;
+    const Launch l = out[i - 1];
+    out[i - 1] = Launch{l.steps / 2, false};
+    out.insert(out.begin() + (ptrdiff_t)i, Launch{l.steps - l.steps / 2, l.check});
+  }
+  return true;
+}
+
+// Enqueue one launch of `steps` steps from lattice src into dst.
+// *second: a running mean went to the second buffer (the one-step kernel
+// updates it in place).
+int enqueue_launch(lbm_handle *h, const StepPlan &p, int steps, const void *src, void *dst,
+                   bool *second) {
+  hipError_t e;
+  lbm::StepConfig c = p.kind == StepPlan::STRIP && steps > 1 ? p.cfg : h->cfg;
+  c.qfield = h->qf;
+  c.qfield_out = h->qf2;
+  *second = false;
+  if (p.kind == StepPlan::TILE) {
+    double source[9 * lbm::TILE_MAX_STEPS];
+    if (h->channel)
+      for (int j = 0; j < steps; ++j) source_dev(h, h->steps + 1 + j, source + 9 * j);
+    e = lbm::launch_tile(c, p.region, steps, h->channel ? source : nullptr, src, dst, h->stream);
+    *second = h->qf && h->qalpha != 0.0;
+  } else if (p.kind == StepPlan::STRIP && steps > 1) {
+    e = lbm::launch_multi_steps(c, steps, src, dst, h->stream);
+    *second = h->qf && h->qalpha != 0.0;
+  } else {
+    if (h->channel) source_dev(h, h->steps + 1, c.src_dev);
+    e = lbm::launch_step(c, src, dst, h->stream);
+  }
+  return e == hipSuccess ? LBM_OK : hip_fail(e, "step kernel");
+}
+
+int run_launch(lbm_handle *h, const StepPlan &p, int steps) {
+  bool second = false;
+  int rc = enqueue_launch(h, p, steps, h->lat[h->cur], h->lat[1 - h->cur], &second);
+  if (rc) return rc;
+  h->cur = 1 - h->cur;
+  h->steps += steps;
+  if (second) {
+    std::swap(h->qf, h->qf2);
+    h->cfg.qfield = h->qf;
+    h->cfg.qfield_out = h->qf2;
+  }
+  return LBM_OK;
+}
+
+// The second reference-field buffer of the several-step kernels' running mean.
 int ensure_qf2(lbm_handle *h) {
   if (h->qf2) return LBM_OK;
   const size_t eb = h->user.storage == LBM_STORAGE_F64 ? 8 : 4;
@@ -510,42 +690,39 @@ int lbm_set_sponge_separable_dev(lbm_handle *h, const double *chi_x, const doubl
 int lbm_step(lbm_handle *h, int64_t n) {
   if (!h) return fail(LBM_EINVAL, "handle is NULL");
   if (n < 0) return fail(LBM_EINVAL, "n must be >= 0");
-  int64_t k = 0;
-  const int per = h->cfg.kernel;  // time steps per launch of the multi-step kernel
-  // a channel, rows of 2^32 bytes or more, a running-mean reference state,
+  // A channel, rows of 2^32 bytes or more, a running-mean reference state,
   // or a per-cell one with parameters other than the default form run in the
-  // one-step kernel only
-  if (per >= lbm::KERNEL_MULTI_MIN && lbm::multi_step_supports(h->cfg)) {
-    // a running-mean reference: each launch writes the updated field to the
-    // second buffer, which then becomes the current one
+  // tile kernel or one step per launch only.
+  const StepPlan p = step_plan(h, n);
+  if (p.kind != StepPlan::ONE) {
     const bool qa = h->qf && h->qalpha != 0.0;
-    if (qa && n - k >= 2) {
-      int rc = ensure_qf2(h);
-      if (rc) return rc;
-    }
-    while (n - k >= 2) {
-      const int m = n - k >= per ? per : (int)(n - k);
-      hipError_t e = lbm::launch_multi_steps(h->cfg, m, h->lat[h->cur], h->lat[1 - h->cur], h->stream);
-      if (e != hipSuccess) return hip_fail(e, "multi-step kernel");
-      h->cur = 1 - h->cur;
-      h->steps += m;
-      k += m;
-      if (qa) {
-        std::swap(h->qf, h->qf2);
-        h->cfg.qfield = h->qf;
-        h->cfg.qfield_out = h->qf2;
+    bool in_place = false;  // the one-step kernel keeps the running mean where it is
+    if (qa) {
+      // a captured sequence of the shape as created must leave the mean in the
+      // buffer that its replay starts from, and allocates nothing
+      hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
+      if (!h->shape_set)
+        HIP_TRY(hipStreamIsCapturing(h->stream, &cs), "hipStreamIsCapturing");
+      in_place = cs != hipStreamCaptureStatusNone;
+      if (!in_place) {
+        int rc = ensure_qf2(h);
+        if (rc) return rc;
       }
-      int rc = detector_after_launch(h, h->stream, nullptr);
-      if (rc) return rc;
+    }
+    std::vector<Launch> todo;
+    if (!in_place && plan_launches(h, n, p, todo)) {
+      for (const Launch &l : todo) {
+        int rc = run_launch(h, p, l.steps);
+        if (rc) return rc;
+        if (l.check && (rc = detector_after_launch(h, h->stream, nullptr)) != LBM_OK) return rc;
+      }
+      return LBM_OK;
     }
   }
-  for (; k < n; ++k) {
-    if (h->channel) source_dev(h, h->steps + 1, h->cfg.src_dev);
-    hipError_t e = lbm::launch_step(h->cfg, h->lat[h->cur], h->lat[1 - h->cur], h->stream);
-    if (e != hipSuccess) return hip_fail(e, "step kernel");
-    h->cur = 1 - h->cur;
-    h->steps += 1;
-    int rc = detector_after_launch(h, h->stream, nullptr);
+  const StepPlan one{};
+  for (int64_t k = 0; k < n; ++k) {
+    int rc = run_launch(h, one, 1);
+    if (!rc) rc = detector_after_launch(h, h->stream, nullptr);
     if (rc) return rc;
   }
   return LBM_OK;
@@ -727,6 +904,7 @@ int lbm_set_tuning(lbm_handle *h, const lbm_tuning *t) {
   h->cfg.block = t->block;
   h->cfg.nontemporal = t->kernel == 1 ? t->nontemporal : 0;
   if (t->kernel >= 2) h->cfg.rows = t->rows;
+  h->shape_set = true;
   return LBM_OK;
 }
 
@@ -747,16 +925,27 @@ int lbm_autotune(lbm_handle *h, int32_t reps, lbm_tuning *best, double *best_ms)
   if (reps < 1) return fail(LBM_EINVAL, "reps must be >= 1");
   std::vector<lbm_tuning> cands;
   const int blocks[4] = {64, 128, 256, 512};
-  for (int b : blocks) cands.push_back(lbm_tuning{0, b, 0, 0});
-  if (lbm::vec_supported(h->cfg))
-    for (int nt = 0; nt < 2; ++nt)
-      for (int b : blocks) cands.push_back(lbm_tuning{1, b, nt, 0});
-  const int rows[4] = {0, 8, 16, 32};
-  if (lbm::multi_step_supports(h->cfg))  // lbm_step would not run them otherwise
-    for (int kk = lbm::KERNEL_MULTI_MIN; kk <= lbm::KERNEL_MULTI_MAX; ++kk)
-      for (int b : blocks)
-        if (b <= lbm::multi_step_max_block(h->user.storage, kk))
-          for (int r : rows) cands.push_back(lbm_tuning{kk, b, 0, r});
+  int tile_region, tile_steps;
+  const bool strips = lbm::multi_step_supports(h->cfg);
+  const bool tiles = best_tiles(h->cfg, 1 << 20, h->cus, strips, &tile_region, &tile_steps) <
+                     other_time(h->cfg, strips);
+  if (h->channel && tiles) {
+    cands.push_back(lbm_tuning{0, 256, 0, 0});  // the tiles, whatever the shape
+  } else {
+    for (int b : blocks) cands.push_back(lbm_tuning{0, b, 0, 0});
+    if (lbm::vec_supported(h->cfg))
+      for (int nt = 0; nt < 2; ++nt)
+        for (int b : blocks) cands.push_back(lbm_tuning{1, b, nt, 0});
+    const int rows[4] = {0, 8, 16, 32};
+    // rows = 0 means the tiles on a small lattice, for every step count and block
+    if (tiles) cands.push_back(lbm_tuning{4, 256, 0, 0});
+    if (strips)  // lbm_step would not run them otherwise
+      for (int kk = lbm::KERNEL_MULTI_MIN; kk <= lbm::KERNEL_MULTI_MAX; ++kk)
+        for (int b : blocks)
+          if (b <= lbm::multi_step_max_block(h->user.storage, kk))
+            for (int r : rows)
+              if (r || !tiles) cands.push_back(lbm_tuning{kk, b, 0, r});
+  }
   hipEvent_t e0, e1;
   HIP_TRY(hipEventCreate(&e0), "hipEventCreate");
   hipError_t e = hipEventCreate(&e1);
@@ -783,29 +972,50 @@ int lbm_autotune(lbm_handle *h, int32_t reps, lbm_tuning *best, double *best_ms)
       return hip_fail(e, "autotune reference copy");
     }
   }
+  // The candidates step a copy of the lattice to and fro between a scratch
+  // buffer and the lattice that the next step overwrites anyway, so that they
+  // meet memory as a run does (from one unchanging lattice into another, one of
+  // about the last-level cache's size mostly hits: 2048^2 FP64 then took blocks
+  // of 64, 10% slower in a run). Without room for it they go one way.
+  void *scratch = nullptr;
+  if (hipMallocAsync(&scratch, h->lat_bytes, h->stream) != hipSuccess) {
+    (void)hipGetLastError();
+    scratch = nullptr;
+  }
+  if (scratch)
+    e = hipMemcpyAsync(scratch, h->lat[h->cur], h->lat_bytes, hipMemcpyDeviceToDevice, h->stream);
+  const void *from = scratch ? scratch : h->lat[h->cur];
+  void *to = h->lat[1 - h->cur];
   const lbm::StepConfig saved = h->cfg;
+  const bool saved_set = h->shape_set;
   double best_t = 1e300;
   lbm_tuning best_c = cands[0];
+  int rc_launch = LBM_OK;
+  h->shape_set = true;
   for (const lbm_tuning &c : cands) {
     h->cfg.kernel = c.kernel;
     h->cfg.block = c.block;
     h->cfg.nontemporal = c.nontemporal;
     h->cfg.rows = c.kernel >= 2 ? c.rows : saved.rows;
-    // the candidate reads the current lattice and overwrites the other one,
-    // whose contents the next step replaces anyway
-    for (int k = 0; k < 2 + reps && e == hipSuccess; ++k) {
+    const StepPlan p = step_plan(h, 1 << 20);
+    for (int k = 0; k < 2 + reps && e == hipSuccess && !rc_launch; ++k) {
+      bool second;
       if (k == 2) e = hipEventRecord(e0, h->stream);
-      if (e == hipSuccess)
-        e = c.kernel >= 2 ? lbm::launch_multi_steps(h->cfg, c.kernel, h->lat[h->cur],
-                                                    h->lat[1 - h->cur], h->stream)
-                          : lbm::launch_step(h->cfg, h->lat[h->cur], h->lat[1 - h->cur], h->stream);
+      if (e != hipSuccess) break;
+      rc_launch = enqueue_launch(h, p, p.most, from, to, &second);
+      if (scratch) {
+        void *t = const_cast<void *>(from);
+        from = to;
+        to = t;
+      }
     }
+    if (rc_launch) break;
     if (e == hipSuccess) e = hipEventRecord(e1, h->stream);
     if (e == hipSuccess) e = hipEventSynchronize(e1);
     float ms = 0.f;
     if (e == hipSuccess) e = hipEventElapsedTime(&ms, e0, e1);
     if (e != hipSuccess) break;
-    const double per = ms / reps / (c.kernel >= 2 ? (double)c.kernel : 1.0);  // per time step
+    const double per = ms / reps / (double)p.most;  // per time step
     if (per < best_t) {
       best_t = per;
       best_c = c;
@@ -814,12 +1024,16 @@ int lbm_autotune(lbm_handle *h, int32_t reps, lbm_tuning *best, double *best_ms)
   (void)hipEventDestroy(e0);
   (void)hipEventDestroy(e1);
   h->cfg = saved;
+  h->shape_set = saved_set;
+  if (scratch) (void)hipFreeAsync(scratch, h->stream);
   if (qf_keep) {
     const hipError_t e2 = hipMemcpyAsync(h->qf, qf_keep, qf_bytes, hipMemcpyDeviceToDevice, h->stream);
     (void)hipFreeAsync(qf_keep, h->stream);
     if (e == hipSuccess) e = e2;
   }
+  if (rc_launch) return rc_launch;
   if (e != hipSuccess) return hip_fail(e, "autotune");
+  h->shape_set = true;
   h->cfg.kernel = best_c.kernel;
   h->cfg.block = best_c.block;
   h->cfg.nontemporal = best_c.nontemporal;

@@ -123,6 +123,16 @@ hipError_t launch_batch(int storage, const BatchDomain *doms, const int2 *tiles,
   return hipErrorInvalidValue;
 }
 
+hipError_t launch_tile(const StepConfig &c, int region, int steps, const double *source,
+                       const void *src, void *dst, hipStream_t stream) {
+  switch (c.storage) {
+    case 0: return launch_tile_f64(c, region, steps, source, src, dst, stream);
+    case 1: return launch_tile_f32(c, region, steps, source, src, dst, stream);
+    case 2: return launch_tile_f16(c, region, steps, source, src, dst, stream);
+  }
+  return hipErrorInvalidValue;
+}
+
 hipError_t launch_batch_multi(int storage, int k, int nw, int form, const BatchDomain *doms,
                               const int4 *items, int *nitems, int grid, int j,
                               hipStream_t stream) {

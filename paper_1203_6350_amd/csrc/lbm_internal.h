@@ -77,7 +77,19 @@ inline bool multi_step_supports(const StepConfig &c) {
 // k = 2..4 time steps in one launch (src at t -> dst at t + k).
 hipError_t launch_multi_steps(const StepConfig &c, int k, const void *src, void *dst,
                               hipStream_t stream);
-// per storage type (lbm_strip_f64/f32/f16.hip)
+// Tile kernel (lbm_tile_f64/f32/f16.hip): 1..TILE_MAX_STEPS steps in one
+// launch on regions of `region` cells a side (24 or 32, and in FP32 and FP16
+// 40 or 48). source: for a channel, the source column's deviations
+// [steps][9], else NULL. A running-mean reference is written to qfield_out.
+constexpr int TILE_MAX_STEPS = 14;
+hipError_t launch_tile(const StepConfig &c, int region, int steps, const double *source,
+                       const void *src, void *dst, hipStream_t stream);
+hipError_t launch_tile_f64(const StepConfig &c, int region, int steps, const double *source,
+                           const void *src, void *dst, hipStream_t stream);
+hipError_t launch_tile_f32(const StepConfig &c, int region, int steps, const double *source,
+                           const void *src, void *dst, hipStream_t stream);
+hipError_t launch_tile_f16(const StepConfig &c, int region, int steps, const double *source,
+                           const void *src, void *dst, hipStream_t stream);
 // Per storage type and step count (lbm_strip_f64/f32/f16.hip, one object
 // per K): the single-lattice strip launch, the batched one and its
 // resident workgroups per CU.

@@ -1,0 +1,11 @@
+// lbm_tile_f32.hip -- tile kernels for F32 storage.
+#include "lbm_tile.h"
+
+namespace lbm {
+
+hipError_t launch_tile_f32(const StepConfig &c, int region, int steps, const double *source,
+                           const void *src, void *dst, hipStream_t stream) {
+  return launch_tile_storage<float>(c, region, steps, source, src, dst, stream);
+}
+
+}  // namespace lbm
