@@ -62,7 +62,10 @@ int lbm3_set_sponge(lbm3_handle *h, const double *chi, const lbm3_qref *q);
 int lbm3_set_sponge_separable(lbm3_handle *h, const double *chi_x, const double *chi_y,
                               const double *chi_z, int32_t combine, const lbm3_qref *q);
 
-/* Enqueue n >= 0 steps on the handle's stream. */
+/* Enqueue n >= 0 steps on the handle's stream: two per launch where that is
+ * faster (FP32 and FP64 lattices of about 10^6 cells or more, unless
+ * lbm3_set_tuning chose a shape), else one. The lattice buffer that is current
+ * afterwards is the one that n single-step launches leave. */
 int lbm3_step(lbm3_handle *h, int64_t n);
 int lbm3_sync(lbm3_handle *h);
 
@@ -74,7 +77,7 @@ int lbm3_set_populations(lbm3_handle *h, const double *f);
  * may be NULL); synchronises. */
 int lbm3_moments(lbm3_handle *h, double *rho, double *ux, double *uy, double *uz);
 
-/* Launch shape of the step: kernel 0 = one cell per thread (a workgroup
+/* Launch shape of the single steps, and from then on of every step: kernel 0 = one cell per thread (a workgroup
  * covers consecutive cells of one row); kernel 1 = two consecutive cells of
  * a row per thread (nx even); block = threads per workgroup, 64..512 in
  * steps of 64. Default: kernel 1 for FP16 storage when nx is even, else
@@ -86,7 +89,9 @@ int lbm3_get_tuning(lbm3_handle *h, int32_t *kernel, int32_t *block);
 /* Time every available launch shape on the handle's own lattice (reps >= 1
  * steps each, after one untimed step; the state is left as it was: each
  * candidate reads the current lattice and writes the other one), keep the
- * fastest and report it (any output may be NULL). Synchronises. */
+ * fastest and report it (any output may be NULL); two steps per launch are
+ * kept if they are faster still (the time is then theirs, the shape that of
+ * a call's single steps). Synchronises. */
 int lbm3_autotune(lbm3_handle *h, int32_t reps, int32_t *kernel, int32_t *block,
                   double *ms_per_step);
 

@@ -12,6 +12,7 @@
 #include <hip/hip_fp16.h>
 
 #include <cmath>
+#include <type_traits>
 
 #include "lbm3_device.h"
 #include "lbm_internal.h"
@@ -231,6 +232,224 @@ __global__ __launch_bounds__(512) void step3_rows(
   for (int i = 0; i < 15; ++i) __builtin_memcpy(dst + i * ps + cell0, &out[i], sizeof(out[i]));
 }
 
+// ---------------------------------------------------------------- two steps per launch
+// One launch advances the lattice by two steps, reading and writing it once.
+// A workgroup takes RX x RY columns of cells, one per thread, and marches in z: at
+// plane zz step 1 pulls from the lattice and collides, hands its in-plane
+// moving populations (12 of 15) to the neighbours through LDS, and step 2
+// collides at plane zz - 1 from what the threads hold of the planes zz - 2 (the
+// populations moving up), zz - 1 (those staying in their plane) and zz (those
+// moving down). Step 2 is valid on the inner (RX - 2) x (RY - 2) columns, which
+// are the outputs; a chunk of planes re-runs step 1 on one plane at each end.
+// The one-step kernel moves 120 B per update at 0.90 of a copy's rate, so
+// only less traffic helps; a chunk is tall because its two extra planes are
+// overhead (two3_depth).
+// Intermediate results are rounded through the storage format: the result is
+// bit-identical to two one-step launches.
+template <typename S, int RX, int RY>
+struct Two3 {
+  static constexpr int CELLS = RX * RY, NT = (CELLS + 63) / 64 * 64;
+  static constexpr int TX = RX - 2, TY = RY - 2;
+};
+
+template <typename C>
+struct Chi3 {
+  const C *field, *cx, *cy, *cz;
+  int mode;
+};
+
+// A value that is the same in all lanes, as a scalar.
+__device__ __forceinline__ float uniform(float v) {
+  return __builtin_bit_cast(float, __builtin_amdgcn_readfirstlane(__builtin_bit_cast(int, v)));
+}
+__device__ __forceinline__ double uniform(double v) {
+  const long long b = __builtin_bit_cast(long long, v);
+  const unsigned lo = __builtin_amdgcn_readfirstlane((int)b),
+                 hi = __builtin_amdgcn_readfirstlane((int)(b >> 32));
+  return __builtin_bit_cast(double, (long long)(((unsigned long long)hi << 32) | lo));
+}
+
+template <typename S, int VAR, int RX, int RY>
+__global__ __launch_bounds__((Two3<S, RX, RY>::NT)) void step3_two(
+    const S *__restrict__ src, S *__restrict__ dst, Lat3<S> L,
+    CollideParams3<typename Store<S>::C> p, Chi3<typename Store<S>::C> X, int depth, int ntx,
+    int nty, int per_xcd, int nwg) {
+  typedef typename Store<S>::C C;
+  typedef Two3<S, RX, RY> G;
+  __shared__ C lds[2][12][G::CELLS];
+  // Workgroup i runs on XCD i % 8: each XCD gets a contiguous run of tiles, x
+  // first, so that the memory lines that neighbours share (a row of a tile
+  // straddles one on each side) come from its L2.
+  const int v = (blockIdx.x & 7) * per_xcd + (blockIdx.x >> 3);
+  if (v >= nwg) return;
+  const int tile = v % (ntx * nty), chunk = v / (ntx * nty);
+  const int ty = tile / ntx, tx = tile - ty * ntx;
+  const int id = threadIdx.x;
+  const int ly = id / RX, lx = id - ly * RX;
+  const bool cell = G::CELLS % 64 == 0 || id < G::CELLS;
+  const int gx = tx * G::TX + lx - 1, gy = ty * G::TY + ly - 1;
+  const bool inner = cell && lx >= 1 && lx < RX - 1 && ly >= 1 && ly < RY - 1;
+  const bool out = inner && gx < L.nx && gy < L.ny;
+  // periodic columns (a tile may be wider than the lattice)
+  int x = gx % L.nx, y = gy % L.ny;
+  x = x < 0 ? x + L.nx : x;
+  y = y < 0 ? y + L.ny : y;
+  const int xm = x == 0 ? L.nx - 1 : x - 1, xp = x == L.nx - 1 ? 0 : x + 1;
+  const int ym = y == 0 ? L.ny - 1 : y - 1, yp = y == L.ny - 1 ? 0 : y + 1;
+  const unsigned pitch = (unsigned)L.pitch, E = sizeof(S);
+  // byte offsets within a slice of the columns that the pulls read, [cy][cx]
+  const unsigned o00 = (y * pitch + x) * E, om0 = (y * pitch + xm) * E, op0 = (y * pitch + xp) * E,
+                 o0m = (ym * pitch + x) * E, o0p = (yp * pitch + x) * E,
+                 omm = (ym * pitch + xm) * E, opm = (ym * pitch + xp) * E,
+                 omp = (yp * pitch + xm) * E, opp = (yp * pitch + xp) * E;
+  const int Z0 = chunk * depth, Z1 = min(Z0 + depth, L.nz);  // output planes
+  C mref[15];
+  if (VAR == V_I || VAR == V_II) {
+    ref_moments3(p, mref);
+#pragma unroll
+    for (int k = 0; k < 15; ++k) mref[k] = uniform(mref[k]);
+  }
+  C cxy = C(0);
+  if (X.mode == CHI_SEP_MAX) {
+    const C a = X.cx[x], b = X.cy[y];
+    cxy = a > b ? a : b;
+  } else if (X.mode == CHI_SEP_SUM) {
+    cxy = X.cx[x] + X.cy[y];
+  }
+  auto chi_of = [&](int z) {
+    switch (X.mode) {
+      case CHI_FIELD: return X.field[(int64_t)z * L.slice + o00 / E];
+      case CHI_SEP_MAX: {
+        const C d = X.cz[z];
+        return cxy > d ? cxy : d;
+      }
+      case CHI_SEP_SUM: return cxy + X.cz[z];
+      default: return C(0);
+    }
+  };
+  auto wrapz = [&](int z) { return z < 0 ? z + L.nz : (z >= L.nz ? z - L.nz : z); };
+  // A slice of a population is read and written through a buffer resource: its
+  // address is scalar and the lane's byte offset is used as it is, where a
+  // global access takes a 64-bit vector add (45 of 700 VALU instructions a plane).
+  const unsigned slice_bytes = (unsigned)(L.slice * E);
+  typedef typename std::conditional<sizeof(S) == 4, uint32_t, uint64_t>::type Bits;
+  auto rsrc = [&](const S *base) {
+    return __builtin_amdgcn_make_buffer_rsrc(const_cast<S *>(base), 0, (int)slice_bytes, 0x00020000);
+  };
+  auto ld = [&](int i, int z, unsigned off) {
+    const __amdgpu_buffer_rsrc_t rs = rsrc(src + i * L.ps + (int64_t)z * L.slice);
+    S v;
+    if constexpr (sizeof(S) == 4) {
+      const Bits w = __builtin_amdgcn_raw_buffer_load_b32(rs, (int)off, 0, 0);
+      __builtin_memcpy(&v, &w, sizeof(S));
+    } else {
+      const auto w = __builtin_amdgcn_raw_buffer_load_b64(rs, (int)off, 0, 0);
+      __builtin_memcpy(&v, &w, sizeof(S));
+    }
+    return Store<S>::load(&v, L.scale[i]);
+  };
+  auto st = [&](int i, int z, C v) {
+    const __amdgpu_buffer_rsrc_t rs = rsrc(dst + i * L.ps + (int64_t)z * L.slice);
+    S t;
+    Store<S>::store(&t, v, L.inv_scale[i]);
+    if constexpr (sizeof(S) == 4) {
+      Bits w;
+      __builtin_memcpy(&w, &t, sizeof(S));
+      __builtin_amdgcn_raw_buffer_store_b32(w, rs, (int)o00, 0, 0);
+    } else {
+      decltype(__builtin_amdgcn_raw_buffer_load_b64(rs, 0, 0, 0)) w;
+      __builtin_memcpy(&w, &t, sizeof(S));
+      __builtin_amdgcn_raw_buffer_store_b64(w, rs, (int)o00, 0, 0);
+    }
+  };
+  auto load = [&](C g[15], int zz) {  // the pulls of step 1 at plane zz
+    const int z0 = wrapz(zz), zm = wrapz(z0 - 1), zp = wrapz(z0 + 1);
+    g[0] = ld(0, z0, o00);
+    g[1] = ld(1, z0, om0);
+    g[2] = ld(2, z0, op0);
+    g[3] = ld(3, z0, o0m);
+    g[4] = ld(4, z0, o0p);
+    g[5] = ld(5, zm, o00);
+    g[6] = ld(6, zp, o00);
+    g[7] = ld(7, zm, omm);
+    g[8] = ld(8, zm, opm);
+    g[9] = ld(9, zm, omp);
+    g[10] = ld(10, zm, opp);
+    g[11] = ld(11, zp, omm);
+    g[12] = ld(12, zp, opm);
+    g[13] = ld(13, zp, omp);
+    g[14] = ld(14, zp, opp);
+  };
+  // One plane: step 1 at zz on the pulled values g (the next plane's go to
+  // `next`), step 2 at zz - 1 from `old` (moving up, of plane zz - 2, replaced by
+  // plane zz's) and `flat` (in-plane, of plane zz - 1, replaced likewise).
+  C chi1 = chi_of(wrapz(Z0 - 1)), chi2 = C(0);
+  C flat[5];
+  auto plane = [&](int zz, C g[15], C next[15], C old[5]) {
+    const C chi = chi1;
+    if (zz < Z1) {  // in flight while this plane collides
+      load(next, zz + 1);
+      chi1 = chi_of(wrapz(zz + 1));
+    }
+    collide3<C, VAR>(g, chi, p, mref);
+#pragma unroll
+    for (int i = 0; i < 15; ++i) g[i] = roundtrip<S>(g[i], L.scale[i], L.inv_scale[i]);
+    C(*buf)[G::CELLS] = lds[zz & 1];
+    if (cell) {
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        buf[i][id] = g[1 + i];
+        buf[4 + i][id] = g[7 + i];
+        buf[8 + i][id] = g[11 + i];
+      }
+    }
+    __syncthreads();
+    if (inner) {
+      C h[15];
+#pragma unroll
+      for (int i = 0; i < 5; ++i) h[i] = flat[i];
+      h[5] = old[0];
+#pragma unroll
+      for (int i = 1; i < 5; ++i) h[6 + i] = old[i];
+      flat[0] = g[0];
+      flat[1] = buf[0][id - 1];
+      flat[2] = buf[1][id + 1];
+      flat[3] = buf[2][id - RX];
+      flat[4] = buf[3][id + RX];
+      old[0] = g[5];
+      old[1] = buf[4][id - RX - 1];
+      old[2] = buf[5][id - RX + 1];
+      old[3] = buf[6][id + RX - 1];
+      old[4] = buf[7][id + RX + 1];
+      if (zz > Z0) {
+        h[6] = g[6];
+        h[11] = buf[8][id - RX - 1];
+        h[12] = buf[9][id - RX + 1];
+        h[13] = buf[10][id + RX - 1];
+        h[14] = buf[11][id + RX + 1];
+        collide3<C, VAR>(h, chi2, p, mref);
+        if (out) {
+#pragma unroll
+          for (int i = 0; i < 15; ++i) st(i, zz - 1, h[i]);
+        }
+      }
+    }
+    chi2 = chi;
+  };
+  // two planes per round, so that the two sets of pulled values and of values
+  // moving up keep their registers
+  C ga[15], gb[15], ua[5], ub[5];
+#pragma unroll
+  for (int k = 0; k < 5; ++k) flat[k] = ua[k] = ub[k] = C(0);
+  load(ga, Z0 - 1);
+  for (int zz = Z0 - 1;; zz += 2) {
+    plane(zz, ga, gb, ua);
+    if (zz + 1 > Z1) break;
+    plane(zz + 1, gb, ga, ub);
+    if (zz + 2 > Z1) break;
+  }
+}
+
 template <typename S, int VAR, int CHI, int V>
 static hipError_t launch_rows3(const Step3Config &c, const Lat3<S> &L,
                                const CollideParams3<typename Store<S>::C> &p, const void *src,
@@ -296,6 +515,94 @@ hipError_t launch_step3(const Step3Config &c, const void *src, void *dst, hipStr
     case 0: return step3_var<double>(c, src, dst, stream);
     case 1: return step3_var<float>(c, src, dst, stream);
     case 2: return step3_var<__half>(c, src, dst, stream);
+  }
+  return hipErrorInvalidValue;
+}
+
+// Columns of the two-step kernel's workgroups. Wide: one workgroup of 1024
+// threads (at most 128 registers, so FP32 only) per compute unit. Narrow: 512
+// threads, two per compute unit in FP32, one in FP64 (209 registers). From HBM
+// the wide one is faster (256^3 FP32 Type II: 59.0 against 51.5 G updates/s,
+// one-step 46.0; its counters: 4.05 TB/s with reads 1.29 x, VALU issue busy
+// 0.49, so neither fewer instructions nor streaming stores moved it), where the
+// pair of lattices stays in the last-level cache the narrow one (96^3 49.4
+// against 45.7, one-step 39.5). FP64 256^3: 31.1 against one-step 22.6.
+struct Two3Shape {
+  int rx, per_cu;  // columns in x of a workgroup (RY in y), workgroups per compute unit
+};
+constexpr int TWO3_RY = 15, TWO3_WIDE = 66, TWO3_NARROW = 34;
+
+static Two3Shape two3_shape(const Step3Config &c) {
+  if (c.storage == 0) return {TWO3_NARROW, 1};
+  const int64_t bytes = 2 * 15 * 4 * (int64_t)c.nx * c.ny * c.nz;
+  return bytes > (int64_t(256) << 20) ? Two3Shape{TWO3_WIDE, 1} : Two3Shape{TWO3_NARROW, 2};
+}
+
+int two3_depth(const Step3Config &c, double *use) {
+  if (use) *use = 0.0;
+  if (c.storage == 2) return 0;  // FP16 is bound by VALU issue at one step already
+  const int64_t eb = c.storage == 0 ? 8 : 4;
+  // a slice is addressed through one buffer range
+  if ((int64_t)c.pitch * c.ny * eb >= (int64_t(1) << 32) || c.nz < 2) return 0;
+  const Two3Shape w = two3_shape(c);
+  const int TX = w.rx - 2, TY = TWO3_RY - 2;
+  const int64_t tiles = (int64_t)((c.nx + TX - 1) / TX) * ((c.ny + TY - 1) / TY);
+  // chunk heights that give whole rounds of resident workgroups: the one that
+  // wastes least
+  const int64_t slots = (int64_t)w.per_cu * c.cus;
+  double best = 0.0;
+  int depth = 0;
+  for (int64_t chunks = 1; chunks <= c.nz; ++chunks) {
+    const int64_t d = (c.nz + chunks - 1) / chunks;
+    const int64_t wgs = tiles * ((c.nz + d - 1) / d), rounds = (wgs + slots - 1) / slots;
+    const double u = (double)c.nx * c.ny * c.nz / ((double)rounds * slots * TX * TY * (d + 2));
+    if (u > best) {
+      best = u;
+      depth = (int)d;
+    }
+    if (d <= 4) break;
+  }
+  if (use) *use = best;
+  return depth;
+}
+
+template <typename S, int VAR, int RX>
+static hipError_t launch_two_v(const Step3Config &c, const void *src, void *dst,
+                               hipStream_t stream) {
+  typedef typename Store<S>::C C;
+  typedef Two3<S, RX, TWO3_RY> G;
+  const int ntx = (c.nx + G::TX - 1) / G::TX, nty = (c.ny + G::TY - 1) / G::TY;
+  const int depth = two3_depth(c, nullptr);
+  const int64_t nwg = (int64_t)ntx * nty * ((c.nz + depth - 1) / depth), per = (nwg + 7) / 8;
+  if (8 * per > 0x7fffffff) return hipErrorInvalidValue;
+  const Chi3<C> X = {(const C *)c.chi_field, (const C *)c.chi_x, (const C *)c.chi_y,
+                     (const C *)c.chi_z, c.chi_mode};
+  step3_two<S, VAR, RX, TWO3_RY><<<dim3((unsigned)(8 * per)), dim3(G::NT), 0, stream>>>(
+      (const S *)src, (S *)dst, make_lat3<S>(c), make_params3<C>(c), X, depth, ntx, nty, (int)per,
+      (int)nwg);
+  return hipGetLastError();
+}
+
+template <typename S, int RX>
+static hipError_t launch_two_s(const Step3Config &c, const void *src, void *dst, hipStream_t s) {
+  switch (c.variant) {
+    case V_NONE: return launch_two_v<S, V_NONE, RX>(c, src, dst, s);
+    case V_I: return launch_two_v<S, V_I, RX>(c, src, dst, s);
+    case V_II: return launch_two_v<S, V_II, RX>(c, src, dst, s);
+    case V_III: return launch_two_v<S, V_III, RX>(c, src, dst, s);
+    case V_VISC: return launch_two_v<S, V_VISC, RX>(c, src, dst, s);
+  }
+  return hipErrorInvalidValue;
+}
+
+hipError_t launch_two3(const Step3Config &c, const void *src, void *dst, hipStream_t stream) {
+  if (two3_depth(c, nullptr) < 1) return hipErrorInvalidValue;
+  switch (c.storage) {
+    case 0: return launch_two_s<double, TWO3_NARROW>(c, src, dst, stream);
+    case 1:
+      return two3_shape(c).rx == TWO3_WIDE
+                 ? launch_two_s<float, TWO3_WIDE>(c, src, dst, stream)
+                 : launch_two_s<float, TWO3_NARROW>(c, src, dst, stream);
   }
   return hipErrorInvalidValue;
 }

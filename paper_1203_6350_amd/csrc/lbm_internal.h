@@ -223,8 +223,14 @@ struct Step3Config {
   const void *chi_x, *chi_y, *chi_z;
   int kernel;            // 0: one cell per thread; 1: two cells of a row per thread (nx even)
   int block;             // threads per workgroup, 64..512, a multiple of 64
+  int cus;               // compute units of the device
 };
 hipError_t launch_step3(const Step3Config &c, const void *src, void *dst, hipStream_t stream);
+// Two steps in one launch (FP32 and FP64). two3_depth: planes per workgroup, or
+// 0 where the kernel does not take the lattice; *use (may be NULL): the share
+// of the launch's capacity that computes cells.
+int two3_depth(const Step3Config &c, double *use);
+hipError_t launch_two3(const Step3Config &c, const void *src, void *dst, hipStream_t stream);
 hipError_t launch_init3(const Step3Config &c, const double *rho, const double *ux,
                         const double *uy, const double *uz, void *dst, hipStream_t stream);
 hipError_t launch_setpop3(const Step3Config &c, const double *f, void *dst, hipStream_t stream);
