@@ -17,14 +17,25 @@
 // exceptional shifts after 10 and 20 stalled sweeps). Eigenvalues are
 // returned sorted by (-|lambda|, arg lambda).
 //
-// Each lane holds its wavenumber's matrix in registers (81 complex values,
-// every index fixed at compile time: the loops are fully unrolled), so the
-// solve runs from the register file at the VALU rate. The QR sweeps are
-// wave-wide: every lane runs the same instruction stream over the full
-// 9 x 9 matrix, and a lane's own state (the bottom row of its active window,
-// its shift, its stall counter) enters only through predicates: rotations
-// outside its window are the identity. A wave ends when all its lanes have
-// converged.
+// Each lane holds its wavenumber's matrix in registers (every index fixed at
+// compile time: the loops are fully unrolled). The reduction leaves the
+// subdiagonal real and the sweeps keep it so, which makes every rotation 12
+// operations a pair instead of 16. The QR sweeps are wave-wide and run level by
+// level: at level h (8 down to 2) a sweep works on rows and columns 0..h only,
+// and a lane takes part while the bottom of its active window is h or h - 1, so
+// that the entries at the bottom are one of two fixed positions; a lane
+// further ahead waits, masked off. With that slack of one a wave needs no more
+// sweeps than lanes running freely would (29 a wave, 26 a lane on MRT sets
+// with flow), and the sweep has neither gathers nor predicates. Complex
+// products are fused multiply-adds.
+//
+// Bound by VALU issue at one wave per SIMD (512 registers): at level 8 half of
+// the 2330 instructions of a sweep are FP64, a third move the window between
+// the two halves of the register file, which hold it only together. One
+// window 0..8 in every sweep with the entries at a lane's own bottom selected
+// over all positions, and complex subdiagonals, took 15.7 ms for 64 sets x
+// 256^2 wavenumbers (268 M eigenproblems/s); the levels take 9.8 ms, with the
+// real subdiagonal 8.3 ms (505 M/s).
 #include "lbm_device.h"
 #include "lbm_internal.h"
 
@@ -127,12 +138,6 @@ __device__ void eig2(cplx a, cplx b, cplx c, cplx d, cplx &l1, cplx &l2) {
   l2 = sub(d, divc(bc, z1));
 }
 
-__device__ __forceinline__ bool before(cplx a, cplx b) {
-  const double ma = absc(a), mb = absc(b);
-  if (ma != mb) return ma > mb;
-  return atan2(a.im, a.re) < atan2(b.im, b.re);
-}
-
 }  // namespace
 
 // 1/sqrt(x) for x > 0 to about one ulp: the hardware estimate refined by
@@ -155,60 +160,62 @@ struct RegMat {
   }
 };
 
-// Element (i, j) of the tridiagonal band (|i - j| <= 1) at the lane's own
-// (run-time) indices, read by selecting over the static positions.
-__device__ __forceinline__ cplx pick(const RegMat &H, int i, int j) {
-  cplx v = mk(0.0, 0.0);
-#pragma unroll
-  for (int a = 0; a < N; ++a)
-#pragma unroll
-    for (int b = 0; b < N; ++b)
-      if (b >= a - 1 && b <= a + 1) {  // the sub-, main and superdiagonal are all we read
-        const bool hit = a == i && b == j;
-        v.re = hit ? H.r[a][b] : v.re;
-        v.im = hit ? H.m[a][b] : v.im;
-      }
-  return v;
+// a b + c, a b, conj(a) b + c and c - a b with fused multiply-adds.
+__device__ __forceinline__ cplx cfma(cplx a, cplx b, cplx c) {
+  return mk(__builtin_fma(a.re, b.re, __builtin_fma(-a.im, b.im, c.re)),
+            __builtin_fma(a.re, b.im, __builtin_fma(a.im, b.re, c.im)));
+}
+__device__ __forceinline__ cplx cmul(cplx a, cplx b) {
+  return mk(__builtin_fma(a.re, b.re, -(a.im * b.im)), __builtin_fma(a.re, b.im, a.im * b.re));
+}
+__device__ __forceinline__ cplx neg(cplx a) { return mk(-a.re, -a.im); }
+__device__ __forceinline__ double norm2(cplx a) { return __builtin_fma(a.re, a.re, a.im * a.im); }
+__device__ __forceinline__ cplx pick2(bool first, cplx a, cplx b) {
+  return mk(first ? a.re : b.re, first ? a.im : b.im);
 }
 
-// Householder reduction to upper Hessenberg form, H <- Q^H H Q.
+// |z|, and its phase z/|z| (1 for z = 0, or where |z|^2 is not positive).
+__device__ __forceinline__ double polar(cplx z, cplx &e) {
+  const double n2 = norm2(z);
+  const bool on = n2 > 0.0;
+  const double ir = on ? rsqrt_f64(n2) : 0.0;
+  e = mk(on ? z.re * ir : 1.0, z.im * ir);
+  return n2 * ir;
+}
+
+// Householder reduction to upper Hessenberg form with a real subdiagonal. The
+// reflection of column k, x = H(k+1.., k), is I - tau v v^H with v = x/|x| + g e1,
+// g = +-1 of Re x0's sign and tau = g conj(v0)/|v0|^2: it maps x to -g |x| e1, and
+// |v0| >= 1. H <- (I - tau v v^H) H (I - tau v v^H)^H.
 __device__ __forceinline__ void hessenberg_reg(RegMat &H) {
 #pragma unroll
   for (int k = 0; k < N - 2; ++k) {
     double xn2 = 0.0;
 #pragma unroll
-    for (int i = k + 1; i < N; ++i) xn2 += H.r[i][k] * H.r[i][k] + H.m[i][k] * H.m[i][k];
-    const double xn = sqrt(xn2);
-    const cplx x0 = H.at(k + 1, k);
-    const double ax0 = absc(x0);
-    const cplx ph = ax0 > 0.0 ? scal(1.0 / ax0, x0) : mk(1.0, 0.0);
-    const cplx alpha = scal(-xn, ph);  // -e^{i arg x0} ||x||
-    // v = x - alpha e1, normalised (v = 0, the identity, for a zero column)
+    for (int i = k + 1; i < N; ++i)
+      xn2 = __builtin_fma(H.r[i][k], H.r[i][k], __builtin_fma(H.m[i][k], H.m[i][k], xn2));
+    const bool on = xn2 > 0.0;  // a zero column stays as it is
+    const double ixn = on ? rsqrt_f64(xn2) : 0.0;
+    const double g = H.r[k + 1][k] >= 0.0 ? 1.0 : -1.0;
     cplx v[N];
-    double vn2 = 0.0;
 #pragma unroll
-    for (int i = k + 1; i < N; ++i) {
-      v[i] = i == k + 1 ? sub(x0, alpha) : H.at(i, k);
-      vn2 += v[i].re * v[i].re + v[i].im * v[i].im;
-    }
-    const double inv = vn2 > 0.0 ? rsqrt_f64(vn2) : 0.0;
-#pragma unroll
-    for (int i = k + 1; i < N; ++i) v[i] = scal(inv, v[i]);
+    for (int i = k + 1; i < N; ++i) v[i] = scal(ixn, H.at(i, k));
+    v[k + 1].re += g;
+    const cplx tau = scal(on ? g / norm2(v[k + 1]) : 0.0, conjc(v[k + 1]));
     // left: rows k+1.., columns k+1..
 #pragma unroll
     for (int j = k + 1; j < N; ++j) {
       cplx w = mk(0.0, 0.0);
 #pragma unroll
-      for (int i = k + 1; i < N; ++i) w = add(w, mul(conjc(v[i]), H.at(i, j)));
-      w = scal(2.0, w);
+      for (int i = k + 1; i < N; ++i) w = cfma(conjc(v[i]), H.at(i, j), w);
+      w = neg(cmul(tau, w));
 #pragma unroll
-      for (int i = k + 1; i < N; ++i) H.put(i, j, sub(H.at(i, j), mul(v[i], w)));
+      for (int i = k + 1; i < N; ++i) H.put(i, j, cfma(v[i], w, H.at(i, j)));
     }
-    // column k below the subdiagonal: the reflection maps x to alpha e1
-    // (with v = 0 the column was zero below x0 already); the entries below
-    // the subdiagonal become compile-time zeros, which frees their registers
-    // for the QR sweeps (they never read them)
-    H.put(k + 1, k, vn2 > 0.0 ? alpha : x0);
+    // column k: (-g |x|, 0, ...); the entries below the subdiagonal become
+    // compile-time zeros, which frees their registers for the QR sweeps
+    // (they never read them)
+    H.put(k + 1, k, mk(-g * (xn2 * ixn), 0.0));
 #pragma unroll
     for (int i = k + 2; i < N; ++i) H.put(i, k, mk(0.0, 0.0));
     // right: all rows, columns k+1..
@@ -216,130 +223,190 @@ __device__ __forceinline__ void hessenberg_reg(RegMat &H) {
     for (int i = 0; i < N; ++i) {
       cplx w = mk(0.0, 0.0);
 #pragma unroll
-      for (int j = k + 1; j < N; ++j) w = add(w, mul(H.at(i, j), v[j]));
-      w = scal(2.0, w);
+      for (int j = k + 1; j < N; ++j) w = cfma(H.at(i, j), v[j], w);
+      w = neg(cmul(conjc(tau), w));
 #pragma unroll
-      for (int j = k + 1; j < N; ++j) H.put(i, j, sub(H.at(i, j), mul(w, conjc(v[j]))));
+      for (int j = k + 1; j < N; ++j) H.put(i, j, cfma(w, conjc(v[j]), H.at(i, j)));
     }
   }
-}
-
-// Rotation [c s; -conj(s) conj(c)] with c = conj(x)/r, s = conj(y)/r,
-// r = sqrt(|x|^2 + |y|^2), which maps (x, y) to (r, 0); the identity when
-// inactive or when x = y = 0.
-__device__ __forceinline__ void givens(cplx x, cplx y, bool act, cplx &c, cplx &s) {
-  const double n2 = x.re * x.re + x.im * x.im + y.re * y.re + y.im * y.im;
-  const bool on = act && n2 > 0.0;
-  const double ir = on ? rsqrt_f64(n2) : 0.0;
-  c = on ? mk(x.re * ir, -x.im * ir) : mk(1.0, 0.0);
-  s = on ? mk(y.re * ir, -y.im * ir) : mk(0.0, 0.0);
-}
-
-// H <- H G^H on columns q, q + 1 for rows 0..rmax, G = [c s; -conj(s) conj(c)].
-__device__ __forceinline__ void right_rot(RegMat &H, int q, int rmax, cplx c, cplx s) {
+  // the last subdiagonal's phase e: row N - 1 times conj(e), column N - 1 times e
+  const cplx y = H.at(N - 1, N - 2);
+  cplx e;
+  H.put(N - 1, N - 2, mk(polar(y, e), 0.0));
 #pragma unroll
-  for (int i = 0; i <= rmax; ++i) {
-    const cplx t1 = H.at(i, q), t2 = H.at(i, q + 1);
-    H.put(i, q, add(mul(t1, conjc(c)), mul(t2, conjc(s))));
-    H.put(i, q + 1, sub(mul(t2, c), mul(t1, s)));
-  }
+  for (int i = 0; i < N - 1; ++i) H.put(i, N - 1, cmul(e, H.at(i, N - 1)));
 }
 
-constexpr int VN_MAX_SWEEPS = 40 * N;
+// Wilkinson shift of [a b; c d], c real: its eigenvalue nearer d, d - bc / (p + y) with
+// p = (a - d)/2, y = sqrt(p^2 + bc) on p's side (so |p + y| >= |p - y|); d where
+// that is not finite. It steers the convergence only, so the reciprocals
+// are refined estimates.
+__device__ __forceinline__ cplx shift_of(cplx a, cplx b, double c, cplx d) {
+  const cplx p = scal(0.5, sub(a, d));
+  const cplx bc = scal(c, b);
+  const cplx q = cfma(p, p, bc);
+  const double r2 = norm2(q);
+  const double r = r2 > 0.0 ? r2 * rsqrt_f64(r2) : 0.0;
+  const double t2 = 0.5 * (r + fabs(q.re));
+  const double it = t2 > 0.0 ? rsqrt_f64(t2) : 0.0;
+  const double t = t2 * it, u = 0.5 * q.im * it;  // |q.im| / (2 t)
+  cplx y = q.re >= 0.0 ? mk(t, u) : mk(fabs(u), copysign(t, q.im));
+  if (__builtin_fma(p.re, y.re, p.im * y.im) < 0.0) y = neg(y);
+  const cplx z = add(p, y);
+  const double z2 = norm2(z);
+  const double e = __builtin_amdgcn_rcp(z2);
+  const double iz = e * __builtin_fma(-z2, e, 2.0);
+  const cplx m = cmul(scal(iz, bc), conjc(z));
+  return z2 > 0.0 && __builtin_isfinite(m.re) && __builtin_isfinite(m.im) ? sub(d, m) : d;
+}
 
-// Eigenvalues of the upper Hessenberg H by single-shift QR sweeps on the
-// lane's active window 0..hi (Wilkinson shift from its trailing 2 x 2,
-// exceptional shifts after 10 and 20 stalled sweeps; the bottom eigenvalue
-// deflates when its subdiagonal is negligible). Returns false if the lane
-// did not converge within VN_MAX_SWEEPS sweeps.
-__device__ __forceinline__ bool qr_reg(RegMat &H, double2 *ev, int stride) {
+// conj(c) a + s b and c b - s a, s real: a rotation of the pair (a, b).
+__device__ __forceinline__ cplx rot1(cplx c, double s, cplx a, cplx b) {
+  return mk(__builtin_fma(s, b.re, __builtin_fma(c.re, a.re, c.im * a.im)),
+            __builtin_fma(s, b.im, __builtin_fma(c.re, a.im, -(c.im * a.re))));
+}
+__device__ __forceinline__ cplx rot2(cplx c, double s, cplx a, cplx b) {
+  return mk(__builtin_fma(-s, a.re, __builtin_fma(c.re, b.re, -(c.im * b.im))),
+            __builtin_fma(-s, a.im, __builtin_fma(c.re, b.im, c.im * b.re)));
+}
+
+// H <- H G^H on columns q, q + 1, G = [c s; -s conj(c)], where row q + 1 holds
+// (0, r) with r real.
+__device__ __forceinline__ void right_rot(RegMat &H, int q, cplx c, double s) {
+#pragma unroll
+  for (int i = 0; i <= q; ++i) {
+    const cplx a = H.at(i, q), b = H.at(i, q + 1);
+    H.put(i, q, rot1(c, s, a, b));
+    H.put(i, q + 1, rot2(c, s, a, b));
+  }
+  const double r = H.r[q + 1][q + 1];
+  H.put(q + 1, q, mk(s * r, 0.0));
+  H.put(q + 1, q + 1, scal(r, c));
+}
+
+constexpr int VN_MAX_SWEEPS = 40 * N;  // a lane's own, over all its eigenvalues
+
+// The entries of the level's window as new values. Without it an entry is one
+// value from the reduction to the last sweep, and what the reduction (324
+// registers) spills stays spilled in sweeps that would fit.
+__device__ __forceinline__ double detach(double x) {
+  double y;
+  asm("v_mov_b64 %0, %1" : "=v"(y) : "v"(x));
+  return y;
+}
+template <int h>
+__device__ __forceinline__ void detach_window(RegMat &H) {
+#pragma unroll
+  for (int i = 0; i <= h; ++i)
+#pragma unroll
+    for (int j = i > 0 ? i - 1 : 0; j <= h; ++j) {
+      H.r[i][j] = detach(H.r[i][j]);
+      H.m[i][j] = detach(H.m[i][j]);
+    }
+}
+
+// QR sweeps of level h: until no lane's active window 0..hi ends at h (each
+// sweep: Wilkinson shift from the window's trailing 2 x 2, exceptional
+// shifts after 10 and 20 stalled sweeps; a bottom eigenvalue deflates when its
+// subdiagonal is negligible, two checks per sweep). A lane that has used up its
+// sweeps (one with a NaN does) leaves with hi = -1 and the wave goes on without
+// it; every sweep is one of some lane at h, so the loop ends.
+template <int h>
+__device__ __forceinline__ void qr_level(RegMat &H, int &hi, int &it, int &sweeps, double2 *ev,
+                                         int stride) {
+  constexpr int l = h > 2 ? h - 1 : h;  // the lowest window end that takes part
   const double eps = 2.220446049250313e-16;
-  int hi = N - 1, it = 0;
-  bool done = false;
-  for (int sweep = 0; sweep < VN_MAX_SWEEPS; ++sweep) {
-    // deflate converged eigenvalues at the bottom (two checks per sweep)
+  detach_window<h>(H);
+  for (;;) {
 #pragma unroll
     for (int rep = 0; rep < 2; ++rep) {
-      if (!done) {
-        if (hi <= 0) {
-          ev[0] = make_double2(H.r[0][0], H.m[0][0]);
-          done = true;
-        } else {
-          const cplx d = pick(H, hi, hi - 1);
-          const cplx a = pick(H, hi - 1, hi - 1), b = pick(H, hi, hi);
-          if (abs1(d) <= eps * (abs1(a) + abs1(b))) {
-            ev[hi * stride] = make_double2(b.re, b.im);
-            --hi;
-            it = 0;
-          } else if (hi == 1) {
-            cplx l0, l1;
-            eig2(a, pick(H, 0, 1), d, b, l0, l1);
-            ev[0] = make_double2(l0.re, l0.im);
-            ev[stride] = make_double2(l1.re, l1.im);
-            done = true;
-          }
-        }
+      const bool top = hi == h;
+      const double d = top ? H.r[h][h - 1] : H.r[l][l - 1];
+      const cplx a = pick2(top, H.at(h - 1, h - 1), H.at(l - 1, l - 1));
+      const cplx b = pick2(top, H.at(h, h), H.at(l, l));
+      if (hi >= l && fabs(d) <= eps * (abs1(a) + abs1(b))) {
+        ev[hi * stride] = make_double2(b.re, b.im);
+        --hi;
+        it = 0;
       }
     }
-    if (__all(done)) break;
-    // shift of the active window
-    cplx mu = mk(0.0, 0.0);
-    if (!done) {
-      const cplx a = pick(H, hi - 1, hi - 1), b = pick(H, hi - 1, hi);
-      const cplx c = pick(H, hi, hi - 1), d = pick(H, hi, hi);
-      if (it == 10 || it == 20) {
-        const double e2 = hi >= 2 ? fabs(pick(H, hi - 1, hi - 2).re) : 0.0;
-        mu = add(d, mk(0.75 * fabs(c.re) + e2, 0.0));
-      } else {
-        cplx l1, l2;
-        eig2(a, b, c, d, l1, l2);
-        mu = abs1(sub(l1, d)) <= abs1(sub(l2, d)) ? l1 : l2;
+    if (hi >= l && sweeps >= VN_MAX_SWEEPS) hi = -1;
+    if (!__any(hi == h)) return;
+    if (hi < l) continue;
+    const bool top = hi == h;
+    const double c = top ? H.r[h][h - 1] : H.r[l][l - 1];
+    const cplx d = pick2(top, H.at(h, h), H.at(l, l));
+    cplx mu = shift_of(pick2(top, H.at(h - 1, h - 1), H.at(l - 1, l - 1)),
+                       pick2(top, H.at(h - 1, h), H.at(l - 1, l)), c, d);
+    if (it == 10 || it == 20)
+      mu = mk(d.re + __builtin_fma(0.75, fabs(c), fabs(top || l < 2 ? H.r[h - 1][h - 2]
+                                                                    : H.r[l - 1][l - 2])), d.im);
+    ++it;
+    ++sweeps;
+    // H - mu I on the window; what lies below it (row and column h of a window
+    // that ends at h - 1) is no longer read, and takes part in any way
+#pragma unroll
+    for (int i = 0; i <= h; ++i) H.put(i, i, sub(H.at(i, i), mu));
+    // R = G_{h-1} ... G_0 (H - mu I), then R G_0^H ... G_{h-1}^H, with each
+    // right rotation applied once the next left one is: the left rotation k
+    // reads H(k, k) before the right rotation k - 1 changes it. A left rotation
+    // maps its own column's pair (x, y) to (r, 0), r real. With y = 0 at the
+    // window's end it takes R's last diagonal entry to its modulus, which
+    // keeps the subdiagonal real.
+    cplx cp = mk(1.0, 0.0);
+    double sp = 0.0;
+#pragma unroll
+    for (int k = 0; k < h; ++k) {
+      const cplx x = H.at(k, k);
+      const double y = k < h - 1 || top ? H.r[k + 1][k] : 0.0;
+      const double n2 = __builtin_fma(y, y, norm2(x));
+      const bool on = n2 > 0.0;
+      const double ir = on ? rsqrt_f64(n2) : 0.0;
+      const cplx cc = mk(on ? x.re * ir : 1.0, x.im * ir);  // conj(c)
+      const double s = y * ir;
+      H.put(k, k, mk(n2 * ir, 0.0));
+#pragma unroll
+      for (int j = k + 1; j <= h; ++j) {
+        const cplx a = H.at(k, j), b = H.at(k + 1, j);
+        H.put(k, j, rot1(cc, s, a, b));
+        H.put(k + 1, j, rot2(cc, s, a, b));
       }
-      ++it;
+      if (k > 0) right_rot(H, k - 1, cp, sp);
+      cp = conjc(cc);
+      sp = s;
     }
-    // H - mu I on the window
+    cplx e;
+    H.put(h, h, mk(polar(H.at(h, h), e), 0.0));
+    right_rot(H, h - 1, cp, sp);
 #pragma unroll
-    for (int i = 0; i < N; ++i) {
-      const bool in = !done && i <= hi;
-      H.r[i][i] -= in ? mu.re : 0.0;
-      H.m[i][i] -= in ? mu.im : 0.0;
-    }
-    // R = G_{hi-1} ... G_0 (H - mu I), then R G_0^H ... G_{hi-1}^H, with
-    // each right rotation applied once the next left one is: the left
-    // rotation k reads H(k, k) before the right rotation k - 1 changes it.
-    // Rotations that no lane of the wave needs (k >= hi in every lane) are
-    // skipped as a whole; a pending right rotation is applied first.
-    cplx cp = mk(1.0, 0.0), sp = mk(0.0, 0.0);
-    bool pend = false;
+    for (int i = 0; i <= h; ++i) H.put(i, h, cmul(e, H.at(i, h)));
 #pragma unroll
-    for (int k = 0; k < N - 1; ++k) {
-      if (__any(!done && k < hi)) {
-        cplx c, s;
-        givens(H.at(k, k), H.at(k + 1, k), !done && k < hi, c, s);
-#pragma unroll
-        for (int j = k; j < N; ++j) {
-          const cplx t1 = H.at(k, j), t2 = H.at(k + 1, j);
-          H.put(k, j, add(mul(c, t1), mul(s, t2)));
-          H.put(k + 1, j, sub(mul(conjc(c), t2), mul(conjc(s), t1)));
-        }
-        if (k > 0) right_rot(H, k - 1, k, cp, sp);
-        cp = c;
-        sp = s;
-        pend = true;
-      } else if (pend) {
-        right_rot(H, k - 1, k, cp, sp);
-        pend = false;
-      }
-    }
-    if (pend) right_rot(H, N - 2, N - 1, cp, sp);
-#pragma unroll
-    for (int i = 0; i < N; ++i) {
-      const bool in = !done && i <= hi;
-      H.r[i][i] += in ? mu.re : 0.0;
-      H.m[i][i] += in ? mu.im : 0.0;
-    }
+    for (int i = 0; i <= h; ++i) H.put(i, i, add(H.at(i, i), mu));
   }
-  return done;
+}
+
+template <int h>
+__device__ __forceinline__ void qr_levels(RegMat &H, int &hi, int &it, int &sweeps, double2 *ev,
+                                          int stride) {
+  qr_level<h>(H, hi, it, sweeps, ev, stride);
+  if constexpr (h > 2) qr_levels<h - 1>(H, hi, it, sweeps, ev, stride);
+}
+
+// Eigenvalues of the upper Hessenberg H. Returns false if the lane did not
+// converge within VN_MAX_SWEEPS sweeps.
+__device__ __forceinline__ bool qr_reg(RegMat &H, double2 *ev, int stride) {
+  int hi = N - 1, it = 0, sweeps = 0;
+  qr_levels<N - 1>(H, hi, it, sweeps, ev, stride);
+  if (hi == 1) {
+    const cplx a = H.at(0, 0), b = H.at(0, 1), c = H.at(1, 0), d = H.at(1, 1);
+    cplx l0 = a, l1 = d;
+    if (abs1(c) > 2.220446049250313e-16 * (abs1(a) + abs1(d))) eig2(a, b, c, d, l0, l1);
+    ev[0] = make_double2(l0.re, l0.im);
+    ev[stride] = make_double2(l1.re, l1.im);
+  } else if (hi == 0) {
+    ev[0] = make_double2(H.r[0][0], H.m[0][0]);
+  }
+  return hi >= 0;
 }
 
 // One wavenumber per lane, 64 lanes per workgroup (one wave); blockIdx.y
@@ -398,25 +465,31 @@ __global__ __launch_bounds__(64) void vn_kernel(const VnParamsDev *__restrict__ 
   const bool ok = qr_reg(H, evs + t, 64);
   if (kidx >= nk) return;
   cplx ev[N];
+  double mag[N];
 #pragma unroll
   for (int i = 0; i < N; ++i) {
     const double2 v = evs[i * 64 + t];
     ev[i] = ok ? mk(v.x, v.y) : mk(__builtin_nan(""), __builtin_nan(""));
+    mag[i] = absc(ev[i]);
   }
-  // insertion sort by (-|lambda|, arg lambda)
-  for (int i = 1; i < N; ++i) {
-    const cplx v = ev[i];
-    int j = i - 1;
-    while (j >= 0 && before(v, ev[j])) {
-      ev[j + 1] = ev[j];
-      --j;
+  // insertion sort by (-|lambda|, arg lambda), as a network of neighbours
+#pragma unroll
+  for (int i = 1; i < N; ++i)
+#pragma unroll
+    for (int j = i; j > 0; --j) {
+      bool swap = mag[j] > mag[j - 1];
+      if (mag[j] == mag[j - 1])
+        swap = atan2(ev[j].im, ev[j].re) < atan2(ev[j - 1].im, ev[j - 1].re);
+      const cplx u = ev[j - 1], v = ev[j];
+      ev[j - 1] = swap ? v : u;
+      ev[j] = swap ? u : v;
+      const double mu = mag[j - 1], mv = mag[j];
+      mag[j - 1] = swap ? mv : mu;
+      mag[j] = swap ? mu : mv;
     }
-    ev[j + 1] = v;
-  }
-  for (int i = 0; i < N; ++i) {
-    eig[(out * 9 + i) * 2] = ev[i].re;
-    eig[(out * 9 + i) * 2 + 1] = ev[i].im;
-  }
+#pragma unroll
+  for (int i = 0; i < N; ++i)
+    ((double2 *)eig)[out * 9 + i] = make_double2(ev[i].re, ev[i].im);
 }
 
 hipError_t launch_vn(const VnParamsDev *params_dev, int nparams, int64_t nk,
