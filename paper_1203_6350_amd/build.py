@@ -17,7 +17,8 @@ OUT = os.path.join(HERE, "liblbm.so")
 # (source, extra flags, object name): the strip kernels compile once per
 # step count K, so that the largest translation units build side by side
 SOURCES = [(f, [], f.rsplit(".", 1)[0]) for f in
-           ("lbm_api.cpp", "lbm_kernels.hip", "lbm_vn.hip", "lbm_batch.hip", "lbm3_kernels.hip")]
+           ("lbm_api.cpp", "lbm_kernels.hip", "lbm_vn.hip", "lbm_batch.hip", "lbm3_kernels.hip",
+            "lbm_readout.cpp")]
 SOURCES += [("lbm_strip_%s.hip" % st, ["-DLBM_STRIP_ONLY_K=%d" % k], "lbm_strip_%s_k%d" % (st, k))
             for st in ("f32", "f64", "f16") for k in (4, 3, 2)]
 SOURCES += [("lbm_tile_%s.hip" % st, [], "lbm_tile_%s" % st) for st in ("f32", "f64", "f16")]

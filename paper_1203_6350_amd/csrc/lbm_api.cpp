@@ -97,6 +97,7 @@ struct lbm_handle {
   double *diag_out = nullptr;
   int64_t steps = 0;
   size_t lat_bytes = 0;
+  lbm::ReadStage read;        // pinned memory of large read-outs (lattices of its own only)
   int device = 0;
   int cus = 256;              // compute units of the device
   bool shape_set = false;     // lbm_set_tuning or lbm_autotune chose the launch shape
@@ -773,9 +774,12 @@ int lbm_moments(lbm_handle *h, double *rho, double *ux, double *uy) {
   double *d = nullptr;
   HIP_TRY(hipMallocAsync((void **)&d, sizeof(double) * 3 * N, h->stream), "hipMallocAsync(moments)");
   hipError_t e = lbm::launch_moments(h->cfg, h->lat[h->cur], d, d + N, d + 2 * N, h->stream);
-  if (e == hipSuccess && rho) e = hipMemcpyAsync(rho, d, sizeof(double) * N, hipMemcpyDeviceToHost, h->stream);
-  if (e == hipSuccess && ux) e = hipMemcpyAsync(ux, d + N, sizeof(double) * N, hipMemcpyDeviceToHost, h->stream);
-  if (e == hipSuccess && uy) e = hipMemcpyAsync(uy, d + 2 * N, sizeof(double) * N, hipMemcpyDeviceToHost, h->stream);
+  double *outs[3] = {rho, ux, uy};
+  lbm::ReadPart parts[3];
+  int n = 0;
+  for (int k = 0; k < 3; ++k)
+    if (outs[k]) parts[n++] = {outs[k], d + k * N, sizeof(double) * (size_t)N};
+  if (e == hipSuccess) e = lbm::read_out(h->own_lat ? &h->read : nullptr, parts, n, h->stream);
   (void)hipFreeAsync(d, h->stream);
   if (e == hipSuccess) e = hipStreamSynchronize(h->stream);
   if (e != hipSuccess) return hip_fail(e, "moments");
@@ -825,7 +829,8 @@ int lbm_get_populations(lbm_handle *h, double *f) {
   double *d = nullptr;
   HIP_TRY(hipMallocAsync((void **)&d, sizeof(double) * 9 * N, h->stream), "hipMallocAsync(populations)");
   hipError_t e = lbm::launch_get_populations(h->cfg, h->lat[h->cur], d, h->stream);
-  if (e == hipSuccess) e = hipMemcpyAsync(f, d, sizeof(double) * 9 * N, hipMemcpyDeviceToHost, h->stream);
+  const lbm::ReadPart part = {f, d, sizeof(double) * 9 * (size_t)N};
+  if (e == hipSuccess) e = lbm::read_out(h->own_lat ? &h->read : nullptr, &part, 1, h->stream);
   (void)hipFreeAsync(d, h->stream);
   if (e == hipSuccess) e = hipStreamSynchronize(h->stream);
   if (e != hipSuccess) return hip_fail(e, "get_populations");
@@ -859,7 +864,9 @@ int lbm_save_state(lbm_handle *h, void *host, size_t bytes) {
   if (!h || !host) return fail(LBM_EINVAL, "NULL argument");
   if (bytes != h->lat_bytes + sizeof(int64_t)) return fail(LBM_EINVAL, "state buffer size mismatch");
   HIP_TRY(hipStreamSynchronize(h->stream), "hipStreamSynchronize");
-  HIP_TRY(hipMemcpy(host, h->lat[h->cur], h->lat_bytes, hipMemcpyDeviceToHost), "hipMemcpy(state)");
+  const lbm::ReadPart part = {host, h->lat[h->cur], h->lat_bytes};
+  HIP_TRY(lbm::read_out(h->own_lat ? &h->read : nullptr, &part, 1, h->stream), "hipMemcpy(state)");
+  HIP_TRY(hipStreamSynchronize(h->stream), "hipStreamSynchronize");
   std::memcpy((char *)host + h->lat_bytes, &h->steps, sizeof(int64_t));
   return LBM_OK;
 }
@@ -1055,6 +1062,7 @@ void lbm_destroy(lbm_handle *h) {
     (void)hipStreamSynchronize(h->stream);
     for (int k = 0; k < 2; ++k)
       if (h->lat[k]) (void)hipFree(h->lat[k]);
+    lbm::read_stage_free(h->read);
   }
   delete h;
 }
@@ -1903,6 +1911,7 @@ struct lbm3_handle {
   void *chi_field = nullptr, *chi_x = nullptr, *chi_y = nullptr, *chi_z = nullptr;
   int64_t steps = 0;
   size_t lat_bytes = 0;
+  lbm::ReadStage read;        // pinned memory of large read-outs
   int64_t ncell = 0;
   bool shape_set = false;     // lbm3_set_tuning chose the launch shape: one step per launch
 };
@@ -2155,7 +2164,8 @@ int lbm3_get_populations(lbm3_handle *h, double *f) {
   HIP_TRY(hipMallocAsync((void **)&d, bytes, h->stream), "hipMallocAsync(populations)");
   hipError_t e = lbm::launch_getpop3(h->cfg, h->lat[h->cur], d, nullptr, nullptr, nullptr,
                                      nullptr, h->stream);
-  if (e == hipSuccess) e = hipMemcpyAsync(f, d, bytes, hipMemcpyDeviceToHost, h->stream);
+  const lbm::ReadPart part = {f, d, bytes};
+  if (e == hipSuccess) e = lbm::read_out(&h->read, &part, 1, h->stream);
   (void)hipFreeAsync(d, h->stream);
   if (e == hipSuccess) e = hipStreamSynchronize(h->stream);
   if (e != hipSuccess) return hip_fail(e, "get populations");
@@ -2185,8 +2195,11 @@ int lbm3_moments(lbm3_handle *h, double *rho, double *ux, double *uy, double *uz
   double *outs[4] = {rho, ux, uy, uz};
   hipError_t e = lbm::launch_getpop3(h->cfg, h->lat[h->cur], nullptr, dd[0], dd[1], dd[2], dd[3],
                                      h->stream);
-  for (int k = 0; k < 4 && e == hipSuccess; ++k)
-    if (outs[k]) e = hipMemcpyAsync(outs[k], dd[k], bytes, hipMemcpyDeviceToHost, h->stream);
+  lbm::ReadPart parts[4];
+  int n = 0;
+  for (int k = 0; k < 4; ++k)
+    if (outs[k]) parts[n++] = {outs[k], dd[k], bytes};
+  if (e == hipSuccess) e = lbm::read_out(&h->read, parts, n, h->stream);
   (void)hipFreeAsync(d, h->stream);
   if (e == hipSuccess) e = hipStreamSynchronize(h->stream);
   if (e != hipSuccess) return hip_fail(e, "moments");
@@ -2292,6 +2305,7 @@ void lbm3_destroy(lbm3_handle *h) {
   (void)hipStreamSynchronize(h->stream);
   for (int k = 0; k < 2; ++k)
     if (h->lat[k]) (void)hipFree(h->lat[k]);
+  lbm::read_stage_free(h->read);
   delete h;
 }
 

@@ -248,4 +248,19 @@ hipError_t launch_vn(const VnParamsDev *params_dev, int nparams, int64_t nk,
                      const double *kx, const double *ky, double *eig,
                      double *G, hipStream_t stream);
 
+// Results to host memory (lbm_readout.cpp). The stage is a handle's pinned memory
+// for large read-outs, taken at the first one; NULL copies without one. The
+// copies are in stream order after what the stream holds; to a program's own
+// pages they may have ended when the call returns.
+struct ReadStage {
+  void *mem = nullptr;
+};
+struct ReadPart {
+  void *dst;
+  const void *src;
+  size_t bytes;
+};
+hipError_t read_out(ReadStage *stage, const ReadPart *parts, int nparts, hipStream_t stream);
+void read_stage_free(ReadStage &s);
+
 }  // namespace lbm
