@@ -352,14 +352,16 @@ const char *lbm_last_error(void);
 /* ---- batched stepping of many lattices --------------------------------
  * A batch steps many independent lattices (each an lbm_handle with its own
  * size, relaxation rates, damping variant, sponge and reference state) with
- * persistent launches captured in HIP graphs: by default each launch
+ * launches captured in HIP graphs: by default each launch
  * advances every member by K steps (the strip kernel over a table of work
- * items, which its workgroups take one by one, tallest first; K = 4 for
- * FP32 storage, 3 for FP64 and FP16) and a member's
+ * items, which its persistent workgroups take one by one, tallest first; K = 4
+ * for FP32 storage, 3 for FP64 and FP16) and a member's
  * remainder of fewer than K steps in a tick runs as one-step launches over
- * a table of 256-cell tiles. A batch whose work items do not fill the
- * device once (few or small members) runs its ticks as one-step tile
- * launches only, which spread it over the whole device. All members must
+ * a table of 256-cell tiles. A batch of few or small members (up to some 3
+ * million cells in all) takes up to 14 steps per launch on square tiles of its
+ * members instead; members with conserved rates other than 0, with n != m or
+ * with per-cell reference states, where the strips' work items do not fill
+ * the device once, take one-step launches. All members must
  * share the storage mode and the device. Members may carry a fixed per-cell
  * reference state (lbm_set_qref_field; Sec. 2.2); members with a running-
  * mean reference (lbm_set_qref_average with alpha != 0), a line source or
@@ -410,15 +412,17 @@ int lbm_batch_set_grid(lbm_batch *b, int32_t blocks_per_cu);
  * adjacent strips of one member; LBM_EINVAL otherwise), `rows`
  * rows per work item (1..4096, or 0 for an automatic height: the member
  * rows over the resident workgroups, so that a launch has an item for each,
- * clamped to 8..64 rows). Default: K as above, block 128, rows 0. Rebuilds
+ * clamped to 8..64 rows). Default: K as above, block 128, rows 0, or square
+ * tiles; a shape set here is taken wherever it has enough work items. Rebuilds
  * the work-item table; synchronises the batch stream. Results are
  * bit-identical for every shape. */
 int lbm_batch_set_tuning(lbm_batch *b, const lbm_tuning *t);
 int lbm_batch_get_tuning(lbm_batch *b, lbm_tuning *t);
 
 /* Smallest number of strip work items for which a tick uses K-step launches
- * (fewer: one-step tile launches only). -1 (default): the number of
- * strip-kernel workgroups resident on the device at once; 0: always. */
+ * (fewer: square tiles or one-step launches). -1 (default): the number of
+ * strip-kernel workgroups resident on the device at once, and square tiles
+ * where they are faster; 0: always. */
 int lbm_batch_set_min_items(lbm_batch *b, int32_t min_items);
 
 /* Wait for the batch's work. Returns LBM_EUNSTABLE when the detector of a

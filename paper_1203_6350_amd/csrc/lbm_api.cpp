@@ -13,6 +13,7 @@
 #include <algorithm>
 #include <atomic>
 #include <cstring>
+#include <initializer_list>
 #include <map>
 #include <string>
 #include <tuple>
@@ -420,9 +421,9 @@ struct TileTime {
   double first, step, next, next_step;
 };
 constexpr TileTime TILE_TIMES[3][4] = {
-    {{24, 6.2, 0.51, 3.4, 0.49}, {32, 7.7, 0.70, 5.8, 0.58}, {0, 0, 0, 0, 0}, {0, 0, 0, 0, 0}},
-    {{24, 4.9, 0.39, 2.0, 0.10}, {32, 6.0, 0.44, 2.4, 0.57}, {40, 8.4, 0.74, 4.9, 0.68}, {48, 10.4, 1.10, 7.2, 0.97}},
-    {{24, 5.0, 0.51, 0.5, 0.38}, {32, 5.5, 0.66, 2.3, 0.68}, {40, 6.9, 1.13, 4.8, 1.00}, {48, 8.9, 1.55, 5.2, 1.70}}};
+    {{24, 6.2, 0.51, 4.2, 0.46}, {32, 7.7, 0.70, 5.8, 0.60}, {0, 0, 0, 0, 0}, {0, 0, 0, 0, 0}},
+    {{24, 4.9, 0.39, 2.4, 0.40}, {32, 6.0, 0.44, 2.8, 0.72}, {40, 8.4, 0.74, 4.9, 0.68}, {48, 10.4, 1.10, 7.2, 0.97}},
+    {{24, 5.0, 0.51, 3.0, 0.48}, {32, 5.5, 0.66, 3.2, 0.87}, {40, 6.9, 1.13, 5.0, 1.40}, {48, 8.9, 1.55, 6.0, 1.85}}};
 
 // The fastest tile launch for up to n steps: region, steps per launch and its
 // time per step (1e300 where there is none). Beyond two rounds of tiles the
@@ -1206,11 +1207,17 @@ struct lbm_batch {
   int multi_rows = 0;  // rows per work item, 0: automatic (8..64, an item per resident workgroup)
   int multi_grid = 0;  // persistent workgroups of the strip kernel
   int min_items = -1;  // strip launches need this many items (-1: multi_grid)
+  bool shape_set = false;  // lbm_batch_set_tuning chose the shape
   int4 *d_items = nullptr;
   int *d_nitems = nullptr;
   int nitems = 0;
   size_t item_cap = 0;
   int multi_form = 0;  // BATCH_DEF / BATCH_QF of the member list when the items were made
+  // several steps per launch on square tiles (batches of few or small members):
+  // the table for ticks of min(tick, TILE_MAX_STEPS) = bt_for steps (0: none made)
+  int4 *d_btiles = nullptr;
+  size_t bt_cap = 0;
+  int bt_for = 0, bt_region = 0, bt_most = 0, nbt = 0;
   // instability detector: per-member trip slots (one copy at lbm_batch_sync)
   // and the descriptors of one tick's checks, staged like the members'
   unsigned long long *d_trip = nullptr;            // [dom_cap]
@@ -1226,7 +1233,8 @@ struct lbm_batch {
   int chk_slot = 0;
   bool any_detector = false;  // some check ran since the member list was set
   // graphs keyed by (K or 0, K-step launches or ticks, remainder launches,
-  // tile workgroups per CU, strip workgroup waves, default form)
+  // tile workgroups per CU, strip workgroup waves, default form), or by (most
+  // steps per launch, launches, -1, workgroups, region, 0) for square tiles
   std::map<std::tuple<int, int, int, int, int, int>, hipGraphExec_t> graphs;
 };
 
@@ -1310,10 +1318,15 @@ void free_graphs(lbm_batch *b) {
 // (j = 0 .. nmulti-1, strip kernel form `form`) then `nsingle` one-step
 // tile launches (k = 0 .. nsingle-1; with K-step launches these take the
 // members' remainders).
-int batch_graph(lbm_batch *b, int K, int nmulti, int nsingle, int form, hipGraphExec_t *out) {
-  const int grid = b->cus * b->blocks_per_cu;
-  const auto key = std::make_tuple(K, nmulti, nsingle, b->blocks_per_cu, K ? b->multi_nw : 0,
-                                   K ? form : 0);
+// With region > 0 instead `nmulti` tile launches of at most K steps on regions of
+// that size, one workgroup per tile.
+int batch_graph(lbm_batch *b, int K, int nmulti, int nsingle, int form, int region,
+                hipGraphExec_t *out) {
+  // (rounded up, so that most changes of the member list keep the graph)
+  const int grid = region ? (b->nbt + 255) / 256 * 256 : b->cus * b->blocks_per_cu;
+  const auto key = region ? std::make_tuple(K, nmulti, -1, grid, region, 0)
+                          : std::make_tuple(K, nmulti, nsingle, b->blocks_per_cu,
+                                            K ? b->multi_nw : 0, K ? form : 0);
   auto it = b->graphs.find(key);
   if (it != b->graphs.end()) {
     *out = it->second;
@@ -1323,10 +1336,12 @@ int batch_graph(lbm_batch *b, int K, int nmulti, int nsingle, int form, hipGraph
   hipError_t e = hipSuccess;
   // zero the item tickets of the tick's strip launches (a kernel node: the
   // graph is replayed every tick)
-  if (nmulti > 0) e = lbm::launch_fill_i32(b->d_nitems + 1, nmulti, 0, b->stream);
+  if (nmulti > 0 && !region) e = lbm::launch_fill_i32(b->d_nitems + 1, nmulti, 0, b->stream);
   for (int j = 0; j < nmulti && e == hipSuccess; ++j)
-    e = lbm::launch_batch_multi(b->storage, K, b->multi_nw, form, b->d_doms,
-                                b->d_items, b->d_nitems, b->multi_grid, j, b->stream);
+    e = region ? lbm::launch_batch_tile(b->storage, region, K, b->d_doms, b->d_btiles,
+                                        b->d_ntiles + 1, grid, j, b->stream)
+               : lbm::launch_batch_multi(b->storage, K, b->multi_nw, form, b->d_doms,
+                                         b->d_items, b->d_nitems, b->multi_grid, j, b->stream);
   for (int k = 0; k < nsingle && e == hipSuccess; ++k)
     e = lbm::launch_batch(b->storage, b->d_doms, b->d_tiles, b->d_ntiles, grid, k, K, b->stream);
   hipGraph_t g = nullptr;
@@ -1357,6 +1372,7 @@ void lbm_batch_destroy(lbm_batch *b) {
   if (b->d_ntiles) (void)hipFree(b->d_ntiles);
   if (b->d_items) (void)hipFree(b->d_items);
   if (b->d_nitems) (void)hipFree(b->d_nitems);
+  if (b->d_btiles) (void)hipFree(b->d_btiles);
   if (b->d_trip) (void)hipFree(b->d_trip);
   if (b->d_chk) (void)hipFree(b->d_chk);
   for (int k = 0; k < 2; ++k) {
@@ -1393,16 +1409,19 @@ int validate_members(lbm_handle *const *members, int32_t count) {
   return LBM_OK;
 }
 
-// Copy the tile table (optional) and the item table to the device through
-// the next pinned staging slot, in stream order on the batch stream: the
-// copies land after every launch enqueued before them.
-int upload_tables(lbm_batch *b, const std::vector<int2> *tiles, const std::vector<int4> *items) {
+// Copy tables to the device through the next pinned staging slot, in stream order
+// on the batch stream: the copies land after every launch enqueued before them.
+struct Table {
+  void *dev;
+  const void *host;
+  size_t bytes;
+};
+int upload_tables(lbm_batch *b, std::initializer_list<Table> tables) {
   const int sl = b->tab_slot;
   b->tab_slot ^= 1;
   HIP_TRY(hipEventSynchronize(b->tab_copied[sl]), "hipEventSynchronize");  // slot free again
-  const size_t tb = tiles ? sizeof(int2) * tiles->size() : 0;
-  const size_t ib = items ? sizeof(int4) * items->size() : 0;
-  const size_t need = tb + ib + 16;
+  size_t need = 0;
+  for (const Table &t : tables) need += t.bytes;
   if (need > b->tab_cap[sl]) {
     if (b->h_tab[sl]) (void)hipHostFree(b->h_tab[sl]);
     b->h_tab[sl] = nullptr;
@@ -1412,24 +1431,79 @@ int upload_tables(lbm_batch *b, const std::vector<int2> *tiles, const std::vecto
     b->tab_cap[sl] = cap;
   }
   char *h = b->h_tab[sl];
-  size_t off = 0;
-  if (tiles) {
-    std::memcpy(h, tiles->data(), tb);
-    std::memcpy(h + tb, &b->ntiles, sizeof(int));
-    HIP_TRY(hipMemcpyAsync(b->d_tiles, h, tb, hipMemcpyHostToDevice, b->stream), "copy(tiles)");
-    HIP_TRY(hipMemcpyAsync(b->d_ntiles, h + tb, sizeof(int), hipMemcpyHostToDevice, b->stream),
-            "copy(ntiles)");
-    off = tb + 8;
-  }
-  if (items) {
-    std::memcpy(h + off, items->data(), ib);
-    std::memcpy(h + off + ib, &b->nitems, sizeof(int));
-    if (ib)
-      HIP_TRY(hipMemcpyAsync(b->d_items, h + off, ib, hipMemcpyHostToDevice, b->stream), "copy(items)");
-    HIP_TRY(hipMemcpyAsync(b->d_nitems, h + off + ib, sizeof(int), hipMemcpyHostToDevice, b->stream),
-            "copy(nitems)");
+  for (const Table &t : tables) {
+    if (!t.bytes) continue;
+    std::memcpy(h, t.host, t.bytes);
+    HIP_TRY(hipMemcpyAsync(t.dev, h, t.bytes, hipMemcpyHostToDevice, b->stream), "copy(tables)");
+    h += t.bytes;
   }
   HIP_TRY(hipEventRecord(b->tab_copied[sl], b->stream), "hipEventRecord");
+  return LBM_OK;
+}
+
+// What square tiles have to beat for members of `cells` cells in all, in us a
+// step: strips (128 members of 64^2 .. 36 of 200^2 in FP32 14.0 .. 15.1, 16 of 256^2
+// 13.8), or single steps (2 of 64^2 3.3, 100 of 64^2 7.5, 4 of 256^2 7.6).
+double batch_other_time(int storage, double cells, bool strips) {
+  static const double strip[3][2] = {{9.5, 9e-6}, {9.5, 4.5e-6}, {10.0, 4.5e-6}};
+  static const double one[3][2] = {{3.4, 1.8e-5}, {3.0, 1.05e-5}, {3.1, 1.0e-5}};
+  const double *t = strips ? strip[storage] : one[storage];
+  return t[0] + t[1] * cells;
+}
+
+// The square tiles for ticks of n steps: region and steps per launch by the tiles'
+// times, and their table. No tiles (bt_region = 0) where the launches that the
+// batch has otherwise are faster, which they are beyond some 3 million cells.
+// (Tiles against those, FP32: 2 of 64^2 1.05 and 3.3 us a step, 8 of 256^2 4.3 and
+// 12.7, 50 of 128^2 7.9 and 14.0.)
+int choose_batch_tiles(lbm_batch *b, int n, bool strips) {
+  double cells = 0;
+  for (const lbm_handle *h : b->members) cells += (double)h->user.nx * h->user.ny;
+  double best = batch_other_time(b->storage, cells, strips);
+  int region = 0, most = 0;
+  for (const TileTime &t : TILE_TIMES[b->storage])
+    for (int s = 2; t.region && s <= n; ++s) {
+      const int T = t.region - 2 * (s - 1);
+      if (T < 4 || cells / ((double)T * T) > 16.0 * b->cus) break;
+      int64_t tiles = 0;
+      for (const lbm_handle *h : b->members)
+        tiles += ((h->user.nx + T - 1) / T) * ((h->user.ny + T - 1) / T);
+      const double rounds = (double)((tiles + b->cus - 1) / b->cus);
+      const double us = (t.first + t.step * s + (rounds - 1) * (t.next + t.next_step * s)) / s;
+      if (us < best) {
+        best = us;
+        region = t.region;
+        most = s;
+      }
+    }
+  if (region && (region != b->bt_region || most != b->bt_most || !b->bt_for)) {
+    const int T = region - 2 * (most - 1);
+    std::vector<int4> tiles;
+    for (size_t i = 0; i < b->members.size(); ++i)
+      for (int64_t y = 0; y < b->members[i]->user.ny; y += T)
+        for (int64_t x = 0; x < b->members[i]->user.nx; x += T)
+          tiles.push_back(make_int4((int)i, (int)x, (int)y, 0));
+    if (tiles.size() > b->bt_cap) {
+      HIP_TRY(hipStreamSynchronize(b->stream), "hipStreamSynchronize");
+      free_graphs(b);
+      if (b->d_btiles) (void)hipFree(b->d_btiles);
+      b->d_btiles = nullptr;
+      b->bt_cap = b->bt_for = 0;
+      const size_t cap = (size_t)(1.5 * tiles.size());
+      HIP_TRY(hipMalloc((void **)&b->d_btiles, sizeof(int4) * cap), "batch tiles");
+      b->bt_cap = cap;
+    }
+    b->nbt = (int)tiles.size();
+    int rc = upload_tables(b, {{b->d_btiles, tiles.data(), sizeof(int4) * tiles.size()},
+                               {b->d_ntiles + 1, &b->nbt, sizeof(int)}});
+    if (rc) {
+      b->bt_for = 0;
+      return rc;
+    }
+  }
+  b->bt_region = region;
+  b->bt_most = most;
+  b->bt_for = n;
   return LBM_OK;
 }
 
@@ -1490,7 +1564,8 @@ int build_items(lbm_batch *b) {
   std::vector<int4> items;
   int rc = make_items(b, items);
   if (rc) return rc;
-  return upload_tables(b, nullptr, &items);
+  return upload_tables(b, {{b->d_items, items.data(), sizeof(int4) * items.size()},
+                           {b->d_nitems, &b->nitems, sizeof(int)}});
 }
 
 // Rebuild the tile table for a new member list; reuses the device buffers
@@ -1554,7 +1629,11 @@ int batch_set_members_impl(lbm_batch *b, lbm_handle *const *members, int32_t cou
   std::vector<int4> items;
   rc = make_items(b, items);
   if (rc) return rc;
-  return upload_tables(b, &tiles, &items);
+  b->bt_for = 0;  // the next tick cuts its own
+  return upload_tables(b, {{b->d_tiles, tiles.data(), sizeof(int2) * tiles.size()},
+                           {b->d_ntiles, &b->ntiles, sizeof(int)},
+                           {b->d_items, items.data(), sizeof(int4) * items.size()},
+                           {b->d_nitems, &b->nitems, sizeof(int)}});
 }
 
 // After a tick: one launch checks every member whose detector is due at
@@ -1615,7 +1694,7 @@ int lbm_batch_create(lbm_handle *const *members, int32_t count, void *stream,
   int dev = 0;
   if (e == hipSuccess) e = hipGetDevice(&dev);
   if (e == hipSuccess) e = hipDeviceGetAttribute(&b->cus, hipDeviceAttributeMultiprocessorCount, dev);
-  if (e == hipSuccess) e = hipMalloc((void **)&b->d_ntiles, sizeof(int));
+  if (e == hipSuccess) e = hipMalloc((void **)&b->d_ntiles, 2 * sizeof(int));  // and of square tiles
   // item count and one ticket per strip launch of a tick (at most 4096 / 2)
   if (e == hipSuccess) e = hipMalloc((void **)&b->d_nitems, sizeof(int) * (1 + 4096 / 2));
   // default shape: K-step strip launches (K = 4 for FP32, 3 for FP64 and FP16)
@@ -1666,11 +1745,13 @@ int lbm_batch_set_tuning(lbm_batch *b, const lbm_tuning *t) {
     if (t->rows < 0 || t->rows > 4096) return fail(LBM_EINVAL, "rows must be 0 or 1..4096");
   }
   HIP_TRY(hipStreamSynchronize(b->stream), "hipStreamSynchronize");
+  b->shape_set = true;
   b->multi_k = t->kernel >= 2 ? t->kernel : 0;
   if (b->multi_k) {
     b->multi_nw = t->block / 64;
     b->multi_rows = t->rows;
   }
+  b->bt_for = 0;
   return build_items(b);
 }
 
@@ -1678,6 +1759,7 @@ int lbm_batch_set_min_items(lbm_batch *b, int32_t min_items) {
   if (!b) return fail(LBM_EINVAL, "batch is NULL");
   if (min_items < -1) return fail(LBM_EINVAL, "min_items must be -1 or >= 0");
   b->min_items = min_items;
+  b->bt_for = 0;  // strips or single steps: the tiles' alternative may be another
   return LBM_OK;
 }
 
@@ -1720,17 +1802,33 @@ int lbm_batch_tick(lbm_batch *b, int32_t tick, const int32_t *member_steps) {
                          hipMemcpyHostToDevice, b->stream), "hipMemcpy(descriptors)");
   HIP_TRY(hipEventRecord(b->copied[sl], b->stream), "hipEventRecord");
   // K-step strip launches need enough work items to fill the persistent
-  // grid (each item marches its rows in sequence); a smaller batch runs as
-  // one-step tile launches, which spread it over the whole device. With
+  // grid (each item marches its rows in sequence); a smaller batch takes
+  // one-step launches. Batches as created take several steps per launch on square
+  // tiles instead of either where these are faster (choose_batch_tiles), as
+  // do batches with a chosen strip shape and too few items for it. With
   // K-step launches, member i takes st / K of them and then st mod K
   // one-step launches; every launch flips its current lattice once. The
   // graph holds tick / K K-step launches (members needing fewer skip the
   // rest) and as many one-step launches as the largest remainder, so one
   // tick length needs at most K graphs whatever the members' step counts.
   const int need = b->min_items >= 0 ? b->min_items : b->multi_grid;
-  const int K = b->multi_k && b->nitems >= need ? b->multi_k : 0;
-  int nmulti = 0, nsingle = tick;
-  if (K) {
+  int K = b->multi_k && b->nitems >= need ? b->multi_k : 0;
+  int nmulti = 0, nsingle = tick, region = 0;
+  if (b->multi_k && (!K || (!b->shape_set && b->min_items < 0)) && tick >= 2 &&
+      (form & lbm::BATCH_DEF) && !(form & lbm::BATCH_QF)) {
+    const int bt = std::min(tick, lbm::TILE_MAX_STEPS);
+    if (bt != b->bt_for) {
+      int rc = choose_batch_tiles(b, bt, K != 0);
+      if (rc) return rc;
+    }
+    region = b->bt_region;
+  }
+  if (region) {
+    K = 0;
+    for (size_t i = 0; i < n; ++i)
+      nmulti = std::max(nmulti, lbm::batch_tile_launches(member_steps ? member_steps[i] : tick,
+                                                         b->bt_most));
+  } else if (K) {
     nmulti = tick / K;
     nsingle = 0;
     for (size_t i = 0; i < n; ++i) {
@@ -1739,12 +1837,13 @@ int lbm_batch_tick(lbm_batch *b, int32_t tick, const int32_t *member_steps) {
     }
   }
   hipGraphExec_t ex = nullptr;
-  int rc = batch_graph(b, K, nmulti, nsingle, form, &ex);
+  int rc = region ? batch_graph(b, b->bt_most, nmulti, 0, 0, region, &ex)
+                  : batch_graph(b, K, nmulti, nsingle, form, 0, &ex);
   if (rc) return rc;
   HIP_TRY(hipGraphLaunch(ex, b->stream), "hipGraphLaunch");
   for (size_t i = 0; i < n; ++i) {
     const int st = member_steps ? member_steps[i] : tick;
-    const int launches = K ? st / K + st % K : st;
+    const int launches = K ? st / K + st % K : st;  // (tiles: of the same parity)
     b->members[i]->cur ^= launches & 1;
     b->members[i]->steps += st;
   }

@@ -133,6 +133,17 @@ hipError_t launch_tile(const StepConfig &c, int region, int steps, const double 
   return hipErrorInvalidValue;
 }
 
+hipError_t launch_batch_tile(int storage, int region, int most, const BatchDomain *doms,
+                             const int4 *tiles, const int *ntiles, int grid, int j,
+                             hipStream_t stream) {
+  switch (storage) {
+    case 0: return launch_batch_tile_f64(region, most, doms, tiles, ntiles, grid, j, stream);
+    case 1: return launch_batch_tile_f32(region, most, doms, tiles, ntiles, grid, j, stream);
+    case 2: return launch_batch_tile_f16(region, most, doms, tiles, ntiles, grid, j, stream);
+  }
+  return hipErrorInvalidValue;
+}
+
 hipError_t launch_batch_multi(int storage, int k, int nw, int form, const BatchDomain *doms,
                               const int4 *items, int *nitems, int grid, int j,
                               hipStream_t stream) {

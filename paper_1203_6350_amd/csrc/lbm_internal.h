@@ -90,6 +90,29 @@ hipError_t launch_tile_f32(const StepConfig &c, int region, int steps, const dou
                            const void *src, void *dst, hipStream_t stream);
 hipError_t launch_tile_f16(const StepConfig &c, int region, int steps, const double *source,
                            const void *src, void *dst, hipStream_t stream);
+struct BatchDomain;
+// Tiles of many lattices in one launch (launch j of a tick): the table lists
+// (member, first column, first row) of outputs of region - 2 (most - 1) cells a
+// side; members of the default form without per-cell reference states.
+hipError_t launch_batch_tile(int storage, int region, int most, const BatchDomain *doms,
+                             const int4 *tiles, const int *ntiles, int grid, int j,
+                             hipStream_t stream);
+#define LBM_TILE_DECL(ST)                                                                        \
+  hipError_t launch_batch_tile_##ST(int region, int most, const BatchDomain *doms,              \
+                                    const int4 *tiles, const int *ntiles, int grid, int j,      \
+                                    hipStream_t stream);
+LBM_TILE_DECL(f32)
+LBM_TILE_DECL(f64)
+LBM_TILE_DECL(f16)
+#undef LBM_TILE_DECL
+// The launches in which a member takes `stop` steps, at most `most` in each: of
+// the same parity as `stop`, so that the lattice that is current afterwards is
+// the one that single steps leave. Launch j of n takes the steps from
+// stop j / n to stop (j + 1) / n.
+__host__ __device__ inline int batch_tile_launches(int stop, int most) {
+  const int n = (stop + most - 1) / most;
+  return n + ((n ^ stop) & 1);
+}
 // Per storage type and step count (lbm_strip_f64/f32/f16.hip, one object
 // per K): the single-lattice strip launch, the batched one and its
 // resident workgroups per CU.

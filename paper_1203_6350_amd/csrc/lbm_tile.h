@@ -21,6 +21,10 @@
 // and one LDS round trip a step), the 48^2 one by VALU issue, half of it on the
 // shrinking halo.
 //
+// The same tiles of many small lattices make one launch of a batch (us a step,
+// FP32): 2 of 64^2 3.3 -> 1.05, 8 of 256^2 12.7 -> 4.3, 50 of 128^2 14.0 -> 7.7, 36 of
+// 200^2 15.1 -> 10.4.
+//
 // The eight moving populations live in LDS in two copies (step j writes copy
 // j mod 2 and reads it after one barrier); the resting one stays in its
 // thread's register. Every intermediate result is rounded through the storage
@@ -84,14 +88,16 @@ struct TileGeom {
 };
 
 template <typename S, typename G, int FORM, int VAR>
-__device__ __forceinline__ void tile_run(const TileLat<S> &L, int X0, int Y0, int steps,
+__device__ __forceinline__ void tile_run(const TileLat<S> &L, int X0, int Y0, int steps, int inset,
                                          typename Store<S>::C *lds,
                                          const TileChannel<typename Store<S>::C, (FORM & TILE_CH) != 0> *ch) {
   typedef typename Store<S>::C C;
   constexpr bool DEF = (FORM & TILE_DEF) != 0, QF = (FORM & TILE_QF) != 0,
                  CH = (FORM & TILE_CH) != 0;
   constexpr int R = G::R, N = G::N;
-  const int H = steps - 1 + (CH ? 1 : 0);  // halo: the outputs are the cells H.. R-H-1
+  // halo: the outputs are the cells H .. R-H-1; a launch of fewer steps than its
+  // tiles were cut for leaves a frame of `inset` cells out
+  const int in0 = inset + (CH ? 1 : 0), H = steps - 1 + in0;
   constexpr int BUF = 8 * G::PLANE;
   int lx[N], ly[N];
   C g0[N], chi[N], q[N][QF ? 3 : 1];
@@ -114,8 +120,8 @@ __device__ __forceinline__ void tile_run(const TileLat<S> &L, int X0, int Y0, in
   }
   // Step j runs on the cells within steps - j of the outputs.
 #define LBM_TILE_NEED(k, j)                                                        \
-  ((unsigned)(lx[k] - ((j) - 1 + CH)) < (unsigned)(R - 2 * ((j) - 1 + CH)) &&      \
-   (unsigned)(ly[k] - ((j) - 1 + CH)) < (unsigned)(R - 2 * ((j) - 1 + CH)))
+  ((unsigned)(lx[k] - ((j) - 1 + in0)) < (unsigned)(R - 2 * ((j) - 1 + in0)) &&    \
+   (unsigned)(ly[k] - ((j) - 1 + in0)) < (unsigned)(R - 2 * ((j) - 1 + in0)))
   auto finish = [&](C g[9], int k, int j) {  // collide, then store or hand on
     C c0, c1, c2;
     if constexpr (QF) {
@@ -249,15 +255,15 @@ __device__ __forceinline__ void tile_run(const TileLat<S> &L, int X0, int Y0, in
 }
 
 template <typename S, typename G, int FORM>
-__device__ __forceinline__ void tile_variant(const TileLat<S> &L, int X0, int Y0, int steps,
+__device__ __forceinline__ void tile_variant(const TileLat<S> &L, int X0, int Y0, int steps, int inset,
                                              typename Store<S>::C *lds,
                                              const TileChannel<typename Store<S>::C, (FORM & TILE_CH) != 0> *ch) {
   switch (L.variant) {
-    case V_I: tile_run<S, G, FORM, V_I>(L, X0, Y0, steps, lds, ch); break;
-    case V_II: tile_run<S, G, FORM, V_II>(L, X0, Y0, steps, lds, ch); break;
-    case V_III: tile_run<S, G, FORM, V_III>(L, X0, Y0, steps, lds, ch); break;
-    case V_VISC: tile_run<S, G, FORM, V_VISC>(L, X0, Y0, steps, lds, ch); break;
-    default: tile_run<S, G, FORM, V_NONE>(L, X0, Y0, steps, lds, ch); break;
+    case V_I: tile_run<S, G, FORM, V_I>(L, X0, Y0, steps, inset, lds, ch); break;
+    case V_II: tile_run<S, G, FORM, V_II>(L, X0, Y0, steps, inset, lds, ch); break;
+    case V_III: tile_run<S, G, FORM, V_III>(L, X0, Y0, steps, inset, lds, ch); break;
+    case V_VISC: tile_run<S, G, FORM, V_VISC>(L, X0, Y0, steps, inset, lds, ch); break;
+    default: tile_run<S, G, FORM, V_NONE>(L, X0, Y0, steps, inset, lds, ch); break;
   }
 }
 
@@ -282,7 +288,7 @@ __global__ __launch_bounds__(G::NT) void tile_kernel(
   // from its inputs: a last tile of that column alone starts one cell earlier
   // (column nx - 2 is then stored twice, with the same values)
   if ((FORM & TILE_CH) && X0 > L.nx - 2) X0 = L.nx - 2;
-  tile_variant<S, G, FORM>(L, X0, ty * T, steps, lds + G::PAD, &ch);
+  tile_variant<S, G, FORM>(L, X0, ty * T, steps, 0, lds + G::PAD, &ch);
 }
 
 template <typename S>
@@ -370,6 +376,97 @@ static hipError_t launch_tile_storage(const StepConfig &c, int region, int steps
         return launch_tile_form<S, TileGeom<48, 768>>(c, steps, source, src, dst, stream);
       break;
   }
+  return hipErrorInvalidValue;
+}
+
+// Tiles of many lattices in one launch (launch j of a tick): the table lists
+// (member, first column, first row) of the outputs, cut for `most` steps. Each
+// member takes its steps of the tick evenly over batch_tile_launches of them.
+// The descriptors' numbers become the same scalar operands as kernel arguments.
+template <typename C>
+__device__ __forceinline__ C uniform(double v) {
+  if constexpr (sizeof(C) == 4)
+    return __builtin_bit_cast(float, __builtin_amdgcn_readfirstlane(__builtin_bit_cast(int, (float)v)));
+  else
+    return v;
+}
+
+template <typename S, typename G>
+__global__ __launch_bounds__(G::NT) void batch_tile_kernel(
+    const BatchDomain *__restrict__ doms, const int4 *__restrict__ tiles,
+    const int *__restrict__ ntiles, int j, int most) {
+  typedef typename Store<S>::C C;
+  __shared__ C lds[tile_lds_elems<G, TILE_DEF>()];
+  const int nt = *ntiles, per_xcd = (nt + 7) / 8;
+  const int v = (blockIdx.x & 7) * per_xcd + (blockIdx.x >> 3);
+  if ((int)(blockIdx.x >> 3) >= per_xcd || v >= nt) return;
+  const int4 t = tiles[v];
+  const BatchDomain &d = doms[t.x];
+  const int stop = d.stop_at, launches = batch_tile_launches(stop, most);
+  if (j >= launches) return;
+  const int steps = stop * (j + 1) / launches - stop * j / launches;
+  const int par = (d.parity + j) & 1;
+  TileLat<S> L;
+  L.src = (const S *)d.lat[par];
+  L.dst = (S *)d.lat[par ^ 1];
+  L.nx = d.nx;
+  L.ny = d.ny;
+  L.pitch = d.pitch;
+  L.ps = d.ps;
+#pragma unroll
+  for (int i = 0; i < 9; ++i) {
+    L.scale[i] = uniform<C>(d.scale[i]);
+    L.inv_scale[i] = uniform<C>(d.inv_scale[i]);
+    L.p.s[i] = uniform<C>(d.s[i]);
+  }
+  L.p.n = uniform<C>(d.n);
+  L.p.m = uniform<C>(d.m);
+  L.p.rho_b = uniform<C>(d.rho_b);
+  L.p.ubx = uniform<C>(d.ubx);
+  L.p.uby = uniform<C>(d.uby);
+  L.p.dcf0 = uniform<C>(d.dcf[0]);
+  L.p.dcf1 = uniform<C>(d.dcf[1]);
+  L.p.dcf2 = uniform<C>(d.dcf[2]);
+  set_relax_coeffs(L.p);
+  if constexpr (sizeof(C) == 4)
+#pragma unroll
+    for (int i = 0; i < 9; ++i) {
+      L.p.sig[i] = uniform<C>(L.p.sig[i]);
+      L.p.tau[i] = uniform<C>(L.p.tau[i]);
+    }
+  L.variant = d.variant;
+  L.chi_mode = d.chi_mode;
+  L.chi_field = (const C *)d.chi_field;
+  L.chix = (const C *)d.chi_x;
+  L.chiy = (const C *)d.chi_y;
+  L.qf = nullptr;
+  L.qf_out = nullptr;
+  L.qps = 0;
+  L.alpha = C(0);
+  tile_variant<S, G, TILE_DEF>(L, t.y, t.z, steps, most - steps, lds + G::PAD, nullptr);
+}
+
+template <typename S>
+static hipError_t launch_batch_tile_storage(int region, int most, const BatchDomain *doms,
+                                            const int4 *tiles, const int *ntiles, int grid, int j,
+                                            hipStream_t stream) {
+  if (most < 1 || most > TILE_MAX_STEPS || region - 2 * (most - 1) < 1 || grid < 1)
+    return hipErrorInvalidValue;
+#define LBM_BTILE(R, NT)                                                                        \
+  batch_tile_kernel<S, TileGeom<R, NT>><<<dim3((unsigned)grid), dim3(NT), 0, stream>>>(          \
+      doms, tiles, ntiles, j, most);                                                             \
+  return hipGetLastError();
+  switch (region) {
+    case 24: LBM_BTILE(24, 576)
+    case 32: LBM_BTILE(32, 1024)
+    case 40:
+      if constexpr (sizeof(typename Store<S>::C) == 4) { LBM_BTILE(40, 832) }
+      break;
+    case 48:
+      if constexpr (sizeof(typename Store<S>::C) == 4) { LBM_BTILE(48, 768) }
+      break;
+  }
+#undef LBM_BTILE
   return hipErrorInvalidValue;
 }
 
