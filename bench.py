@@ -34,7 +34,7 @@ PEAK_HBM_GBPS = 8000.0
 PEAK_VALU_TFLOPS = 78.6
 # Arithmetic of one cell update (FMA = 2 flop) as the collision executes it
 # with the default parameters (conserved rates 0, n = m), counted on the
-# compiled loop of the four-step kernel (built as the library is, without
+# compiled loop of the strip kernel (built as the library is, without
 # automatic contraction): M g, the shifted conserved moments,
 # the equilibrium deviations, relaxation and damping folded with D^-1, and
 # M^T; the one reciprocal of rho per cell and of 1 + n chi per row count once.
@@ -67,7 +67,7 @@ VALU_SUMMARY = os.path.join(ROOT, "profiles", "step_f32_typeII_4096_valu.txt")
 
 def valu_issue(tuning):
     """VALU issue-busy fraction and lane-instructions per cell update of the
-    four-step kernel from the committed SQ-counter summary (one section per
+    kernel-4 strips from the committed SQ-counter summary (one section per
     launch shape), or None when the strip sources changed since or the shape
     was not profiled."""
     if not os.path.exists(VALU_SUMMARY) or tuning.get("kernel") != 4:
@@ -85,6 +85,15 @@ def valu_issue(tuning):
             return {"valu_issue_busy": float(busy.group(1)),
                     "lane_instructions_per_update": float(lane.group(1))}
     return None
+
+
+def launch_steps(tuning, storage="f32"):
+    """Time steps per launch of a launch shape: its step count, or six for the
+    four-step shape with fitted rows in FP32 (without a running-mean reference)."""
+    k = tuning["kernel"]
+    if k == 4 and tuning.get("rows", 0) == 0 and storage == "f32":
+        return 6
+    return k if k >= 2 else 1
 
 
 def counter_traffic(tuning):
@@ -138,8 +147,10 @@ def time_variant(lbm, wl, torch, spec, fields, steps, warmup, diag_every=100, fi
     else:
         lat.set_tuning(**fixed)
         tuning = lat.tuning()
-    per = tuning["kernel"] if tuning["kernel"] >= 2 else 1  # time steps per launch
+    per = launch_steps(tuning, spec.storage)
     launches, rest = divmod(steps, per)
+    if not launches:  # fewer steps than a launch holds: one shorter launch
+        per, launches, rest = steps, 1, 0
     diag = torch.empty(7, dtype=torch.float64, device="cuda")
     lat.step(warmup)
     torch.cuda.synchronize()
@@ -548,7 +559,7 @@ def qref_leg(lbm, wl, torch, n=4096, steps=400, warmup=20, alpha=1e-3):
         else:
             lat.autotune(reps=5)
         t = lat.tuning()
-        per = t["kernel"] if t["kernel"] >= 2 else 1
+        per = max(1, t["kernel"]) if a else launch_steps(t)
         lat.step(warmup)
         e0 = torch.cuda.Event(enable_timing=True)
         e1 = torch.cuda.Event(enable_timing=True)
@@ -706,8 +717,8 @@ def main():
               file=sys.stderr)
         sys.exit(2)
     if args.steps < 4 or args.warmup < 0:
-        # the timed steps must hold at least one launch of the four-step
-        # kernel, whose mean duration the roofline divides by
+        # the timed steps must hold at least one launch of several steps,
+        # whose mean duration the roofline divides by
         print("bench.py: --steps must be at least 4 and --warmup at least 0", file=sys.stderr)
         sys.exit(2)
 

@@ -459,7 +459,7 @@ double best_tiles(const lbm::StepConfig &c, int64_t n, int cus, bool strips, int
 // 6.3 and 7.9), or the one-step kernel's where there are no strips.
 double other_time(const lbm::StepConfig &c, bool strips) {
   const double cells = (double)c.nx * c.ny;
-  static const double fixed[3] = {3.0, 2.6, 2.9}, rate[3] = {7.3e-6, 4.6e-6, 5.5e-6};
+  static const double fixed[3] = {3.0, 2.6, 2.9}, rate[3] = {7.3e-6, 4.3e-6, 5.5e-6};
   static const double one_fixed[3] = {3.4, 3.0, 3.0}, one_rate[3] = {2.5e-5, 1.15e-5, 8e-6};
   return strips ? fixed[c.storage] + rate[c.storage] * cells
                 : one_fixed[c.storage] + one_rate[c.storage] * cells;
@@ -483,18 +483,21 @@ StepPlan step_plan(const lbm_handle *h, int64_t n) {
   if (n < 2 || !strips || (h->shape_set && !chosen)) return p;
   p.kind = StepPlan::STRIP;
   p.cfg = h->cfg;
+  // fitted rows of the four-step shape: six steps where the kernel has them
+  const bool six = lbm::six_steps_support(h->cfg);
   if (h->shape_set) {
-    p.most = k;
+    p.most = k == 4 && h->cfg.rows == 0 && six ? 6 : k;
     return p;
   }
   // as created: the shape that is fastest or within 5% of it from 300^2 to 3000
   // x 2500 cells (wide workgroups pay once the chunks are tall)
-  p.most = 4;
-  p.cfg.kernel = p.most;
+  p.most = six ? 6 : 4;
+  p.cfg.kernel = 4;
   p.cfg.rows = 0;
-  p.cfg.block = h->user.storage == LBM_STORAGE_F16              ? 64
-                : (int64_t)h->user.nx * h->user.ny < 3000000 ? (h->user.storage == LBM_STORAGE_F64 ? 128 : 64)
-                                                                : 256;
+  p.cfg.block = h->user.storage == LBM_STORAGE_F16                      ? 64
+                : six || (int64_t)h->user.nx * h->user.ny >= 3000000 ? 256
+                : h->user.storage == LBM_STORAGE_F64                  ? 128
+                                                                        : 64;
   return p;
 }
 

@@ -74,7 +74,18 @@ inline bool multi_step_supports(const StepConfig &c) {
   return (float)c.s[0] == 0.0f && (float)c.s[1] == 0.0f && (float)c.s[2] == 0.0f &&
          (float)c.n == (float)c.m;
 }
-// k = 2..4 time steps in one launch (src at t -> dst at t + k).
+// Five and six steps per launch: FP32 in the default form without a running-mean
+// reference. A launch costs its memory traffic whether it collides four or six
+// times: from four to six steps 4096^2 goes from 235 to 260 GLUPS, 2048^2 from 204 to
+// 231, 1024^2 from 135 to 146 (each in its best block of fitted rows), 2048^2 with a
+// per-cell reference from 191 to 211. A running mean's values do not fit the
+// registers (164 -> 151), nor do FP64's; FP16 is bound by VALU issue already.
+inline bool six_steps_support(const StepConfig &c) {
+  return c.storage == 1 && multi_step_supports(c) && !(c.qfield && c.qalpha != 0.0) && (float)c.s[0] == 0.0f &&
+         (float)c.s[1] == 0.0f && (float)c.s[2] == 0.0f && (float)c.n == (float)c.m;
+}
+// k = 2..4 time steps in one launch (src at t -> dst at t + k), 2..6 where
+// six_steps_support.
 hipError_t launch_multi_steps(const StepConfig &c, int k, const void *src, void *dst,
                               hipStream_t stream);
 // Tile kernel (lbm_tile_f64/f32/f16.hip): 1..TILE_MAX_STEPS steps in one
@@ -229,6 +240,8 @@ int batch_multi_per_cu(int storage, int k, int nw, int form);
 LBM_STRIP_DECL_K(f64)
 LBM_STRIP_DECL_K(f32)
 LBM_STRIP_DECL_K(f16)
+hipError_t launch_multi_f32_k5(const StepConfig &c, const void *src, void *dst, hipStream_t stream);
+hipError_t launch_multi_f32_k6(const StepConfig &c, const void *src, void *dst, hipStream_t stream);
 
 // Three-dimensional D3Q15 step (lbm3_kernels.hip): everything a kernel
 // needs in FP64, converted per launch to the compute precision.

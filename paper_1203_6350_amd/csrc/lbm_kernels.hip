@@ -416,6 +416,12 @@ hipError_t launch_multi_steps(const StepConfig &c, int k, const void *src, void 
     case 4: return launch_multi_##ST##_k4(c, src, dst, stream);        \
   }                                                                    \
   return hipErrorInvalidValue;
+  if (k > 4) {
+    if (!six_steps_support(c)) return hipErrorInvalidValue;
+    return k == 5   ? launch_multi_f32_k5(c, src, dst, stream)
+           : k == 6 ? launch_multi_f32_k6(c, src, dst, stream)
+                    : hipErrorInvalidValue;
+  }
   switch (c.storage) {
     case 0: { LBM_MULTI_K(f64) }
     case 1: { LBM_MULTI_K(f32) }

@@ -15,7 +15,7 @@ namespace lbm {
 
 // ---------------------------------------------------------------- several steps per launch
 // Temporal blocking: one launch advances the lattice by K = 2, 3 or 4 time
-// steps, reading and writing it once.
+// steps (FP32 also 5 and 6), reading and writing it once.
 //
 // Each wave owns a strip of STRIP = 64 - 2K output columns of one chunk of
 // rows: lane l holds column X0 - K + l (mod nx), so the 64 lanes cover the
@@ -127,6 +127,8 @@ struct StripState {
   C a256[3][3];         // input rows: populations 2, 5, 6
   C craw[6];            // sponge input (chi_raw) of the rows, slot q % 6
   C qraw[6][3];         // reference-state deviations of the rows (V_QF), slot q % 6
+  // K > 4: the inputs of rows a - 5 and a - 6, which the rings drop
+  C craw_old[2], qraw_old[2][3];
   C b013[K - 1][2][3];  // results of steps 1..K-1: populations 0, 1, 3
   C b256[K - 1][3][3];  // results of steps 1..K-1: populations 2, 5, 6
 };
@@ -237,16 +239,15 @@ struct StripCtx {
       st.qraw[md<6>(Q)][2] = qf[2 * qps + cell];
     }
   }
-  // The collision of a cell of the row in ring slot Q; with a running-mean
-  // reference the slot then holds the cell's updated reference.
-  template <int Q>
-  __device__ __forceinline__ void collide_at(StripState<C, K> &st, C g[9]) const {
-    const C chi = chi_of(st.craw[md<6>(Q)]);
+  // The collision of a cell with sponge input `raw` and reference state q; with
+  // a running-mean reference q then holds the cell's updated one.
+  __device__ __forceinline__ void collide_cell(C raw, C q[3], C g[9]) const {
+    const C chi = chi_of(raw);
     if constexpr (QF) {
       CollideParams<C> pc = p;
-      pc.dcf0 = st.qraw[md<6>(Q)][0];
-      pc.dcf1 = st.qraw[md<6>(Q)][1];
-      pc.dcf2 = st.qraw[md<6>(Q)][2];
+      pc.dcf0 = q[0];
+      pc.dcf1 = q[1];
+      pc.dcf2 = q[2];
       // pre-collision conserved moments (rows 0-2 of M, summed as the
       // collision sums them)
       C dr = C(0), djx = C(0), djy = C(0);
@@ -259,9 +260,9 @@ struct StripCtx {
       if (!FREE && ((VAR & V_MASK) == V_I || (VAR & V_MASK) == V_II)) ref_moments(pc, mr);
       collide<C, VAR & V_MASK, (VAR & V_DEF) != 0, FREE>(g, chi, pc, mr);
       if constexpr (QA) {
-        st.qraw[md<6>(Q)][0] = fmaC(alpha, dr - pc.dcf0, pc.dcf0);
-        st.qraw[md<6>(Q)][1] = fmaC(alpha, djx - pc.dcf1, pc.dcf1);
-        st.qraw[md<6>(Q)][2] = fmaC(alpha, djy - pc.dcf2, pc.dcf2);
+        q[0] = fmaC(alpha, dr - pc.dcf0, pc.dcf0);
+        q[1] = fmaC(alpha, djx - pc.dcf1, pc.dcf1);
+        q[2] = fmaC(alpha, djy - pc.dcf2, pc.dcf2);
       }
     } else {
       collide<C, VAR & V_MASK, (VAR & V_DEF) != 0, FREE>(g, chi, p, mref);
@@ -329,8 +330,19 @@ struct StripCtx {
     load_256<P + 1>(st, r_next);
     // the cell inputs of row a + 1 go to another ring slot than row a - 1's,
     // and are first needed in the next iteration
+    if constexpr (K > 4) {
+      st.craw_old[1] = st.craw_old[0];
+      st.craw_old[0] = st.craw[md<6>(P + 1)];
+      if constexpr (QF) {
+#pragma unroll
+        for (int i = 0; i < 3; ++i) {
+          st.qraw_old[1][i] = st.qraw_old[0][i];
+          st.qraw_old[0][i] = st.qraw[md<6>(P + 1)][i];
+        }
+      }
+    }
     row_inputs<P + 1>(st, r_next);
-    collide_at<P - 1>(st, g);
+    collide_cell(st.craw[md<6>(P - 1)], st.qraw[md<6>(P - 1)], g);
     chain<P, J, 2>(st, g, a);
   }
 
@@ -347,7 +359,8 @@ struct StripCtx {
       pull<C>(st.b256[j - 2][md<3>(P - j - 1)], st.b013[j - 2][md<2>(P - j)], g[4], g[7], g[8],
               o);
       keep<j - 1, P - (j - 1)>(st, g);
-      collide_at<P - j>(st, o);
+      C *q = j > 4 ? st.qraw_old[j > 4 ? j - 5 : 0] : st.qraw[md<6>(P - j)];
+      collide_cell(j > 4 ? st.craw_old[j > 4 ? j - 5 : 0] : st.craw[md<6>(P - j)], q, o);
       if constexpr (j == K) {
         if (store_lane) {
 #pragma unroll
@@ -356,9 +369,9 @@ struct StripCtx {
         if constexpr (QA) {
           if (store_lane) {
             const int64_t cell = (int64_t)(a - K) * pitch + X0 + (threadIdx.x & 63) - K;
-            qf_out[cell] = st.qraw[md<6>(P - K)][0];
-            qf_out[qps + cell] = st.qraw[md<6>(P - K)][1];
-            qf_out[2 * qps + cell] = st.qraw[md<6>(P - K)][2];
+            qf_out[cell] = q[0];
+            qf_out[qps + cell] = q[1];
+            qf_out[2 * qps + cell] = q[2];
           }
         }
       } else {
@@ -471,7 +484,7 @@ __device__ __forceinline__ void strip_run(const StripCtx<S, VAR, CHI, K> &c, int
   c.template load_478<3>(st, next(r));
   // Iterations q = 2 .. R + 2K - 1 at input rows a = Y0 - K + q. Step j runs
   // from q = 2j on: q = 2, 3 run step 1, q = 4, 5 steps 1-2, q = 6, 7 steps
-  // 1-3, and from q = 2K on all K steps run (R iterations).
+  // 1-3, ..., and from q = 2K on all K steps run (R iterations).
   int a = c.Y0 - K + 2;
   r = next(r);
   c.template iter<2, 1>(st, a, r, next(r));
@@ -494,6 +507,22 @@ __device__ __forceinline__ void strip_run(const StripCtx<S, VAR, CHI, K> &c, int
     r = next(r);
     c.template iter<1, 3>(st, a, r, next(r));
   }
+  if constexpr (K >= 5) {
+    ++a;
+    r = next(r);
+    c.template iter<2, 4>(st, a, r, next(r));
+    ++a;
+    r = next(r);
+    c.template iter<3, 4>(st, a, r, next(r));
+  }
+  if constexpr (K >= 6) {
+    ++a;
+    r = next(r);
+    c.template iter<4, 5>(st, a, r, next(r));
+    ++a;
+    r = next(r);
+    c.template iter<5, 5>(st, a, r, next(r));
+  }
   int left = R;  // iterations with all K steps
 #define LBM_STRIP_ITER(PH)                                          \
   ++a;                                                              \
@@ -511,16 +540,16 @@ __device__ __forceinline__ void strip_run(const StripCtx<S, VAR, CHI, K> &c, int
 #undef LBM_STRIP_ITER
 }
 
-// One strip, in the form that its part of the layer needs. In FP16 storage,
-// whose strips are bound by VALU issue, a strip clear of the layer (0.90 of the
-// waves of 4096^2 with a 64-cell layer) runs the collision without the
-// damping's products with 0, same values: 4096^2 Type II 210 -> 229 GLUPS (three
-// steps, block 64, rows 32). In FP32 the strips of this width move memory at
-// 4.7 TB/s whether they collide or not (265 us a launch without the collision,
-// 285 with it) and gained 2%; in FP64 the second loop's registers took 9% from
-// batches: these keep the one loop. The choice is made once per strip, so each
-// row loop stays one block; the waves of a workgroup may differ, both loops
-// pass one barrier per row.
+// One strip, in the form that its part of the layer needs. In FP16 storage and
+// beyond four steps, which are bound by VALU issue, a strip clear of the layer
+// (0.90 of the waves of 4096^2 with a 64-cell layer) runs the collision without the
+// damping's products with 0, same values: 4096^2 Type II FP16 210 -> 229 GLUPS
+// (three steps, block 64, rows 32), FP32 with six steps 257 -> 265. Four steps in
+// FP32 move memory at 4.7 TB/s whether they collide or not (265 us a launch without
+// the collision, 285 with it) and gained 2%; in FP64 the second loop's registers
+// took 9% from batches: these keep the one loop. The choice is made once per
+// strip, so each row loop stays one block; the waves of a workgroup may differ,
+// both loops pass one barrier per row.
 template <typename S, int VAR, int CHI, int K>
 __device__ __forceinline__ void strip_do(const S *src, S *dst, int nx, int ny, int64_t pitch,
                                          int64_t ps, int strip, bool idle, int Y0, int R, int nw,
@@ -539,7 +568,7 @@ __device__ __forceinline__ void strip_do(const S *src, S *dst, int nx, int ny, i
               chi_mode, scale, inv_scale, p, qf, qps, qf_out, alpha);
   // (default parameters only, which halves the instances; the undamped scheme
   // is its own free form)
-  constexpr bool LAYER = sizeof(S) == 2 && (VAR & V_MASK) != V_NONE && (VAR & V_DEF) != 0 &&
+  constexpr bool LAYER = (sizeof(S) == 2 || K > 4) && (VAR & V_MASK) != V_NONE && (VAR & V_DEF) != 0 &&
                          CHI != CHI_FIELD;
   if constexpr (LAYER) {
     if (CHI == CHI_ZERO || strip_is_free(c, R)) {
@@ -773,6 +802,12 @@ static hipError_t launch_multi(const StepConfig &c, int k, const void *src, void
     case 2: return launch_multi_k<S, VAR, CHI, 2>(c, src, dst, stream);
     case 3: return launch_multi_k<S, VAR, CHI, 3>(c, src, dst, stream);
     case 4: return launch_multi_k<S, VAR, CHI, 4>(c, src, dst, stream);
+  }
+  if constexpr (sizeof(S) == 4 && (VAR & V_DEF) != 0 && (VAR & V_QA) == 0) {
+    switch (k) {
+      case 5: return launch_multi_k<S, VAR, CHI, 5>(c, src, dst, stream);
+      case 6: return launch_multi_k<S, VAR, CHI, 6>(c, src, dst, stream);
+    }
   }
   return hipErrorInvalidValue;
 }

@@ -1,0 +1,77 @@
+"""Five and six steps per launch of the FP32 strips: bit for bit single steps, on
+lattices narrower than a strip, at the edges of strips, chunks and wraps, for
+every count of steps, variant, sponge form and block, and with checks that fall
+between launches."""
+import numpy as np
+import pytest
+
+pytestmark = pytest.mark.gpu
+
+torch = pytest.importorskip("torch")
+from paper_1203_6350_amd import lbm, workloads as wl  # noqa: E402
+
+# large enough that strips are taken, not square tiles; strips hold 52 or 54 columns
+SHAPES = [(1, 900001), (5, 300007), (900001, 1), (53, 30011), (105, 20000), (1041, 1009), (4096, 307),
+          (60000, 23)]
+
+
+def pair(nx, ny, variant, sponge, tuning, seed):
+    out = []
+    g = np.random.default_rng(seed)
+    f = [1.0 + 1e-3 * g.standard_normal((ny, nx))] + [0.05 + 1e-3 * g.standard_normal((ny, nx))
+                                                      for _ in range(2)]
+    top = 0.5 if variant == "visc" else 0.05 if variant == "I" else 0.3
+    cx, cy = (top * g.random(n) * (g.random(n) < 0.5) for n in (nx, ny))
+    for one in (False, True):
+        lat = lbm.Lattice(nx, ny, s=wl.S_MRT_DEFAULT, storage="f32", variant=variant, ux_base=0.05,
+                          uy_base=0.05, rho=f[0], ux=f[1], uy=f[2])
+        if sponge == "field":
+            lat.set_sponge(np.maximum(cx[None, :], cy[:, None]), (1.001, 0.06, 0.04))
+        elif sponge:
+            lat.set_sponge_separable(cx, cy, sponge, (1.001, 0.06, 0.04))
+        if one:
+            lbm.lbm_set_tuning(lat.h, 0, 256)
+        elif tuning:
+            lbm.lbm_set_tuning(lat.h, *tuning)
+        out.append(lat)
+    return out
+
+
+def check(a, r, n):
+    a.step(n)
+    r.step(n)
+    assert np.array_equal(a.populations(), r.populations(), equal_nan=True)
+
+
+@pytest.mark.parametrize("nx,ny", SHAPES)
+def test_shapes_and_step_counts(nx, ny):
+    a, r = pair(nx, ny, "II", "max", None, nx + ny)
+    for n in (6, 5, 7, 10, 11, 13):
+        check(a, r, n)
+
+
+@pytest.mark.parametrize("variant,sponge", [("none", None), ("I", "max"), ("II", "sum"), ("II", "field"),
+                                            ("III", "field"), ("III", "max"), ("visc", "max")])
+def test_variants_and_sponges(variant, sponge):
+    a, r = pair(1050, 1003, variant, sponge, None, 5)
+    for n in (12, 11):
+        check(a, r, n)
+
+
+@pytest.mark.parametrize("block", [64, 128, 256, 512])
+def test_blocks(block):
+    a, r = pair(1207, 990, "II", "max", (4, block, 0, 0), block)
+    for n in (6, 4, 17, 1):
+        check(a, r, n)
+
+
+def test_checks_between_launches():
+    """A detector that is due every 7 steps trips at the check that it had with
+    four steps per launch."""
+    a, r = pair(1100, 1000, "none", None, (4, 256, 0, 0), 3)
+    for lat in (a, r):
+        lbm.lbm_set_detector(lat.h, 7, 1e-9)
+    a.step(50)
+    with pytest.raises(lbm.LbmUnstable):
+        a.sync()
+    assert a.detector_status() == 8  # the first launch of four steps that ends at or after 7
