@@ -88,11 +88,12 @@ def valu_issue(tuning):
 
 
 def launch_steps(tuning, storage="f32"):
-    """Time steps per launch of a launch shape: its step count, or six for the
-    four-step shape with fitted rows in FP32 (without a running-mean reference)."""
+    """Time steps per launch of a launch shape: its step count, or for the
+    four-step shape with fitted rows six in FP32 and five in FP64 (without a
+    running-mean reference)."""
     k = tuning["kernel"]
-    if k == 4 and tuning.get("rows", 0) == 0 and storage == "f32":
-        return 6
+    if k == 4 and tuning.get("rows", 0) == 0:
+        return {"f32": 6, "f64": 5, "f16": 4}[storage]
     return k if k >= 2 else 1
 
 

@@ -302,7 +302,7 @@ int lbm_set_line_source(lbm_handle *h, const lbm_line_source *src, int32_t outfl
  * A handle whose shape has not been set (lbm_set_tuning, lbm_autotune) leaves
  * the choice to lbm_step, by size, storage and number of steps: the tile
  * kernel on lattices too small to fill the device with strips, else strips of
- * four (FP32: up to six) steps; lbm_get_tuning then reports the shape of its single steps.
+ * four steps (up to six in FP32, five in FP64); lbm_get_tuning then reports the shape of its single steps.
  * Whatever the kernel, the lattice buffer that is current after a call is the
  * one that the set shape's own launches (one per step, if none is set) would
  * have left current, so a captured sequence of an even number of them can be
@@ -328,8 +328,9 @@ typedef struct lbm_tuning {
   int32_t rows;        /* kernels 2-4: rows per chunk, 1..4096, or 0 to fit
                           the launch to the device: the height at which all
                           blocks are resident at once (kernel 4 then takes up
-                          to six steps per launch in FP32 with s0 = s1 = s2 =
-                          0, shift_n = shift_m and no running mean), or, on a
+                          to six steps per launch in FP32 and five in FP64
+                          with s0 = s1 = s2 = 0, shift_n = shift_m and no
+                          running mean, in FP64 no reference field), or, on a
                           lattice too small for that to pay, the tile kernel
                           with up to 14 steps per launch; ignored by kernels
                           0 and 1                                            */

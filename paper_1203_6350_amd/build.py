@@ -20,7 +20,8 @@ SOURCES = [(f, [], f.rsplit(".", 1)[0]) for f in
            ("lbm_api.cpp", "lbm_kernels.hip", "lbm_vn.hip", "lbm_batch.hip", "lbm3_kernels.hip",
             "lbm_readout.cpp")]
 SOURCES += [("lbm_strip_%s.hip" % st, ["-DLBM_STRIP_ONLY_K=%d" % k], "lbm_strip_%s_k%d" % (st, k))
-            for st in ("f32", "f64", "f16") for k in (6, 5, 4, 3, 2) if k <= 4 or st == "f32"]
+            for st in ("f32", "f64", "f16") for k in (6, 5, 4, 3, 2)
+            if k <= {"f32": 6, "f64": 5, "f16": 4}[st]]
 SOURCES += [("lbm_tile_%s.hip" % st, [], "lbm_tile_%s" % st) for st in ("f32", "f64", "f16")]
 
 # - no automatic FMA contraction: the kernels place their fused multiply-adds

@@ -483,19 +483,18 @@ StepPlan step_plan(const lbm_handle *h, int64_t n) {
   if (n < 2 || !strips || (h->shape_set && !chosen)) return p;
   p.kind = StepPlan::STRIP;
   p.cfg = h->cfg;
-  // fitted rows of the four-step shape: six steps where the kernel has them
-  const bool six = lbm::six_steps_support(h->cfg);
+  const int fitted = lbm::fitted_steps(h->cfg);
   if (h->shape_set) {
-    p.most = k == 4 && h->cfg.rows == 0 && six ? 6 : k;
+    p.most = k == 4 && h->cfg.rows == 0 ? fitted : k;
     return p;
   }
   // as created: the shape that is fastest or within 5% of it from 300^2 to 3000
   // x 2500 cells (wide workgroups pay once the chunks are tall)
-  p.most = six ? 6 : 4;
+  p.most = fitted;
   p.cfg.kernel = 4;
   p.cfg.rows = 0;
   p.cfg.block = h->user.storage == LBM_STORAGE_F16                      ? 64
-                : six || (int64_t)h->user.nx * h->user.ny >= 3000000 ? 256
+                : fitted == 6 || (int64_t)h->user.nx * h->user.ny >= 3000000 ? 256
                 : h->user.storage == LBM_STORAGE_F64                  ? 128
                                                                         : 64;
   return p;

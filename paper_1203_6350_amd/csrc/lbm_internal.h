@@ -44,9 +44,9 @@ struct StepConfig {
 enum { KERNEL_GENERIC = 0, KERNEL_VEC = 1, KERNEL_MULTI_MIN = 2, KERNEL_MULTI_MAX = 4 };
 
 // Largest workgroup of the single-lattice K-step kernel: FP64 storage with
-// four steps per launch is built for one wave per SIMD (its registers do
+// four or five steps per launch is built for one wave per SIMD (its registers do
 // not fit two), so its workgroups take at most 256 threads.
-constexpr int multi_step_max_block(int storage, int k) { return storage == 0 && k == 4 ? 256 : 512; }
+constexpr int multi_step_max_block(int storage, int k) { return storage == 0 && k >= 4 ? 256 : 512; }
 
 // The strip kernels address a lane's column within a row as a 32-bit byte
 // offset and read a row through a buffer range of the row's byte count (a
@@ -74,18 +74,26 @@ inline bool multi_step_supports(const StepConfig &c) {
   return (float)c.s[0] == 0.0f && (float)c.s[1] == 0.0f && (float)c.s[2] == 0.0f &&
          (float)c.n == (float)c.m;
 }
-// Five and six steps per launch: FP32 in the default form without a running-mean
-// reference. A launch costs its memory traffic whether it collides four or six
-// times: from four to six steps 4096^2 goes from 235 to 260 GLUPS, 2048^2 from 204 to
-// 231, 1024^2 from 135 to 146 (each in its best block of fitted rows), 2048^2 with a
-// per-cell reference from 191 to 211. A running mean's values do not fit the
-// registers (164 -> 151), nor do FP64's; FP16 is bound by VALU issue already.
-inline bool six_steps_support(const StepConfig &c) {
-  return c.storage == 1 && multi_step_supports(c) && !(c.qfield && c.qalpha != 0.0) && (float)c.s[0] == 0.0f &&
-         (float)c.s[1] == 0.0f && (float)c.s[2] == 0.0f && (float)c.n == (float)c.m;
+// Steps per launch of the four-step shape with fitted rows: six in FP32 and five in
+// FP64, in the default form without a running-mean reference (FP64: without any).
+// A launch costs its memory traffic whether it collides four or six times. FP32,
+// from four to six steps: 4096^2 from 235 to 265 GLUPS, 2048^2 from 204 to 229,
+// 1024^2 from 135 to 146 (each in its best block of fitted rows), 2048^2 with a
+// per-cell reference from 191 to 211. FP64, from four to five: 4096^2 from 124 to 130,
+// 2048^2 from 110 to 123, 1300 x 1200 from 94 to 105 (six: 129, 122, 104). A running
+// mean's values do not fit the registers (FP32 164 -> 151), and FP16 is bound by VALU
+// issue already (five steps: 227 -> 208).
+inline int fitted_steps(const StepConfig &c) {
+  if (!multi_step_supports(c) || c.storage == 2) return 4;
+  if (c.storage == 0)
+    return !c.qfield && c.s[0] == 0.0 && c.s[1] == 0.0 && c.s[2] == 0.0 && c.n == c.m ? 5 : 4;
+  return !(c.qfield && c.qalpha != 0.0) && (float)c.s[0] == 0.0f && (float)c.s[1] == 0.0f &&
+                 (float)c.s[2] == 0.0f && (float)c.n == (float)c.m
+             ? 6
+             : 4;
 }
-// k = 2..4 time steps in one launch (src at t -> dst at t + k), 2..6 where
-// six_steps_support.
+// k = 2..4 time steps in one launch (src at t -> dst at t + k), and up to
+// fitted_steps.
 hipError_t launch_multi_steps(const StepConfig &c, int k, const void *src, void *dst,
                               hipStream_t stream);
 // Tile kernel (lbm_tile_f64/f32/f16.hip): 1..TILE_MAX_STEPS steps in one
@@ -240,6 +248,7 @@ int batch_multi_per_cu(int storage, int k, int nw, int form);
 LBM_STRIP_DECL_K(f64)
 LBM_STRIP_DECL_K(f32)
 LBM_STRIP_DECL_K(f16)
+hipError_t launch_multi_f64_k5(const StepConfig &c, const void *src, void *dst, hipStream_t stream);
 hipError_t launch_multi_f32_k5(const StepConfig &c, const void *src, void *dst, hipStream_t stream);
 hipError_t launch_multi_f32_k6(const StepConfig &c, const void *src, void *dst, hipStream_t stream);
 

@@ -417,10 +417,10 @@ hipError_t launch_multi_steps(const StepConfig &c, int k, const void *src, void 
   }                                                                    \
   return hipErrorInvalidValue;
   if (k > 4) {
-    if (!six_steps_support(c)) return hipErrorInvalidValue;
-    return k == 5   ? launch_multi_f32_k5(c, src, dst, stream)
-           : k == 6 ? launch_multi_f32_k6(c, src, dst, stream)
-                    : hipErrorInvalidValue;
+    if (k > fitted_steps(c)) return hipErrorInvalidValue;
+    return c.storage == 0 ? launch_multi_f64_k5(c, src, dst, stream)
+           : k == 5       ? launch_multi_f32_k5(c, src, dst, stream)
+                          : launch_multi_f32_k6(c, src, dst, stream);
   }
   switch (c.storage) {
     case 0: { LBM_MULTI_K(f64) }

@@ -15,7 +15,7 @@ namespace lbm {
 
 // ---------------------------------------------------------------- several steps per launch
 // Temporal blocking: one launch advances the lattice by K = 2, 3 or 4 time
-// steps (FP32 also 5 and 6), reading and writing it once.
+// steps (FP32 also 5 and 6, FP64 5), reading and writing it once.
 //
 // Each wave owns a strip of STRIP = 64 - 2K output columns of one chunk of
 // rows: lane l holds column X0 - K + l (mod nx), so the 64 lanes cover the
@@ -540,8 +540,8 @@ __device__ __forceinline__ void strip_run(const StripCtx<S, VAR, CHI, K> &c, int
 #undef LBM_STRIP_ITER
 }
 
-// One strip, in the form that its part of the layer needs. In FP16 storage and
-// beyond four steps, which are bound by VALU issue, a strip clear of the layer
+// One strip, in the form that its part of the layer needs. In FP16 storage and in
+// FP32 beyond four steps, which are bound by VALU issue, a strip clear of the layer
 // (0.90 of the waves of 4096^2 with a 64-cell layer) runs the collision without the
 // damping's products with 0, same values: 4096^2 Type II FP16 210 -> 229 GLUPS
 // (three steps, block 64, rows 32), FP32 with six steps 257 -> 265. Four steps in
@@ -568,7 +568,7 @@ __device__ __forceinline__ void strip_do(const S *src, S *dst, int nx, int ny, i
               chi_mode, scale, inv_scale, p, qf, qps, qf_out, alpha);
   // (default parameters only, which halves the instances; the undamped scheme
   // is its own free form)
-  constexpr bool LAYER = (sizeof(S) == 2 || K > 4) && (VAR & V_MASK) != V_NONE && (VAR & V_DEF) != 0 &&
+  constexpr bool LAYER = (sizeof(S) == 2 || (sizeof(S) == 4 && K > 4)) && (VAR & V_MASK) != V_NONE && (VAR & V_DEF) != 0 &&
                          CHI != CHI_FIELD;
   if constexpr (LAYER) {
     if (CHI == CHI_ZERO || strip_is_free(c, R)) {
@@ -584,13 +584,13 @@ __device__ __forceinline__ void strip_do(const S *src, S *dst, int nx, int ny, i
   if constexpr (!LAYER || CHI != CHI_ZERO) strip_run(c, R);
 }
 
-// Waves per SIMD the single-lattice kernel may run: the FP64 four-step form
-// one (its 253 registers would fit two, but the fitted chunks then halve in
+// Waves per SIMD the single-lattice kernel may run: the FP64 five-step form (its
+// registers need both halves of the file) and four-step form one (its 253 registers would fit two, but the fitted chunks then halve in
 // height and the extra warm-up rows cost more than the second wave gains:
 // 0.530 against 0.539 ms per launch at 4096^2), the others unconstrained.
 template <typename S, int K>
 constexpr int strip_max_waves() {
-  return sizeof(S) == 8 && K == 4 ? 1 : 8;
+  return sizeof(S) == 8 && K >= 4 ? 1 : 8;
 }
 template <typename S, int VAR, int CHI, int K>
 __global__ __launch_bounds__(multi_step_max_block(sizeof(S) == 8 ? 0 : 1, K))
@@ -803,11 +803,15 @@ static hipError_t launch_multi(const StepConfig &c, int k, const void *src, void
     case 3: return launch_multi_k<S, VAR, CHI, 3>(c, src, dst, stream);
     case 4: return launch_multi_k<S, VAR, CHI, 4>(c, src, dst, stream);
   }
+  // (fitted_steps)
   if constexpr (sizeof(S) == 4 && (VAR & V_DEF) != 0 && (VAR & V_QA) == 0) {
     switch (k) {
       case 5: return launch_multi_k<S, VAR, CHI, 5>(c, src, dst, stream);
       case 6: return launch_multi_k<S, VAR, CHI, 6>(c, src, dst, stream);
     }
+  }
+  if constexpr (sizeof(S) == 8 && (VAR & V_DEF) != 0 && (VAR & V_QF) == 0) {
+    if (k == 5) return launch_multi_k<S, VAR, CHI, 5>(c, src, dst, stream);
   }
   return hipErrorInvalidValue;
 }

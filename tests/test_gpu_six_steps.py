@@ -1,4 +1,4 @@
-"""Five and six steps per launch of the FP32 strips: bit for bit single steps, on
+"""Five and six steps per launch of the strips (FP32, and five in FP64): bit for bit single steps, on
 lattices narrower than a strip, at the edges of strips, chunks and wraps, for
 every count of steps, variant, sponge form and block, and with checks that fall
 between launches."""
@@ -15,7 +15,7 @@ SHAPES = [(1, 900001), (5, 300007), (900001, 1), (53, 30011), (105, 20000), (104
           (60000, 23)]
 
 
-def pair(nx, ny, variant, sponge, tuning, seed):
+def pair(nx, ny, variant, sponge, tuning, seed, storage="f32"):
     out = []
     g = np.random.default_rng(seed)
     f = [1.0 + 1e-3 * g.standard_normal((ny, nx))] + [0.05 + 1e-3 * g.standard_normal((ny, nx))
@@ -23,7 +23,7 @@ def pair(nx, ny, variant, sponge, tuning, seed):
     top = 0.5 if variant == "visc" else 0.05 if variant == "I" else 0.3
     cx, cy = (top * g.random(n) * (g.random(n) < 0.5) for n in (nx, ny))
     for one in (False, True):
-        lat = lbm.Lattice(nx, ny, s=wl.S_MRT_DEFAULT, storage="f32", variant=variant, ux_base=0.05,
+        lat = lbm.Lattice(nx, ny, s=wl.S_MRT_DEFAULT, storage=storage, variant=variant, ux_base=0.05,
                           uy_base=0.05, rho=f[0], ux=f[1], uy=f[2])
         if sponge == "field":
             lat.set_sponge(np.maximum(cx[None, :], cy[:, None]), (1.001, 0.06, 0.04))
@@ -43,24 +43,27 @@ def check(a, r, n):
     assert np.array_equal(a.populations(), r.populations(), equal_nan=True)
 
 
+@pytest.mark.parametrize("storage", ["f32", "f64"])
 @pytest.mark.parametrize("nx,ny", SHAPES)
-def test_shapes_and_step_counts(nx, ny):
-    a, r = pair(nx, ny, "II", "max", None, nx + ny)
+def test_shapes_and_step_counts(nx, ny, storage):
+    a, r = pair(nx, ny, "II", "max", None, nx + ny, storage)
     for n in (6, 5, 7, 10, 11, 13):
         check(a, r, n)
 
 
+@pytest.mark.parametrize("storage", ["f32", "f64"])
 @pytest.mark.parametrize("variant,sponge", [("none", None), ("I", "max"), ("II", "sum"), ("II", "field"),
                                             ("III", "field"), ("III", "max"), ("visc", "max")])
-def test_variants_and_sponges(variant, sponge):
-    a, r = pair(1050, 1003, variant, sponge, None, 5)
+def test_variants_and_sponges(variant, sponge, storage):
+    a, r = pair(1050, 1003, variant, sponge, None, 5, storage)
     for n in (12, 11):
         check(a, r, n)
 
 
-@pytest.mark.parametrize("block", [64, 128, 256, 512])
-def test_blocks(block):
-    a, r = pair(1207, 990, "II", "max", (4, block, 0, 0), block)
+@pytest.mark.parametrize("storage,block", [("f32", 64), ("f32", 128), ("f32", 256), ("f32", 512),
+                                           ("f64", 64), ("f64", 128), ("f64", 256)])
+def test_blocks(storage, block):
+    a, r = pair(1207, 990, "II", "max", (4, block, 0, 0), block, storage)
     for n in (6, 4, 17, 1):
         check(a, r, n)
 
