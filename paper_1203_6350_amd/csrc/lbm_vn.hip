@@ -29,13 +29,17 @@
 // with flow), and the sweep has neither gathers nor predicates. Complex
 // products are fused multiply-adds.
 //
-// Bound by VALU issue at one wave per SIMD (512 registers): at level 8 half of
-// the 2330 instructions of a sweep are FP64, a third move the window between
-// the two halves of the register file, which hold it only together. One
-// window 0..8 in every sweep with the entries at a lane's own bottom selected
-// over all positions, and complex subdiagonals, took 15.7 ms for 64 sets x
-// 256^2 wavenumbers (268 M eigenproblems/s); the levels take 9.8 ms, with the
-// real subdiagonal 8.3 ms (505 M/s).
+// Bound by VALU issue at one wave per SIMD (0.69 busy): half of the instructions
+// are FP64, at level 8 a third move the window between the two halves of the
+// register file. Registers that do not fit went to scratch memory, whose waits
+// took a third of the time; so four rows of the matrix lie in LDS while it is
+// reduced, and the window's last column at levels 8 and 7 (38 KB, a quarter of the
+// CU's).
+//
+// 64 sets x 256^2 wavenumbers: 15.7 ms (268 M eigenproblems/s) with one window 0..8
+// in every sweep, the entries at a lane's own bottom selected over all
+// positions and complex subdiagonals; 9.8 ms by levels, 8.3 ms with the real
+// subdiagonal, 7.5 ms with the last column in LDS, 6.5 ms (641 M/s) with the rows.
 #include "lbm_device.h"
 #include "lbm_internal.h"
 
@@ -160,6 +164,28 @@ struct RegMat {
   }
 };
 
+// The matrix while it is reduced: its first VN_LDS_ROWS rows lie in LDS (a lane's
+// entries [(row * N + column) * 64]), which leaves the registers room for the
+// rest. The clobbers keep the compiler from carrying those rows in registers
+// after all.
+constexpr int VN_LDS_ROWS = 4;
+struct SplitMat {
+  RegMat H;
+  double2 *rows;
+  __device__ __forceinline__ cplx at(int i, int j) const {
+    if (i >= VN_LDS_ROWS) return H.at(i, j);
+    const double2 v = rows[(i * N + j) * 64];
+    return mk(v.x, v.y);
+  }
+  __device__ __forceinline__ void put(int i, int j, cplx v) {
+    if (i >= VN_LDS_ROWS)
+      H.put(i, j, v);
+    else
+      rows[(i * N + j) * 64] = make_double2(v.re, v.im);
+  }
+  __device__ __forceinline__ void settle() const { asm volatile("" ::: "memory"); }
+};
+
 // a b + c, a b, conj(a) b + c and c - a b with fused multiply-adds.
 __device__ __forceinline__ cplx cfma(cplx a, cplx b, cplx c) {
   return mk(__builtin_fma(a.re, b.re, __builtin_fma(-a.im, b.im, c.re)),
@@ -187,54 +213,79 @@ __device__ __forceinline__ double polar(cplx z, cplx &e) {
 // reflection of column k, x = H(k+1.., k), is I - tau v v^H with v = x/|x| + g e1,
 // g = +-1 of Re x0's sign and tau = g conj(v0)/|v0|^2: it maps x to -g |x| e1, and
 // |v0| >= 1. H <- (I - tau v v^H) H (I - tau v v^H)^H.
-__device__ __forceinline__ void hessenberg_reg(RegMat &H) {
+template <int k>
+__device__ __forceinline__ void reflect(SplitMat &H) {
+  double xn2 = 0.0;
+  cplx v[N];
 #pragma unroll
-  for (int k = 0; k < N - 2; ++k) {
-    double xn2 = 0.0;
+  for (int i = k + 1; i < N; ++i) {
+    v[i] = H.at(i, k);
+    xn2 = __builtin_fma(v[i].re, v[i].re, __builtin_fma(v[i].im, v[i].im, xn2));
+  }
+  const bool on = xn2 > 0.0;  // a zero column stays as it is
+  const double ixn = on ? rsqrt_f64(xn2) : 0.0;
+  const double g = v[k + 1].re >= 0.0 ? 1.0 : -1.0;
 #pragma unroll
-    for (int i = k + 1; i < N; ++i)
-      xn2 = __builtin_fma(H.r[i][k], H.r[i][k], __builtin_fma(H.m[i][k], H.m[i][k], xn2));
-    const bool on = xn2 > 0.0;  // a zero column stays as it is
-    const double ixn = on ? rsqrt_f64(xn2) : 0.0;
-    const double g = H.r[k + 1][k] >= 0.0 ? 1.0 : -1.0;
-    cplx v[N];
+  for (int i = k + 1; i < N; ++i) v[i] = scal(ixn, v[i]);
+  v[k + 1].re += g;
+  const cplx tau = scal(on ? g / norm2(v[k + 1]) : 0.0, conjc(v[k + 1]));
+  // left: rows k+1.., columns k+1..
 #pragma unroll
-    for (int i = k + 1; i < N; ++i) v[i] = scal(ixn, H.at(i, k));
-    v[k + 1].re += g;
-    const cplx tau = scal(on ? g / norm2(v[k + 1]) : 0.0, conjc(v[k + 1]));
-    // left: rows k+1.., columns k+1..
+  for (int j = k + 1; j < N; ++j) {
+    cplx w = mk(0.0, 0.0), x[N];
+#pragma unroll
+    for (int i = k + 1; i < N; ++i) {
+      x[i] = H.at(i, j);
+      w = cfma(conjc(v[i]), x[i], w);
+    }
+    w = neg(cmul(tau, w));
+#pragma unroll
+    for (int i = k + 1; i < N; ++i) H.put(i, j, cfma(v[i], w, x[i]));
+    H.settle();
+  }
+  // column k: (-g |x|, 0, ...); the entries below the subdiagonal become
+  // compile-time zeros, which frees their registers for the QR sweeps
+  // (they never read them)
+  H.put(k + 1, k, mk(-g * (xn2 * ixn), 0.0));
+#pragma unroll
+  for (int i = k + 2; i < N; ++i)
+    if (i >= VN_LDS_ROWS) H.put(i, k, mk(0.0, 0.0));
+  // right: all rows, columns k+1..
+#pragma unroll
+  for (int i = 0; i < N; ++i) {
+    cplx w = mk(0.0, 0.0), x[N];
 #pragma unroll
     for (int j = k + 1; j < N; ++j) {
-      cplx w = mk(0.0, 0.0);
-#pragma unroll
-      for (int i = k + 1; i < N; ++i) w = cfma(conjc(v[i]), H.at(i, j), w);
-      w = neg(cmul(tau, w));
-#pragma unroll
-      for (int i = k + 1; i < N; ++i) H.put(i, j, cfma(v[i], w, H.at(i, j)));
+      x[j] = H.at(i, j);
+      w = cfma(x[j], v[j], w);
     }
-    // column k: (-g |x|, 0, ...); the entries below the subdiagonal become
-    // compile-time zeros, which frees their registers for the QR sweeps
-    // (they never read them)
-    H.put(k + 1, k, mk(-g * (xn2 * ixn), 0.0));
+    w = neg(cmul(conjc(tau), w));
 #pragma unroll
-    for (int i = k + 2; i < N; ++i) H.put(i, k, mk(0.0, 0.0));
-    // right: all rows, columns k+1..
-#pragma unroll
-    for (int i = 0; i < N; ++i) {
-      cplx w = mk(0.0, 0.0);
-#pragma unroll
-      for (int j = k + 1; j < N; ++j) w = cfma(H.at(i, j), v[j], w);
-      w = neg(cmul(conjc(tau), w));
-#pragma unroll
-      for (int j = k + 1; j < N; ++j) H.put(i, j, cfma(w, conjc(v[j]), H.at(i, j)));
-    }
+    for (int j = k + 1; j < N; ++j) H.put(i, j, cfma(w, conjc(v[j]), x[j]));
+    H.settle();
   }
+}
+
+template <int k>
+__device__ __forceinline__ void reflect_from(SplitMat &H) {
+  reflect<k>(H);
+  if constexpr (k + 1 < N - 2) reflect_from<k + 1>(H);
+}
+
+__device__ __forceinline__ void hessenberg_reg(SplitMat &H) {
+  reflect_from<0>(H);
   // the last subdiagonal's phase e: row N - 1 times conj(e), column N - 1 times e
   const cplx y = H.at(N - 1, N - 2);
   cplx e;
   H.put(N - 1, N - 2, mk(polar(y, e), 0.0));
 #pragma unroll
   for (int i = 0; i < N - 1; ++i) H.put(i, N - 1, cmul(e, H.at(i, N - 1)));
+  // all in registers from here on
+#pragma unroll
+  for (int i = 0; i < VN_LDS_ROWS; ++i)
+#pragma unroll
+    for (int j = 0; j < N; ++j) H.H.put(i, j, j >= i - 1 ? H.at(i, j) : mk(0.0, 0.0));
+  H.settle();
 }
 
 // Wilkinson shift of [a b; c d], c real: its eigenvalue nearer d, d - bc / (p + y) with
@@ -284,6 +335,9 @@ __device__ __forceinline__ void right_rot(RegMat &H, int q, cplx c, double s) {
   H.put(q + 1, q + 1, scal(r, c));
 }
 
+// From this level on the last column above its diagonal lies in LDS (a lane's
+// entries [row * 64]).
+constexpr int VN_LDS_LEVEL = 7;
 constexpr int VN_MAX_SWEEPS = 40 * N;  // a lane's own, over all its eigenvalues
 
 // The entries of the level's window as new values. Without it an entry is one
@@ -300,6 +354,7 @@ __device__ __forceinline__ void detach_window(RegMat &H) {
   for (int i = 0; i <= h; ++i)
 #pragma unroll
     for (int j = i > 0 ? i - 1 : 0; j <= h; ++j) {
+      if (j == h && i < h && h >= VN_LDS_LEVEL) continue;
       H.r[i][j] = detach(H.r[i][j]);
       H.m[i][j] = detach(H.m[i][j]);
     }
@@ -313,9 +368,25 @@ __device__ __forceinline__ void detach_window(RegMat &H) {
 // it; every sweep is one of some lane at h, so the loop ends.
 template <int h>
 __device__ __forceinline__ void qr_level(RegMat &H, int &hi, int &it, int &sweeps, double2 *ev,
-                                         int stride) {
+                                         int stride, double2 *col) {
+  constexpr bool LDS = h >= VN_LDS_LEVEL;
   constexpr int l = h > 2 ? h - 1 : h;  // the lowest window end that takes part
   const double eps = 2.220446049250313e-16;
+  auto last = [&](int i) {  // H(i, h), i < h
+    if (!LDS) return H.at(i, h);
+    const double2 v = col[i * 64];
+    return mk(v.x, v.y);
+  };
+  auto set_last = [&](int i, cplx v) {
+    if (LDS)
+      col[i * 64] = make_double2(v.re, v.im);
+    else
+      H.put(i, h, v);
+  };
+  if (LDS) {
+#pragma unroll
+    for (int i = 0; i < h; ++i) col[i * 64] = make_double2(H.r[i][h], H.m[i][h]);
+  }
   detach_window<h>(H);
   for (;;) {
 #pragma unroll
@@ -337,7 +408,7 @@ __device__ __forceinline__ void qr_level(RegMat &H, int &hi, int &it, int &sweep
     const double c = top ? H.r[h][h - 1] : H.r[l][l - 1];
     const cplx d = pick2(top, H.at(h, h), H.at(l, l));
     cplx mu = shift_of(pick2(top, H.at(h - 1, h - 1), H.at(l - 1, l - 1)),
-                       pick2(top, H.at(h - 1, h), H.at(l - 1, l)), c, d);
+                       pick2(top, last(h - 1), H.at(l - 1, l)), c, d);
     if (it == 10 || it == 20)
       mu = mk(d.re + __builtin_fma(0.75, fabs(c), fabs(top || l < 2 ? H.r[h - 1][h - 2]
                                                                     : H.r[l - 1][l - 2])), d.im);
@@ -353,7 +424,7 @@ __device__ __forceinline__ void qr_level(RegMat &H, int &hi, int &it, int &sweep
     // maps its own column's pair (x, y) to (r, 0), r real. With y = 0 at the
     // window's end it takes R's last diagonal entry to its modulus, which
     // keeps the subdiagonal real.
-    cplx cp = mk(1.0, 0.0);
+    cplx cp = mk(1.0, 0.0), run = last(0);  // run: H(k, h)
     double sp = 0.0;
 #pragma unroll
     for (int k = 0; k < h; ++k) {
@@ -366,20 +437,28 @@ __device__ __forceinline__ void qr_level(RegMat &H, int &hi, int &it, int &sweep
       const double s = y * ir;
       H.put(k, k, mk(n2 * ir, 0.0));
 #pragma unroll
-      for (int j = k + 1; j <= h; ++j) {
+      for (int j = k + 1; j < h; ++j) {
         const cplx a = H.at(k, j), b = H.at(k + 1, j);
         H.put(k, j, rot1(cc, s, a, b));
         H.put(k + 1, j, rot2(cc, s, a, b));
       }
+      const cplx b = k + 1 < h ? last(k + 1) : H.at(h, h);
+      set_last(k, rot1(cc, s, run, b));
+      run = rot2(cc, s, run, b);
       if (k > 0) right_rot(H, k - 1, cp, sp);
       cp = conjc(cc);
       sp = s;
     }
     cplx e;
-    H.put(h, h, mk(polar(H.at(h, h), e), 0.0));
-    right_rot(H, h - 1, cp, sp);
+    const double r = polar(run, e);
 #pragma unroll
-    for (int i = 0; i <= h; ++i) H.put(i, h, cmul(e, H.at(i, h)));
+    for (int i = 0; i < h; ++i) {
+      const cplx a = H.at(i, h - 1), b = last(i);
+      H.put(i, h - 1, rot1(cp, sp, a, b));
+      set_last(i, cmul(e, rot2(cp, sp, a, b)));
+    }
+    H.put(h, h - 1, mk(sp * r, 0.0));
+    H.put(h, h, cmul(e, scal(r, cp)));
 #pragma unroll
     for (int i = 0; i <= h; ++i) H.put(i, i, add(H.at(i, i), mu));
   }
@@ -387,16 +466,16 @@ __device__ __forceinline__ void qr_level(RegMat &H, int &hi, int &it, int &sweep
 
 template <int h>
 __device__ __forceinline__ void qr_levels(RegMat &H, int &hi, int &it, int &sweeps, double2 *ev,
-                                          int stride) {
-  qr_level<h>(H, hi, it, sweeps, ev, stride);
-  if constexpr (h > 2) qr_levels<h - 1>(H, hi, it, sweeps, ev, stride);
+                                          int stride, double2 *col) {
+  qr_level<h>(H, hi, it, sweeps, ev, stride, col);
+  if constexpr (h > 2) qr_levels<h - 1>(H, hi, it, sweeps, ev, stride, col);
 }
 
 // Eigenvalues of the upper Hessenberg H. Returns false if the lane did not
 // converge within VN_MAX_SWEEPS sweeps.
-__device__ __forceinline__ bool qr_reg(RegMat &H, double2 *ev, int stride) {
+__device__ __forceinline__ bool qr_reg(RegMat &H, double2 *ev, int stride, double2 *col) {
   int hi = N - 1, it = 0, sweeps = 0;
-  qr_levels<N - 1>(H, hi, it, sweeps, ev, stride);
+  qr_levels<N - 1>(H, hi, it, sweeps, ev, stride, col);
   if (hi == 1) {
     const cplx a = H.at(0, 0), b = H.at(0, 1), c = H.at(1, 0), d = H.at(1, 1);
     cplx l0 = a, l1 = d;
@@ -419,7 +498,10 @@ __global__ __launch_bounds__(64) void vn_kernel(const VnParamsDev *__restrict__ 
                                                 double *__restrict__ G) {
   __shared__ double Are[81];  // A = M^-1 A_m M
   __shared__ double Am[81];
-  __shared__ double2 evs[N * 64];  // eigenvalues as they deflate, [index][lane]
+  // the reduction's rows; then the eigenvalues as they deflate, [index][lane],
+  // and the window's last column, [row][lane]. 38 KB with A: a block per SIMD.
+  __shared__ double2 work[VN_LDS_ROWS * N * 64];
+  static_assert(VN_LDS_ROWS * N >= 2 * N - 1, "eigenvalues and column");
   const int pset = blockIdx.y;
   const int t = threadIdx.x;
   if (t == 0) build_Am(params[pset], Am);
@@ -440,7 +522,10 @@ __global__ __launch_bounds__(64) void vn_kernel(const VnParamsDev *__restrict__ 
   // so that every lane of the wave runs the same sweeps
   const int64_t kk = kidx < nk ? kidx : nk - 1;
   const double k1 = kx[kk], k2 = ky[kk];
-  RegMat H;
+  double2 *const evs = work, *const col = work + N * 64;
+  const int64_t out = (int64_t)pset * nk + kidx;
+  SplitMat S;
+  S.rows = work + t;
 #pragma unroll
   for (int i = 0; i < N; ++i) {
     const double ph = -(k1 * cx_of(i) + k2 * cy_of(i));
@@ -449,20 +534,16 @@ __global__ __launch_bounds__(64) void vn_kernel(const VnParamsDev *__restrict__ 
 #pragma unroll
     for (int j = 0; j < N; ++j) {
       const double a = Are[i * 9 + j];
-      H.r[i][j] = cp * a;
-      H.m[i][j] = sp * a;
+      S.put(i, j, mk(cp * a, sp * a));
+      if (G && kidx < nk) {
+        G[(out * 81 + i * N + j) * 2] = cp * a;
+        G[(out * 81 + i * N + j) * 2 + 1] = sp * a;
+      }
     }
   }
-  const int64_t out = (int64_t)pset * nk + kidx;
-  if (G && kidx < nk) {
-#pragma unroll
-    for (int e = 0; e < 81; ++e) {
-      G[(out * 81 + e) * 2] = H.r[e / 9][e % 9];
-      G[(out * 81 + e) * 2 + 1] = H.m[e / 9][e % 9];
-    }
-  }
-  hessenberg_reg(H);
-  const bool ok = qr_reg(H, evs + t, 64);
+  S.settle();
+  hessenberg_reg(S);
+  const bool ok = qr_reg(S.H, evs + t, 64, col + t);
   if (kidx >= nk) return;
   cplx ev[N];
   double mag[N];
