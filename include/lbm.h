@@ -329,8 +329,7 @@ typedef struct lbm_tuning {
                           the launch to the device: the height at which all
                           blocks are resident at once (kernel 4 then takes up
                           to six steps per launch in FP32 and five in FP64
-                          with s0 = s1 = s2 = 0, shift_n = shift_m and no
-                          running mean, in FP64 no reference field), or, on a
+                          with s0 = s1 = s2 = 0 and shift_n = shift_m), or, on a
                           lattice too small for that to pay, the tile kernel
                           with up to 14 steps per launch; ignored by kernels
                           0 and 1                                            */

@@ -75,22 +75,24 @@ inline bool multi_step_supports(const StepConfig &c) {
          (float)c.n == (float)c.m;
 }
 // Steps per launch of the four-step shape with fitted rows: six in FP32 and five in
-// FP64, in the default form without a running-mean reference (FP64: without any).
+// FP64, in the default form (FP64: without a per-cell reference).
 // A launch costs its memory traffic whether it collides four or six times. FP32,
 // from four to six steps: 4096^2 from 235 to 265 GLUPS, 2048^2 from 204 to 229,
 // 1024^2 from 135 to 146 (each in its best block of fitted rows), 2048^2 with a
-// per-cell reference from 191 to 211. FP64, from four to five: 4096^2 from 124 to 130,
-// 2048^2 from 110 to 123, 1300 x 1200 from 94 to 105 (six: 129, 122, 104). A running
-// mean's values do not fit the registers (FP32 164 -> 151), and FP16 is bound by VALU
-// issue already (five steps: 227 -> 208).
+// per-cell reference from 191 to 211; with a running mean five steps (six do not fit
+// the registers, 2048^2 164 -> 151), from 2 million cells on (4096^2 188 -> 195, 2048^2
+// 167 -> 176, but 1200^2 147 -> 145). FP64, from four to five: 4096^2 from 124 to 130,
+// 2048^2 from 110 to 123, 1300 x 1200 from 94 to 105 (six: 129, 122, 104). FP16 is
+// bound by VALU issue already (five steps: 227 -> 208).
 inline int fitted_steps(const StepConfig &c) {
   if (!multi_step_supports(c) || c.storage == 2) return 4;
   if (c.storage == 0)
     return !c.qfield && c.s[0] == 0.0 && c.s[1] == 0.0 && c.s[2] == 0.0 && c.n == c.m ? 5 : 4;
-  return !(c.qfield && c.qalpha != 0.0) && (float)c.s[0] == 0.0f && (float)c.s[1] == 0.0f &&
-                 (float)c.s[2] == 0.0f && (float)c.n == (float)c.m
-             ? 6
-             : 4;
+  if ((float)c.s[0] != 0.0f || (float)c.s[1] != 0.0f || (float)c.s[2] != 0.0f ||
+      (float)c.n != (float)c.m)
+    return 4;
+  if (c.qfield && c.qalpha != 0.0) return (int64_t)c.nx * c.ny < 2000000 ? 4 : 5;
+  return 6;
 }
 // k = 2..4 time steps in one launch (src at t -> dst at t + k), and up to
 // fitted_steps.

@@ -804,11 +804,10 @@ static hipError_t launch_multi(const StepConfig &c, int k, const void *src, void
     case 4: return launch_multi_k<S, VAR, CHI, 4>(c, src, dst, stream);
   }
   // (fitted_steps)
-  if constexpr (sizeof(S) == 4 && (VAR & V_DEF) != 0 && (VAR & V_QA) == 0) {
-    switch (k) {
-      case 5: return launch_multi_k<S, VAR, CHI, 5>(c, src, dst, stream);
-      case 6: return launch_multi_k<S, VAR, CHI, 6>(c, src, dst, stream);
-    }
+  if constexpr (sizeof(S) == 4 && (VAR & V_DEF) != 0) {
+    if (k == 5) return launch_multi_k<S, VAR, CHI, 5>(c, src, dst, stream);
+    if constexpr ((VAR & V_QA) == 0)
+      if (k == 6) return launch_multi_k<S, VAR, CHI, 6>(c, src, dst, stream);
   }
   if constexpr (sizeof(S) == 8 && (VAR & V_DEF) != 0 && (VAR & V_QF) == 0) {
     if (k == 5) return launch_multi_k<S, VAR, CHI, 5>(c, src, dst, stream);

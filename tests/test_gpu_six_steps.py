@@ -68,6 +68,23 @@ def test_blocks(storage, block):
         check(a, r, n)
 
 
+def test_reference_states():
+    """A per-cell reference (six steps) and its running mean (five, from 2 million
+    cells on, and the updated field)."""
+    for alpha in (0.0, 1e-2):
+        a, r = pair(2000, 1001, "II", "max", None, 11)
+        g = np.random.default_rng(2)
+        f = [1.0 + 1e-3 * g.standard_normal((1001, 2000))] + [
+            0.05 + 1e-3 * g.standard_normal((1001, 2000)) for _ in range(2)]
+        for lat in (a, r):
+            lat.set_qref_field(*f)
+            lat.set_qref_average(alpha)
+        for n in (6, 5, 9, 1, 10):
+            check(a, r, n)
+        for x, y in zip(a.qref_field(), r.qref_field()):
+            assert np.array_equal(x, y)
+
+
 def test_checks_between_launches():
     """A detector that is due every 7 steps trips at the check that it had with
     four steps per launch."""
