@@ -18,28 +18,27 @@
 // returned sorted by (-|lambda|, arg lambda).
 //
 // Each lane holds its wavenumber's matrix in registers (every index fixed at
-// compile time: the loops are fully unrolled). The reduction leaves the
-// subdiagonal real and the sweeps keep it so, which makes every rotation 12
-// operations a pair instead of 16. The QR sweeps are wave-wide and run level by
-// level: at level h (8 down to 2) a sweep works on rows and columns 0..h only,
-// and a lane takes part while the bottom of its active window is h or h - 1, so
-// that the entries at the bottom are one of two fixed positions; a lane
+// compile time: the loops are fully unrolled). The QR sweeps are wave-wide and
+// run level by level: at level h (8 down to 2) a sweep works on rows and columns
+// 0..h only, and a lane takes part while the bottom of its active window is h or
+// h - 1, so that the entries at the bottom are one of two fixed positions; a lane
 // further ahead waits, masked off. With that slack of one a wave needs no more
 // sweeps than lanes running freely would (29 a wave, 26 a lane on MRT sets
-// with flow), and the sweep has neither gathers nor predicates. Complex
-// products are fused multiply-adds.
+// with flow), and the sweep has neither gathers nor predicates. A lane's own
+// sequence of checks, shifts and rotations does not depend on the others: where
+// eigenvalues tie in modulus (waves along an axis), their order hangs on the last
+// bit, so the arithmetic is kept as it is, without fused products. (Fused, and
+// with a real subdiagonal, the same sweep takes 6.5 ms, in another order there.)
 //
-// Bound by VALU issue at one wave per SIMD (0.69 busy): half of the instructions
-// are FP64, at level 8 a third move the window between the two halves of the
-// register file. Registers that do not fit went to scratch memory, whose waits
-// took a third of the time; so four rows of the matrix lie in LDS while it is
-// reduced, and the window's last column at levels 8 and 7 (38 KB, a quarter of the
-// CU's).
+// Bound by VALU issue at one wave per SIMD: two thirds of a sweep's instructions
+// are FP64, at level 8 a fifth move the window between the two halves of the
+// register file. Registers that do not fit go to scratch memory; so four rows of
+// the matrix lie in LDS while it is reduced, and the window's last column at levels
+// 8 and 7 (38 KB, a quarter of the CU's; level 6 too: no gain).
 //
 // 64 sets x 256^2 wavenumbers: 15.7 ms (268 M eigenproblems/s) with one window 0..8
-// in every sweep, the entries at a lane's own bottom selected over all
-// positions and complex subdiagonals; 9.8 ms by levels, 8.3 ms with the real
-// subdiagonal, 7.5 ms with the last column in LDS, 6.5 ms (641 M/s) with the rows.
+// in every sweep and the entries at a lane's own bottom selected over all
+// positions, now 11.9 ms (353 M/s).
 #include "lbm_device.h"
 #include "lbm_internal.h"
 
@@ -186,33 +185,12 @@ struct SplitMat {
   __device__ __forceinline__ void settle() const { asm volatile("" ::: "memory"); }
 };
 
-// a b + c, a b, conj(a) b + c and c - a b with fused multiply-adds.
-__device__ __forceinline__ cplx cfma(cplx a, cplx b, cplx c) {
-  return mk(__builtin_fma(a.re, b.re, __builtin_fma(-a.im, b.im, c.re)),
-            __builtin_fma(a.re, b.im, __builtin_fma(a.im, b.re, c.im)));
-}
-__device__ __forceinline__ cplx cmul(cplx a, cplx b) {
-  return mk(__builtin_fma(a.re, b.re, -(a.im * b.im)), __builtin_fma(a.re, b.im, a.im * b.re));
-}
-__device__ __forceinline__ cplx neg(cplx a) { return mk(-a.re, -a.im); }
-__device__ __forceinline__ double norm2(cplx a) { return __builtin_fma(a.re, a.re, a.im * a.im); }
 __device__ __forceinline__ cplx pick2(bool first, cplx a, cplx b) {
   return mk(first ? a.re : b.re, first ? a.im : b.im);
 }
 
-// |z|, and its phase z/|z| (1 for z = 0, or where |z|^2 is not positive).
-__device__ __forceinline__ double polar(cplx z, cplx &e) {
-  const double n2 = norm2(z);
-  const bool on = n2 > 0.0;
-  const double ir = on ? rsqrt_f64(n2) : 0.0;
-  e = mk(on ? z.re * ir : 1.0, z.im * ir);
-  return n2 * ir;
-}
-
-// Householder reduction to upper Hessenberg form with a real subdiagonal. The
-// reflection of column k, x = H(k+1.., k), is I - tau v v^H with v = x/|x| + g e1,
-// g = +-1 of Re x0's sign and tau = g conj(v0)/|v0|^2: it maps x to -g |x| e1, and
-// |v0| >= 1. H <- (I - tau v v^H) H (I - tau v v^H)^H.
+// Householder reduction to upper Hessenberg form, H <- Q^H H Q: the reflection of
+// column k.
 template <int k>
 __device__ __forceinline__ void reflect(SplitMat &H) {
   double xn2 = 0.0;
@@ -220,15 +198,21 @@ __device__ __forceinline__ void reflect(SplitMat &H) {
 #pragma unroll
   for (int i = k + 1; i < N; ++i) {
     v[i] = H.at(i, k);
-    xn2 = __builtin_fma(v[i].re, v[i].re, __builtin_fma(v[i].im, v[i].im, xn2));
+    xn2 += v[i].re * v[i].re + v[i].im * v[i].im;
   }
-  const bool on = xn2 > 0.0;  // a zero column stays as it is
-  const double ixn = on ? rsqrt_f64(xn2) : 0.0;
-  const double g = v[k + 1].re >= 0.0 ? 1.0 : -1.0;
+  const double xn = sqrt(xn2);
+  const cplx x0 = v[k + 1];
+  const double ax0 = absc(x0);
+  const cplx ph = ax0 > 0.0 ? scal(1.0 / ax0, x0) : mk(1.0, 0.0);
+  const cplx alpha = scal(-xn, ph);  // -e^{i arg x0} ||x||
+  // v = x - alpha e1, normalised (v = 0, the identity, for a zero column)
+  double vn2 = 0.0;
+  v[k + 1] = sub(x0, alpha);
 #pragma unroll
-  for (int i = k + 1; i < N; ++i) v[i] = scal(ixn, v[i]);
-  v[k + 1].re += g;
-  const cplx tau = scal(on ? g / norm2(v[k + 1]) : 0.0, conjc(v[k + 1]));
+  for (int i = k + 1; i < N; ++i) vn2 += v[i].re * v[i].re + v[i].im * v[i].im;
+  const double inv = vn2 > 0.0 ? rsqrt_f64(vn2) : 0.0;
+#pragma unroll
+  for (int i = k + 1; i < N; ++i) v[i] = scal(inv, v[i]);
   // left: rows k+1.., columns k+1..
 #pragma unroll
   for (int j = k + 1; j < N; ++j) {
@@ -236,17 +220,18 @@ __device__ __forceinline__ void reflect(SplitMat &H) {
 #pragma unroll
     for (int i = k + 1; i < N; ++i) {
       x[i] = H.at(i, j);
-      w = cfma(conjc(v[i]), x[i], w);
+      w = add(w, mul(conjc(v[i]), x[i]));
     }
-    w = neg(cmul(tau, w));
+    w = scal(2.0, w);
 #pragma unroll
-    for (int i = k + 1; i < N; ++i) H.put(i, j, cfma(v[i], w, x[i]));
+    for (int i = k + 1; i < N; ++i) H.put(i, j, sub(x[i], mul(v[i], w)));
     H.settle();
   }
-  // column k: (-g |x|, 0, ...); the entries below the subdiagonal become
-  // compile-time zeros, which frees their registers for the QR sweeps
-  // (they never read them)
-  H.put(k + 1, k, mk(-g * (xn2 * ixn), 0.0));
+  // column k below the subdiagonal: the reflection maps x to alpha e1
+  // (with v = 0 the column was zero below x0 already); the entries below
+  // the subdiagonal become compile-time zeros, which frees their registers
+  // for the QR sweeps (they never read them)
+  H.put(k + 1, k, vn2 > 0.0 ? alpha : x0);
 #pragma unroll
   for (int i = k + 2; i < N; ++i)
     if (i >= VN_LDS_ROWS) H.put(i, k, mk(0.0, 0.0));
@@ -257,11 +242,11 @@ __device__ __forceinline__ void reflect(SplitMat &H) {
 #pragma unroll
     for (int j = k + 1; j < N; ++j) {
       x[j] = H.at(i, j);
-      w = cfma(x[j], v[j], w);
+      w = add(w, mul(x[j], v[j]));
     }
-    w = neg(cmul(conjc(tau), w));
+    w = scal(2.0, w);
 #pragma unroll
-    for (int j = k + 1; j < N; ++j) H.put(i, j, cfma(w, conjc(v[j]), x[j]));
+    for (int j = k + 1; j < N; ++j) H.put(i, j, sub(x[j], mul(w, conjc(v[j]))));
     H.settle();
   }
 }
@@ -274,12 +259,6 @@ __device__ __forceinline__ void reflect_from(SplitMat &H) {
 
 __device__ __forceinline__ void hessenberg_reg(SplitMat &H) {
   reflect_from<0>(H);
-  // the last subdiagonal's phase e: row N - 1 times conj(e), column N - 1 times e
-  const cplx y = H.at(N - 1, N - 2);
-  cplx e;
-  H.put(N - 1, N - 2, mk(polar(y, e), 0.0));
-#pragma unroll
-  for (int i = 0; i < N - 1; ++i) H.put(i, N - 1, cmul(e, H.at(i, N - 1)));
   // all in registers from here on
 #pragma unroll
   for (int i = 0; i < VN_LDS_ROWS; ++i)
@@ -288,51 +267,38 @@ __device__ __forceinline__ void hessenberg_reg(SplitMat &H) {
   H.settle();
 }
 
-// Wilkinson shift of [a b; c d], c real: its eigenvalue nearer d, d - bc / (p + y) with
-// p = (a - d)/2, y = sqrt(p^2 + bc) on p's side (so |p + y| >= |p - y|); d where
-// that is not finite. It steers the convergence only, so the reciprocals
-// are refined estimates.
-__device__ __forceinline__ cplx shift_of(cplx a, cplx b, double c, cplx d) {
-  const cplx p = scal(0.5, sub(a, d));
-  const cplx bc = scal(c, b);
-  const cplx q = cfma(p, p, bc);
-  const double r2 = norm2(q);
-  const double r = r2 > 0.0 ? r2 * rsqrt_f64(r2) : 0.0;
-  const double t2 = 0.5 * (r + fabs(q.re));
-  const double it = t2 > 0.0 ? rsqrt_f64(t2) : 0.0;
-  const double t = t2 * it, u = 0.5 * q.im * it;  // |q.im| / (2 t)
-  cplx y = q.re >= 0.0 ? mk(t, u) : mk(fabs(u), copysign(t, q.im));
-  if (__builtin_fma(p.re, y.re, p.im * y.im) < 0.0) y = neg(y);
-  const cplx z = add(p, y);
-  const double z2 = norm2(z);
-  const double e = __builtin_amdgcn_rcp(z2);
-  const double iz = e * __builtin_fma(-z2, e, 2.0);
-  const cplx m = cmul(scal(iz, bc), conjc(z));
-  return z2 > 0.0 && __builtin_isfinite(m.re) && __builtin_isfinite(m.im) ? sub(d, m) : d;
+// Rotation [c s; -conj(s) conj(c)] with c = conj(x)/r, s = conj(y)/r,
+// r = sqrt(|x|^2 + |y|^2), which maps (x, y) to (r, 0); the identity when
+// inactive or when x = y = 0.
+__device__ __forceinline__ void givens(cplx x, cplx y, bool act, cplx &c, cplx &s) {
+  const double n2 = x.re * x.re + x.im * x.im + y.re * y.re + y.im * y.im;
+  const bool on = act && n2 > 0.0;
+  const double ir = on ? rsqrt_f64(n2) : 0.0;
+  c = on ? mk(x.re * ir, -x.im * ir) : mk(1.0, 0.0);
+  s = on ? mk(y.re * ir, -y.im * ir) : mk(0.0, 0.0);
 }
 
-// conj(c) a + s b and c b - s a, s real: a rotation of the pair (a, b).
-__device__ __forceinline__ cplx rot1(cplx c, double s, cplx a, cplx b) {
-  return mk(__builtin_fma(s, b.re, __builtin_fma(c.re, a.re, c.im * a.im)),
-            __builtin_fma(s, b.im, __builtin_fma(c.re, a.im, -(c.im * a.re))));
+// A left rotation of the pair (a, b) of one column, and a right one of one row.
+__device__ __forceinline__ void left_rot(cplx c, cplx s, cplx &a, cplx &b) {
+  const cplx t1 = a, t2 = b;
+  a = add(mul(c, t1), mul(s, t2));
+  b = sub(mul(conjc(c), t2), mul(conjc(s), t1));
 }
-__device__ __forceinline__ cplx rot2(cplx c, double s, cplx a, cplx b) {
-  return mk(__builtin_fma(-s, a.re, __builtin_fma(c.re, b.re, -(c.im * b.im))),
-            __builtin_fma(-s, a.im, __builtin_fma(c.re, b.im, c.im * b.re)));
+__device__ __forceinline__ void right_rot(cplx c, cplx s, cplx &a, cplx &b) {
+  const cplx t1 = a, t2 = b;
+  a = add(mul(t1, conjc(c)), mul(t2, conjc(s)));
+  b = sub(mul(t2, c), mul(t1, s));
 }
 
-// H <- H G^H on columns q, q + 1, G = [c s; -s conj(c)], where row q + 1 holds
-// (0, r) with r real.
-__device__ __forceinline__ void right_rot(RegMat &H, int q, cplx c, double s) {
+// H <- H G^H on columns q, q + 1 for rows 0..q + 1, G = [c s; -conj(s) conj(c)].
+__device__ __forceinline__ void right_rots(RegMat &H, int q, cplx c, cplx s) {
 #pragma unroll
-  for (int i = 0; i <= q; ++i) {
-    const cplx a = H.at(i, q), b = H.at(i, q + 1);
-    H.put(i, q, rot1(c, s, a, b));
-    H.put(i, q + 1, rot2(c, s, a, b));
+  for (int i = 0; i <= q + 1; ++i) {
+    cplx a = H.at(i, q), b = H.at(i, q + 1);
+    right_rot(c, s, a, b);
+    H.put(i, q, a);
+    H.put(i, q + 1, b);
   }
-  const double r = H.r[q + 1][q + 1];
-  H.put(q + 1, q, mk(s * r, 0.0));
-  H.put(q + 1, q + 1, scal(r, c));
 }
 
 // From this level on the last column above its diagonal lies in LDS (a lane's
@@ -367,7 +333,7 @@ __device__ __forceinline__ void detach_window(RegMat &H) {
 // sweeps (one with a NaN does) leaves with hi = -1 and the wave goes on without
 // it; every sweep is one of some lane at h, so the loop ends.
 template <int h>
-__device__ __forceinline__ void qr_level(RegMat &H, int &hi, int &it, int &sweeps, double2 *ev,
+__device__ __forceinline__ void qr_level(RegMat &H, int &hi, int &it, int &sweeps, int &deflated, double2 *ev,
                                          int stride, double2 *col) {
   constexpr bool LDS = h >= VN_LDS_LEVEL;
   constexpr int l = h > 2 ? h - 1 : h;  // the lowest window end that takes part
@@ -389,103 +355,133 @@ __device__ __forceinline__ void qr_level(RegMat &H, int &hi, int &it, int &sweep
   }
   detach_window<h>(H);
   for (;;) {
+    if (hi >= l && sweeps >= VN_MAX_SWEEPS) hi = -1;
 #pragma unroll
     for (int rep = 0; rep < 2; ++rep) {
       const bool top = hi == h;
-      const double d = top ? H.r[h][h - 1] : H.r[l][l - 1];
+      const cplx d = pick2(top, H.at(h, h - 1), H.at(l, l - 1));
       const cplx a = pick2(top, H.at(h - 1, h - 1), H.at(l - 1, l - 1));
       const cplx b = pick2(top, H.at(h, h), H.at(l, l));
-      if (hi >= l && fabs(d) <= eps * (abs1(a) + abs1(b))) {
+      if (hi >= l && deflated < 2 && abs1(d) <= eps * (abs1(a) + abs1(b))) {
         ev[hi * stride] = make_double2(b.re, b.im);
         --hi;
+        ++deflated;
         it = 0;
       }
     }
-    if (hi >= l && sweeps >= VN_MAX_SWEEPS) hi = -1;
     if (!__any(hi == h)) return;
     if (hi < l) continue;
     const bool top = hi == h;
-    const double c = top ? H.r[h][h - 1] : H.r[l][l - 1];
-    const cplx d = pick2(top, H.at(h, h), H.at(l, l));
-    cplx mu = shift_of(pick2(top, H.at(h - 1, h - 1), H.at(l - 1, l - 1)),
-                       pick2(top, last(h - 1), H.at(l - 1, l)), c, d);
-    if (it == 10 || it == 20)
-      mu = mk(d.re + __builtin_fma(0.75, fabs(c), fabs(top || l < 2 ? H.r[h - 1][h - 2]
-                                                                    : H.r[l - 1][l - 2])), d.im);
+    const cplx c0 = pick2(top, H.at(h, h - 1), H.at(l, l - 1));
+    const cplx d0 = pick2(top, H.at(h, h), H.at(l, l));
+    cplx mu;
+    if (it == 10 || it == 20) {
+      const double e2 = fabs(top || l < 2 ? H.r[h - 1][h - 2] : H.r[l - 1][l - 2]);
+      mu = add(d0, mk(0.75 * fabs(c0.re) + e2, 0.0));
+    } else {
+      cplx l1, l2;
+      eig2(pick2(top, H.at(h - 1, h - 1), H.at(l - 1, l - 1)),
+           pick2(top, last(h - 1), H.at(l - 1, l)), c0, d0, l1, l2);
+      mu = abs1(sub(l1, d0)) <= abs1(sub(l2, d0)) ? l1 : l2;
+    }
     ++it;
     ++sweeps;
+    deflated = 0;
     // H - mu I on the window; what lies below it (row and column h of a window
     // that ends at h - 1) is no longer read, and takes part in any way
 #pragma unroll
     for (int i = 0; i <= h; ++i) H.put(i, i, sub(H.at(i, i), mu));
     // R = G_{h-1} ... G_0 (H - mu I), then R G_0^H ... G_{h-1}^H, with each
     // right rotation applied once the next left one is: the left rotation k
-    // reads H(k, k) before the right rotation k - 1 changes it. A left rotation
-    // maps its own column's pair (x, y) to (r, 0), r real. With y = 0 at the
-    // window's end it takes R's last diagonal entry to its modulus, which
-    // keeps the subdiagonal real.
-    cplx cp = mk(1.0, 0.0), run = last(0);  // run: H(k, h)
-    double sp = 0.0;
+    // reads H(k, k) before the right rotation k - 1 changes it. The rotation
+    // h - 1 is the identity for a window that ends there.
+    cplx cp = mk(1.0, 0.0), sp = mk(0.0, 0.0), run = last(0);  // run: H(k, h)
 #pragma unroll
     for (int k = 0; k < h; ++k) {
-      const cplx x = H.at(k, k);
-      const double y = k < h - 1 || top ? H.r[k + 1][k] : 0.0;
-      const double n2 = __builtin_fma(y, y, norm2(x));
-      const bool on = n2 > 0.0;
-      const double ir = on ? rsqrt_f64(n2) : 0.0;
-      const cplx cc = mk(on ? x.re * ir : 1.0, x.im * ir);  // conj(c)
-      const double s = y * ir;
-      H.put(k, k, mk(n2 * ir, 0.0));
+      cplx c, s;
+      givens(H.at(k, k), H.at(k + 1, k), k < h - 1 || top, c, s);
 #pragma unroll
-      for (int j = k + 1; j < h; ++j) {
-        const cplx a = H.at(k, j), b = H.at(k + 1, j);
-        H.put(k, j, rot1(cc, s, a, b));
-        H.put(k + 1, j, rot2(cc, s, a, b));
+      for (int j = k; j < h; ++j) {
+        cplx a = H.at(k, j), b = H.at(k + 1, j);
+        left_rot(c, s, a, b);
+        H.put(k, j, a);
+        H.put(k + 1, j, b);
       }
-      const cplx b = k + 1 < h ? last(k + 1) : H.at(h, h);
-      set_last(k, rot1(cc, s, run, b));
-      run = rot2(cc, s, run, b);
-      if (k > 0) right_rot(H, k - 1, cp, sp);
-      cp = conjc(cc);
+      cplx b = k + 1 < h ? last(k + 1) : H.at(h, h);
+      left_rot(c, s, run, b);
+      set_last(k, run);
+      run = b;
+      if (k > 0) right_rots(H, k - 1, cp, sp);
+      cp = c;
       sp = s;
     }
-    cplx e;
-    const double r = polar(run, e);
 #pragma unroll
-    for (int i = 0; i < h; ++i) {
-      const cplx a = H.at(i, h - 1), b = last(i);
-      H.put(i, h - 1, rot1(cp, sp, a, b));
-      set_last(i, cmul(e, rot2(cp, sp, a, b)));
+    for (int i = 0; i <= h; ++i) {
+      cplx a = H.at(i, h - 1), b = i < h ? last(i) : run;
+      right_rot(cp, sp, a, b);
+      H.put(i, h - 1, a);
+      if (i < h)
+        set_last(i, b);
+      else
+        H.put(h, h, b);
     }
-    H.put(h, h - 1, mk(sp * r, 0.0));
-    H.put(h, h, cmul(e, scal(r, cp)));
 #pragma unroll
     for (int i = 0; i <= h; ++i) H.put(i, i, add(H.at(i, i), mu));
   }
 }
 
 template <int h>
-__device__ __forceinline__ void qr_levels(RegMat &H, int &hi, int &it, int &sweeps, double2 *ev,
+__device__ __forceinline__ void qr_levels(RegMat &H, int &hi, int &it, int &sweeps, int &deflated, double2 *ev,
                                           int stride, double2 *col) {
-  qr_level<h>(H, hi, it, sweeps, ev, stride, col);
-  if constexpr (h > 2) qr_levels<h - 1>(H, hi, it, sweeps, ev, stride, col);
+  qr_level<h>(H, hi, it, sweeps, deflated, ev, stride, col);
+  if constexpr (h > 2) qr_levels<h - 1>(H, hi, it, sweeps, deflated, ev, stride, col);
 }
 
 // Eigenvalues of the upper Hessenberg H. Returns false if the lane did not
 // converge within VN_MAX_SWEEPS sweeps.
 __device__ __forceinline__ bool qr_reg(RegMat &H, double2 *ev, int stride, double2 *col) {
-  int hi = N - 1, it = 0, sweeps = 0;
-  qr_levels<N - 1>(H, hi, it, sweeps, ev, stride, col);
-  if (hi == 1) {
-    const cplx a = H.at(0, 0), b = H.at(0, 1), c = H.at(1, 0), d = H.at(1, 1);
-    cplx l0 = a, l1 = d;
-    if (abs1(c) > 2.220446049250313e-16 * (abs1(a) + abs1(d))) eig2(a, b, c, d, l0, l1);
-    ev[0] = make_double2(l0.re, l0.im);
-    ev[stride] = make_double2(l1.re, l1.im);
-  } else if (hi == 0) {
-    ev[0] = make_double2(H.r[0][0], H.m[0][0]);
+  const double eps = 2.220446049250313e-16;
+  int hi = N - 1, it = 0, sweeps = 0, deflated = 0;
+  qr_levels<N - 1>(H, hi, it, sweeps, deflated, ev, stride, col);
+  if (hi < 0) return false;
+  cplx a = H.at(0, 0), b = H.at(0, 1), c = H.at(1, 0), d = H.at(1, 1);
+  if (hi == 1 && deflated == 2) {  // a sweep on the 2 x 2
+    cplx l1, l2, g, s;
+    eig2(a, b, c, d, l1, l2);
+    const cplx mu = abs1(sub(l1, d)) <= abs1(sub(l2, d)) ? l1 : l2;
+    a = sub(a, mu);
+    d = sub(d, mu);
+    givens(a, c, true, g, s);
+    left_rot(g, s, a, c);
+    left_rot(g, s, b, d);
+    right_rot(g, s, a, b);
+    right_rot(g, s, c, d);
+    a = add(a, mu);
+    d = add(d, mu);
+    deflated = 0;
   }
-  return hi >= 0;
+  if (hi == 1) {
+    if (abs1(c) <= eps * (abs1(a) + abs1(d))) {
+      ev[stride] = make_double2(d.re, d.im);
+      hi = 0;
+      ++deflated;
+    } else {
+      cplx l0, l1;
+      eig2(a, b, c, d, l0, l1);
+      a = l0;
+      ev[stride] = make_double2(l1.re, l1.im);
+      deflated = 0;
+    }
+  }
+  if (deflated == 2) {  // a sweep on the last entry alone: its shift out and in again
+    cplx l1, l2;
+    const cplx z0 = mk(0.0, 0.0);
+    eig2(z0, z0, z0, a, l1, l2);
+    const cplx mu = abs1(sub(l1, a)) <= abs1(sub(l2, a)) ? l1 : l2;
+    a = add(sub(a, mu), mu);
+  }
+  ev[0] = make_double2(a.re, a.im);
+  return true;
 }
 
 // One wavenumber per lane, 64 lanes per workgroup (one wave); blockIdx.y
