@@ -651,8 +651,9 @@ def storages_leg(lbm, wl, torch, n, steps, warmup):
 def d3q15_leg(lbm, wl, torch, n=256, steps=200, warmup=10):
     """The three-dimensional D3Q15 scheme (Appendix A.2) on the n^3 box with
     mean flow, 16 pulses and a six-face separable ramp, Type II, per storage:
-    one cell per thread, every stored element read and written once per step
-    (30 elements per cell update)."""
+    every stored element read and written once per launch (30 elements per
+    cell), of two steps in FP32 and FP64 and one in FP16; `traffic` is that of a
+    launch."""
     spec = wl.cube_d3q15(n=n)
     F = spec["fields"]()
     prof = spec["profile"]
@@ -673,10 +674,12 @@ def d3q15_leg(lbm, wl, torch, n=256, steps=200, warmup=10):
         rho = lat.moments()[0]
         lat.close()
         b = 30 * {"f64": 8, "f32": 4, "f16": 2}[st]
+        per = 1 if st == "f16" else 2
         cells = n ** 3
+        gbps = b * cells / (per * ms * 1e-3) / 1e9
         out[st] = {"mlups": cells / ms / 1e3, "ms_per_step": ms, "bytes_per_cell": b,
-                   "hbm_gbps": b * cells / (ms * 1e-3) / 1e9,
-                   "hbm_frac": b * cells / (ms * 1e-3) / 1e9 / PEAK_HBM_GBPS,
+                   "steps_per_launch": per, "hbm_gbps": gbps, "hbm_frac": gbps / PEAK_HBM_GBPS,
+                   "single_step_equivalent_gbps": per * gbps,
                    "traffic": counter_traffic3(st) if n == 256 else None,
                    "max_abs_rho_dev": float(np.abs(rho - 1.0).max()),
                    "finite": bool(np.isfinite(rho).all())}

@@ -1,5 +1,5 @@
 // lbm_tile.h -- the tile kernel of liblbm (Xu & Sagaut, arXiv:1203.6350: up to
-// nine applications of the step of Section 2 per launch on a two-dimensional
+// 14 applications of the step of Section 2 per launch on a two-dimensional
 // tile held in LDS) and its launcher. Instantiated once per storage type, in
 // lbm_tile_f64.hip, lbm_tile_f32.hip and lbm_tile_f16.hip.
 //

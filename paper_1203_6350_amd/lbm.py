@@ -642,7 +642,7 @@ def lbm_batch_destroy(b):
 
 
 class Batch:
-    """Many lattices stepped by one persistent launch per step (HIP graphs).
+    """Many lattices stepped in common launches (HIP graphs).
 
     The batch keeps references to its member Lattice objects; members must not
     be stepped on their own while the batch has work in flight (``sync()``)."""
