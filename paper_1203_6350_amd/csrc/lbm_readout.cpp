@@ -120,7 +120,9 @@ hipError_t read_out(ReadStage *stage, const ReadPart *parts, int nparts, hipStre
     total += parts[k].bytes;
     chunks += (parts[k].bytes + READ_CHUNK - 1) / READ_CHUNK;
   }
-  staged = staged && total >= READ_MIN;
+  // hipStreamPerThread is another stream in each thread: the copies of the others
+  // would not wait for what the caller's holds
+  staged = staged && total >= READ_MIN && stream != hipStreamPerThread;
   for (int k = 0; k < nparts && staged; ++k) staged = pageable(parts[k].dst, stream);
   Job j;
   staged = staged && hipGetDevice(&j.device) == hipSuccess && prepare(*stage);

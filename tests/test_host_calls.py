@@ -1,0 +1,80 @@
+"""The library's host side on a recording HIP runtime (hip_recorder.cpp): which
+kernels and copies its calls enqueue, on which threads, and what they do when
+memory runs out. No GPU takes part."""
+import json
+import os
+import shutil
+import subprocess
+import sys
+
+import pytest
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+
+PRELUDE = """
+import ctypes, json, re, sys
+sys.modules["torch"] = None  # its libraries would bind to the recorder too
+R = ctypes.CDLL(sys.argv[1], ctypes.RTLD_GLOBAL)
+R.recorder_take.restype = ctypes.c_size_t
+import numpy as np
+from paper_1203_6350_amd import lbm
+
+def take():
+    buf = ctypes.create_string_buffer(1 << 26)
+    R.recorder_take(buf, ctypes.c_size_t(len(buf)))
+    return [l.split() for l in buf.value.decode().splitlines()]
+
+def steps(log=None):
+    "The time steps of each launch, with the kernel: o(ne), s(trip) or t(ile)."
+    out = []
+    for l in take() if log is None else log:
+        m = re.search(r"step_multi_strip.*?Li\\d+ELi\\d+ELi(\\d)E", l[1])
+        if m:
+            out.append("s" + m.group(1))
+        elif "11tile_kernel" in l[1]:
+            out.append("t" + l[4])
+        elif re.search("lbm.{1,3}step_", l[1]):
+            out.append("o1")
+    return out
+
+def lattice(nx, ny, storage="f32", **kw):
+    lat = lbm.Lattice(nx, ny, storage=storage, **kw)
+    take()
+    return lat
+"""
+
+
+@pytest.fixture(scope="module")
+def recorder(tmp_path_factory):
+    out = str(tmp_path_factory.mktemp("recorder") / "recorder.so")
+    cxx = shutil.which("g++") or shutil.which("c++")
+    subprocess.check_call([cxx, "-std=c++17", "-O1", "-shared", "-fPIC", "-D__HIP_PLATFORM_AMD__",
+                           "-I/opt/rocm/include", os.path.join(ROOT, "tests", "hip_recorder.cpp"),
+                           "-o", out, "-lpthread"])
+
+    def run(body):
+        r = subprocess.run([sys.executable, "-c", PRELUDE + body, out], cwd=ROOT,
+                           capture_output=True, text=True, timeout=120)
+        assert r.returncode == 0, r.stderr[-2000:]
+        return json.loads(r.stdout.splitlines()[-1])
+    return run
+
+
+def test_copies_on_the_per_thread_stream_stay_on_its_thread(recorder):
+    """hipStreamPerThread names another stream in every thread, so a large
+    read-out of a handle on it must not copy from other threads."""
+    got = recorder("""
+out = {}
+for stream in (2, 0):  # hipStreamPerThread, the default stream
+    lat = lattice(2048, 2048, stream=stream)
+    lat3 = lbm.Lattice3(160, 160, 160, stream=stream)
+    take()
+    n = []
+    for call in (lat.moments, lat.populations, lat.save_state, lat3.moments, lat3.populations):
+        call()
+        n.append(sum(l[0] == "copy" and l[-1] == "other" for l in take()))
+    out[stream] = n
+print(json.dumps(out))
+""")
+    assert got["2"] == [0] * 5
+    assert any(got["0"])  # elsewhere several threads take part
