@@ -13,7 +13,7 @@
 #include <algorithm>
 #include <atomic>
 #include <cstring>
-#include <system_error>
+#include <exception>
 #include <thread>
 
 #include "lbm_device.h"
@@ -139,10 +139,10 @@ hipError_t read_out(ReadStage *stage, const ReadPart *parts, int nparts, hipStre
   std::thread workers[READ_THREADS];
   const int want = (int)std::min<size_t>(READ_THREADS, std::max(1u, std::thread::hardware_concurrency() / 2));
   int n = 1;
-  try {  // with fewer threads the others take more chunks
+  try {  // with fewer threads (none left, or no memory for one) the others take more chunks
     for (; n < want; ++n)
       workers[n] = std::thread([&j, slots, n] { share(j, slots + 2 * n * READ_CHUNK); });
-  } catch (const std::system_error &) {
+  } catch (const std::exception &) {
   }
   share(j, slots);
   for (int t = 1; t < READ_THREADS; ++t)

@@ -78,3 +78,19 @@ print(json.dumps(out))
 """)
     assert got["2"] == [0] * 5
     assert any(got["0"])  # elsewhere several threads take part
+
+
+def test_read_out_without_memory_for_threads(recorder):
+    """No memory for a thread's state (bad_alloc): the threads that there are
+    make all the copies, and nothing leaves through the C interface."""
+    got = recorder("""
+lat = lattice(2048, 2048)
+out = []
+for left in range(4):
+    R.recorder_news_left(left)
+    lat.moments()
+    R.recorder_news_left(-1)
+    out.append(sum(l[0] == "copy" for l in take()))
+print(json.dumps(out))
+""")
+    assert got == [48] * 4  # 96 MiB in chunks of 2
