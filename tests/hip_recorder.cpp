@@ -39,10 +39,13 @@ thread_local Config pushed;
 void line(const char *fmt, const char *what, unsigned a, unsigned b, int c, hipStream_t s) {
   char buf[1024];
   State &st = state();
+  const int left = news_left;
+  news_left = -1;  // the log's own memory does not count
   std::lock_guard<std::mutex> lock(st.m);
   std::snprintf(buf, sizeof(buf), fmt, what, a, b, c, (unsigned long long)(uintptr_t)s,
                 st.caller == std::this_thread::get_id() ? "caller" : "other");
   st.log += buf;
+  news_left = left;
 }
 
 }  // namespace
