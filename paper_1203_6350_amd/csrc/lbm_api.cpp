@@ -407,11 +407,6 @@ struct StepPlan {
   int region = 0, most = 1, per = 1;
   lbm::StepConfig cfg;
 };
-struct Launch {
-  int steps;
-  bool check;
-};
-
 // Time of a tile launch in us, as measured back to back on 256 compute units
 // (one entry per region size): first + step * s for s steps where the tiles
 // all run at once, and next + next_step * s for each further round of tiles.
@@ -500,38 +495,29 @@ StepPlan step_plan(const lbm_handle *h, int64_t n) {
   return p;
 }
 
-// The launches of n steps. False where they could not keep the parity (a
-// single step per launch then does).
-bool plan_launches(const lbm_handle *h, int64_t n, const StepPlan &p, std::vector<Launch> &out) {
-  const int64_t before = n / p.per + (n % p.per != 0);
-  const bool own = p.kind == StepPlan::STRIP && p.per == p.most;  // the handle's own strips
-  int64_t next = h->det_every ? h->det_next : 0;
-  for (int64_t k = 0; k < n;) {
-    int64_t seg = n - k;
-    if (h->det_every) {
-      const int64_t due = next - h->steps;  // in steps from the call's start
-      const int64_t at = (due + p.per - 1) / p.per * p.per;
-      if (at < n) seg = std::max<int64_t>(at - k, 1);
-    }
-    const int64_t count = (seg + p.most - 1) / p.most;
-    for (int64_t i = 0; i < count; ++i) {
-      // evenly, except for the handle's own strips: full launches and a rest
-      const int64_t m = own ? std::min<int64_t>(p.most, seg - i * p.most)
-                            : seg / count + (i < seg % count);
-      out.push_back(Launch{(int)m, i + 1 == count});
-    }
-    k += seg;
-    if (h->det_every) next = ((h->steps + k) / h->det_every + 1) * h->det_every;
-  }
-  if (((int64_t)out.size() ^ before) & 1) {
-    size_t i = out.size();
-    while (i > 0 && out[i - 1].steps < 2) --i;
-    if (i == 0) return false;
-    const Launch l = out[i - 1];
-    out[i - 1] = Launch{l.steps / 2, false};
-    out.insert(out.begin() + (ptrdiff_t)i, Launch{l.steps - l.steps / 2, l.check});
-  }
-  return true;
+// The number of launches of `seg` >= 1 steps, of the parity that the launches of
+// `per` steps would have: as few as `most` steps each allow, or one more.
+int64_t launch_count(int64_t seg, const StepPlan &p) {
+  const int64_t before = (seg - 1) / p.per + 1, count = (seg - 1) / p.most + 1;
+  return count + ((count ^ before) & 1);
+}
+
+// The steps of launch i of `count` that take `seg` steps: evenly, except for the
+// handle's own strips: full launches and a rest.
+int launch_steps(int64_t seg, int64_t count, int64_t i, const StepPlan &p) {
+  if (p.kind == StepPlan::STRIP && p.per == p.most)
+    return (int)std::min<int64_t>(p.most, seg - i * p.most);
+  return (int)(seg / count + (i < seg % count));
+}
+
+// The steps until the next moment at which a detector's check may be made, with
+// `k` of the call's `n` steps taken: the first multiple of `per` steps from the
+// call's start at which it is due, or the call's end.
+int64_t segment(const lbm_handle *h, int64_t k, int64_t n, const StepPlan &p) {
+  if (!h->det_every) return n - k;
+  const int64_t due = std::max<int64_t>(h->det_next - h->steps, 1);
+  const int64_t over = (k % p.per + due % p.per) % p.per, more = over ? p.per - over : 0;
+  return due < n - k - more ? due + more : n - k;
 }
 
 // Enqueue one launch of `steps` steps from lattice src into dst.
@@ -697,7 +683,7 @@ int lbm_step(lbm_handle *h, int64_t n) {
   // A channel, rows of 2^32 bytes or more, a running-mean reference state,
   // or a per-cell one with parameters other than the default form run in the
   // tile kernel or one step per launch only.
-  const StepPlan p = step_plan(h, n);
+  StepPlan p = step_plan(h, n);
   if (p.kind != StepPlan::ONE) {
     const bool qa = h->qf && h->qalpha != 0.0;
     bool in_place = false;  // the one-step kernel keeps the running mean where it is
@@ -713,21 +699,18 @@ int lbm_step(lbm_handle *h, int64_t n) {
         if (rc) return rc;
       }
     }
-    std::vector<Launch> todo;
-    if (!in_place && plan_launches(h, n, p, todo)) {
-      for (const Launch &l : todo) {
-        int rc = run_launch(h, p, l.steps);
-        if (rc) return rc;
-        if (l.check && (rc = detector_after_launch(h, h->stream, nullptr)) != LBM_OK) return rc;
-      }
-      return LBM_OK;
-    }
+    if (in_place) p = StepPlan{};
   }
-  const StepPlan one{};
-  for (int64_t k = 0; k < n; ++k) {
-    int rc = run_launch(h, one, 1);
-    if (!rc) rc = detector_after_launch(h, h->stream, nullptr);
+  // nothing is kept per launch: a call may be of any length
+  for (int64_t k = 0; k < n;) {
+    const int64_t seg = segment(h, k, n, p), count = launch_count(seg, p);
+    for (int64_t i = 0; i < count; ++i) {
+      int rc = run_launch(h, p, launch_steps(seg, count, i, p));
+      if (rc) return rc;
+    }
+    int rc = detector_after_launch(h, h->stream, nullptr);
     if (rc) return rc;
+    k += seg;
   }
   return LBM_OK;
 }

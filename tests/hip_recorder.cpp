@@ -27,7 +27,7 @@ State &state() {
   static State *s = new State;  // outlives the library's own static objects
   return *s;
 }
-std::atomic<int> capturing{0}, async_left{-1};
+std::atomic<int> capturing{0}, async_left{-1}, launches_left{-1}, error{hipSuccess};
 thread_local int news_left = -1;  // this thread's operator new: -1 never fails, else counts down
 struct Config {
   dim3 grid, block;
@@ -74,6 +74,7 @@ size_t recorder_take(char *out, size_t n) {  // the log so far, then empty
 }
 void recorder_capturing(int on) { capturing = on; }
 void recorder_async_left(int n) { async_left = n; }  // hipMallocAsync calls that succeed, -1: all
+void recorder_launches_left(int n) { launches_left = n; }  // kernel launches that succeed, -1: all
 void recorder_news_left(int n) { news_left = n; }    // this thread's allocations that succeed
 
 // ---- kernels
@@ -99,6 +100,11 @@ hipError_t __hipPopCallConfiguration(dim3 *g, dim3 *b, size_t *shmem, hipStream_
   return hipSuccess;
 }
 hipError_t hipLaunchKernel(const void *fn, dim3 g, dim3 b, void **args, size_t, hipStream_t s) {
+  if (launches_left >= 0 && launches_left-- == 0) {
+    launches_left = 0;
+    error = hipErrorLaunchFailure;
+    return hipErrorLaunchFailure;
+  }
   const std::string &name = state().kernels[fn];
   // the tile kernel's third argument is its number of steps
   const int steps = name.find("11tile_kernel") != std::string::npos ? *(int *)args[2] : 0;
@@ -144,7 +150,7 @@ hipError_t hipGetSymbolAddress(void **p, const void *) { return hipMalloc(p, 1 <
 // ---- device, streams, events, graphs
 hipError_t hipGetDevice(int *d) { return *d = 0, hipSuccess; }
 hipError_t hipSetDevice(int) { return hipSuccess; }
-hipError_t hipGetLastError() { return hipSuccess; }
+hipError_t hipGetLastError() { return (hipError_t)error.exchange(hipSuccess); }
 const char *hipGetErrorString(hipError_t) { return "recorded"; }
 hipError_t hipGetDevicePropertiesR0600(hipDeviceProp_tR0600 *p, int) {
   std::memset(p, 0, sizeof(*p));

@@ -20,7 +20,7 @@ import numpy as np
 from paper_1203_6350_amd import lbm
 
 def take():
-    buf = ctypes.create_string_buffer(1 << 26)
+    buf = ctypes.create_string_buffer(R.recorder_take(None, ctypes.c_size_t(0)) + 1)
     R.recorder_take(buf, ctypes.c_size_t(len(buf)))
     return [l.split() for l in buf.value.decode().splitlines()]
 
@@ -94,3 +94,79 @@ for left in range(4):
 print(json.dumps(out))
 """)
     assert got == [48] * 4  # 96 MiB in chunks of 2
+
+
+def test_a_call_of_any_length(recorder):
+    """lbm_step holds nothing that grows with the number of steps: 2^62 of them begin at once
+    (the sixth launch is made to fail, which ends the call)."""
+    got = recorder("""
+import resource
+resource.setrlimit(resource.RLIMIT_AS, (8 << 30, 8 << 30))
+out = []
+for lat in (lattice(2048, 2048), lattice(96, 80), lattice(96, 80, s=(0.3,) * 9)):
+    for every in (0, 7, 2 ** 63 - 1):
+        lat.set_detector(every)
+        take()
+        R.recorder_launches_left(5)
+        try:
+            lat.step(2 ** 62)
+        except lbm.LbmError as e:
+            out.append([e.code, len(take())])
+        R.recorder_launches_left(-1)
+print(json.dumps(out))
+""")
+    assert got == [[-3, 5]] * 9
+
+
+HANDLES = {
+    "strips": "lattice(1300, 1100)",
+    "strips f64": "lattice(1300, 1100, 'f64')",
+    "tiles": "lattice(96, 80)",
+    "tiles f64": "lattice(200, 170, 'f64')",
+    "four steps": "tuned(lattice(1300, 1100), 4, 0)",
+    "four steps f64": "tuned(lattice(1300, 1100, 'f64'), 4, 0)",
+    "three steps": "tuned(lattice(1300, 1100), 3, 8)",
+    "tiles for three": "tuned(lattice(96, 80), 3, 0)",
+}
+
+
+@pytest.mark.parametrize("name", list(HANDLES))
+def test_launches_of_a_call(recorder, name):
+    """The launches of a call take its steps, as many as the set shape's own
+    launches in parity, and a detector's checks fall on the first multiples of
+    the shape's steps, from the call's start, at or after each period."""
+    per = 4 if "four" in name else 3 if "three" in name else 1
+    got = recorder("""
+def tuned(lat, k, rows):
+    lat.set_tuning(kernel=k, block=128, rows=rows)
+    return lat
+out = []
+for every in (0, 7, 16):
+    lat = %s
+    lat.set_detector(every)
+    take()
+    for n in list(range(1, 42)) + [100, 101]:
+        lat.step(n)
+        log, at, k = take(), [], 0
+        for l in log:
+            s = steps([l])
+            k += int(s[0][1:]) if s else 0
+            if not s:
+                at.append(k)
+        out.append([every, n, steps(log), at])
+print(json.dumps(out))
+""" % HANDLES[name])
+    done = {}
+    for every, n, launches, checks in got:
+        assert sum(int(l[1:]) for l in launches) == n
+        assert (len(launches) - (-(-n // per))) % 2 == 0, (n, launches)
+        if every:
+            at, k = [], 0
+            t0, due = done.get(every, (0, every))
+            while k < n:  # the shape's own launches
+                k = min(k + per, n)
+                if t0 + k >= due:
+                    at.append(k)
+                    due = ((t0 + k) // every + 1) * every
+            done[every] = t0 + n, due
+            assert checks == at, (every, n, launches)
