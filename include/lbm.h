@@ -264,9 +264,10 @@ int lbm_get_info(lbm_handle *h, lbm_info *info);
  * one-cell-per-thread kernel otherwise (same results either way); the handle
  * cannot join a batch, and the field is not part of lbm_save_state (read it
  * with lbm_get_qref_field). A running mean in the several-step kernels keeps
- * a second field buffer (allocated at the first such step; a handle whose
- * shape is not set steps a captured stream with the one-cell kernel, in
- * place).
+ * a second field buffer (allocated at the first such step). On a captured
+ * stream the steps are those of the set shape's own launches (in place and one
+ * per launch, if none is set), and from then on every call leaves the mean in
+ * the buffer in which those would, so that replays may be mixed with calls.
  *
  * lbm_set_qref_average: after each step's collision the field follows the
  * cell's pre-collision conserved moments c = (rho, j) as an exponential

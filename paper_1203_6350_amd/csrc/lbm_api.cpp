@@ -91,6 +91,7 @@ struct lbm_handle {
   void *qf2 = nullptr;        // second buffer for the strip kernels' running mean
   int64_t qps = 0;
   double qalpha = 0.0;        // running-mean rate of the reference
+  bool mean_captured = false; // a captured call stepped a running mean: replays hold its buffers
   int channel = 0;            // line source at x = 0 (Sec. 4.2)
   int outflow = 0;            // zero-gradient outflow at x = nx - 1
   lbm_line_source src = {1.0, 0.0, 0.0, 0.0, 0.0, 0.0};
@@ -495,6 +496,28 @@ StepPlan step_plan(const lbm_handle *h, int64_t n) {
   return p;
 }
 
+// The set shape's own launches: its strips, or one step per launch.
+StepPlan own_plan(const lbm_handle *h) {
+  StepPlan p;
+  if (!h->shape_set || h->cfg.kernel < lbm::KERNEL_MULTI_MIN || !lbm::multi_step_supports(h->cfg))
+    return p;
+  p.kind = StepPlan::STRIP;
+  p.most = p.per = h->cfg.kernel;
+  p.cfg = h->cfg;
+  return p;
+}
+
+// Whether the stream is being captured. The default stream cannot be, and asking
+// about it while another stream is captured is an error; a stream that cannot
+// say is taken to be.
+bool is_capturing(hipStream_t stream) {
+  if (!stream) return false;
+  hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
+  if (hipStreamIsCapturing(stream, &cs) == hipSuccess) return cs != hipStreamCaptureStatusNone;
+  (void)hipGetLastError();
+  return true;
+}
+
 // The number of launches of `seg` >= 1 steps, of the parity that the launches of
 // `per` steps would have: as few as `most` steps each allow, or one more.
 int64_t launch_count(int64_t seg, const StepPlan &p) {
@@ -546,17 +569,20 @@ int enqueue_launch(lbm_handle *h, const StepPlan &p, int steps, const void *src,
   return e == hipSuccess ? LBM_OK : hip_fail(e, "step kernel");
 }
 
+// The second buffer of the running mean becomes the current one.
+void swap_mean(lbm_handle *h) {
+  std::swap(h->qf, h->qf2);
+  h->cfg.qfield = h->qf;
+  h->cfg.qfield_out = h->qf2;
+}
+
 int run_launch(lbm_handle *h, const StepPlan &p, int steps) {
   bool second = false;
   int rc = enqueue_launch(h, p, steps, h->lat[h->cur], h->lat[1 - h->cur], &second);
   if (rc) return rc;
   h->cur = 1 - h->cur;
   h->steps += steps;
-  if (second) {
-    std::swap(h->qf, h->qf2);
-    h->cfg.qfield = h->qf;
-    h->cfg.qfield_out = h->qf2;
-  }
+  if (second) swap_mean(h);
   return LBM_OK;
 }
 
@@ -684,22 +710,25 @@ int lbm_step(lbm_handle *h, int64_t n) {
   // or a per-cell one with parameters other than the default form run in the
   // tile kernel or one step per launch only.
   StepPlan p = step_plan(h, n);
-  if (p.kind != StepPlan::ONE) {
-    const bool qa = h->qf && h->qalpha != 0.0;
-    bool in_place = false;  // the one-step kernel keeps the running mean where it is
-    if (qa) {
-      // a captured sequence of the shape as created must leave the mean in the
-      // buffer that its replay starts from, and allocates nothing
-      hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
-      if (!h->shape_set)
-        HIP_TRY(hipStreamIsCapturing(h->stream, &cs), "hipStreamIsCapturing");
-      in_place = cs != hipStreamCaptureStatusNone;
-      if (!in_place) {
-        int rc = ensure_qf2(h);
-        if (rc) return rc;
-      }
+  // A running mean goes to the second buffer and back with each launch of several
+  // steps and stays in place in single steps. A replay starts from the buffer
+  // that its capture started from: captured calls take the shape's own
+  // launches, and once there was one every call leaves the mean in the
+  // buffer in which those would.
+  const bool qa = h->qf && h->qalpha != 0.0;
+  const void *const mean = h->qf;
+  int64_t own_swaps = 0;
+  if (qa) {
+    const StepPlan own = own_plan(h);
+    if (own.kind == StepPlan::STRIP) own_swaps = n / own.per + (n % own.per > 1);
+    if (is_capturing(h->stream)) {
+      h->mean_captured = true;
+      p = own;
     }
-    if (in_place) p = StepPlan{};
+    if (p.kind != StepPlan::ONE && n > 1) {
+      int rc = ensure_qf2(h);
+      if (rc) return rc;
+    }
   }
   // nothing is kept per launch: a call may be of any length
   for (int64_t k = 0; k < n;) {
@@ -711,6 +740,12 @@ int lbm_step(lbm_handle *h, int64_t n) {
     int rc = detector_after_launch(h, h->stream, nullptr);
     if (rc) return rc;
     k += seg;
+  }
+  if (h->mean_captured && qa && (mean != h->qf) != (own_swaps & 1)) {
+    const size_t eb = h->user.storage == LBM_STORAGE_F64 ? 8 : 4;
+    HIP_TRY(hipMemcpyAsync(h->qf2, h->qf, (size_t)(3 * h->qps) * eb, hipMemcpyDeviceToDevice, h->stream),
+            "hipMemcpy(reference)");
+    swap_mean(h);
   }
   return LBM_OK;
 }

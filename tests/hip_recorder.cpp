@@ -133,12 +133,14 @@ hipError_t hipFree(void *p) { return std::free(p), hipSuccess; }
 hipError_t hipFreeAsync(void *p, hipStream_t) { return std::free(p), hipSuccess; }
 hipError_t hipHostFree(void *p) { return std::free(p), hipSuccess; }
 hipError_t hipMemsetAsync(void *, int, size_t, hipStream_t) { return hipSuccess; }
-hipError_t hipMemcpy(void *, const void *, size_t, hipMemcpyKind) { return hipSuccess; }
 hipError_t hipMemcpyAsync(void *, const void *src, size_t, hipMemcpyKind kind, hipStream_t s) {
   char from[32];
   std::snprintf(from, sizeof(from), "%llx", (unsigned long long)(uintptr_t)src);
   line("copy %s %u %u %d %llx %s\n", from, 0, 0, (int)kind, s);
   return hipSuccess;
+}
+hipError_t hipMemcpy(void *d, const void *s, size_t n, hipMemcpyKind k) {
+  return hipMemcpyAsync(d, s, n, k, nullptr);
 }
 hipError_t hipPointerGetAttributes(hipPointerAttribute_t *a, const void *) {
   std::memset(a, 0, sizeof(*a));

@@ -170,3 +170,37 @@ print(json.dumps(out))
                     due = ((t0 + k) // every + 1) * every
             done[every] = t0 + n, due
             assert checks == at, (every, n, launches)
+
+
+@pytest.mark.parametrize("shape,n", [(None, (4, 3, 6)), ((4, 0), (9, 1, 8)), ((4, 0), (8, 5, 9)),
+                                     ((3, 0), (7, 3)), ((3, 8), (4, 4))])
+@pytest.mark.parametrize("size", [(96, 80), (2000, 1100)])
+def test_buffer_of_a_captured_running_mean(recorder, shape, n, size):
+    """Captured calls of a running mean, and the ones after them, leave it in the
+    buffer in which the set shape's own launches would: each launch of several
+    steps changes it, a single step and a shape that is not set do not."""
+    got = recorder("""
+shape, calls, size = %r, %r, %r
+def where(lat):  # the buffer that the field is read from
+    take()
+    lat.qref_field()
+    return [l[1] for l in take() if l[0] == "copy"][0]
+lat = lattice(*size, stream=64)
+one = np.ones(size[::-1])
+lat.set_qref_field(one, 0 * one, 0 * one)
+lat.set_qref_average(0.01)
+if shape:
+    lat.set_tuning(kernel=shape[0], block=128, rows=shape[1])
+    lat.step(shape[0])  # the second buffer is there before the capture
+out = []
+for capturing in (1, 0, 1):
+    R.recorder_capturing(capturing)
+    for k in calls:
+        a = where(lat)
+        lat.step(k)
+        out.append([k, a != where(lat)])
+print(json.dumps(out))
+""" % (shape, n, size))
+    per = shape[0] if shape else None
+    for k, changed in got:
+        assert changed == (per is not None and (k // per + (k % per > 1)) % 2 == 1), got
