@@ -727,7 +727,11 @@ int lbm_step(lbm_handle *h, int64_t n) {
     }
     if (p.kind != StepPlan::ONE && n > 1) {
       int rc = ensure_qf2(h);
-      if (rc) return rc;
+      // without room for it single steps still go, unless the set shape says otherwise
+      if (rc == LBM_ENOMEM && own.kind == StepPlan::ONE)
+        p = own;
+      else if (rc)
+        return rc;
     }
   }
   // nothing is kept per launch: a call may be of any length

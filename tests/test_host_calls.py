@@ -204,3 +204,34 @@ print(json.dumps(out))
     per = shape[0] if shape else None
     for k, changed in got:
         assert changed == (per is not None and (k // per + (k % per > 1)) % 2 == 1), got
+
+
+@pytest.mark.parametrize("size", [(96, 80), (1300, 1100)])
+def test_running_mean_without_room_for_a_second_buffer(recorder, size):
+    """Single steps need no second buffer: a handle as created takes them where
+    there is no memory for one; set strips report it."""
+    got = recorder("""
+size = %r
+out = []
+for shape in (None, 0, 4):
+    lat = lattice(*size, stream=64)
+    one = np.ones(size[::-1])
+    lat.set_qref_field(one, 0 * one, 0 * one)
+    lat.set_qref_average(0.01)
+    if shape is not None:
+        lat.set_tuning(kernel=shape, block=128, rows=8 if shape else 0)
+    take()
+    R.recorder_async_left(0)
+    try:
+        lat.step(9)
+        out.append(steps())
+    except lbm.LbmError as e:
+        out.append(e.code)
+    R.recorder_async_left(-1)
+    take()
+    lat.step(9)
+    out.append(len(steps()))
+print(json.dumps(out))
+""" % (size,))
+    assert got[0] == got[2] == ["o1"] * 9 and got[1] < 9 and got[3] == 9
+    assert got[4] == -2 and got[5] == 3
