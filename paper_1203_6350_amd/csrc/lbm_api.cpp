@@ -398,7 +398,7 @@ int create_common(const lbm_config *cfg, const double *rho, const double *ux,
 
 namespace {
 // How lbm_step advances a handle: tiles on regions of `region` cells a side
-// with up to `most` steps per launch, strips of `most` steps with the shape in
+// with up to `most` steps per launch, strips of up to `most` steps with the shape in
 // `cfg`, or one step per launch. `per` is the step count whose multiples (and
 // the call's end) are the moments at which a due detector check is made, and
 // whose number of launches gives the parity that the call leaves: the lattice
@@ -406,8 +406,34 @@ namespace {
 struct StepPlan {
   enum Kind { ONE, STRIP, TILE } kind = ONE;
   int region = 0, most = 1, per = 1;
+  bool halve = false;  // (STRIP) a launch more than the steps need comes of halving the last
   lbm::StepConfig cfg;
 };
+
+// The number of launches of `seg` >= 1 steps, of the parity that the launches of
+// `per` steps would have: as few as `most` steps each allow, or one more.
+int64_t launch_count(int64_t seg, const StepPlan &p) {
+  const int64_t before = (seg - 1) / p.per + 1, count = (seg - 1) / p.most + 1;
+  return count + ((count ^ before) & 1);
+}
+
+// The steps of launch i of `count` that take `seg` steps: evenly. With as many
+// launches as the set shape would make, they are its own: other step counts move
+// as much memory and cost more (FP32 4096^2, 9 steps as 4 + 4 + 1 787 us, as 3 + 3 + 3 or
+// 5 + 2 + 2 880 to 896).
+int launch_steps(int64_t seg, int64_t count, int64_t i, const StepPlan &p) {
+  if (p.kind == StepPlan::STRIP) {
+    if (count == (seg - 1) / p.per + 1 && (p.per == p.most || !p.halve))
+      return (int)std::min<int64_t>(p.per, seg - i * p.per);
+    const int64_t base = count - 1, last = base ? seg / base : 0;
+    if (p.halve && last >= 2 && base == (seg - 1) / p.most + 1)
+      return (int)(i == base       ? last - last / 2
+                   : i == base - 1 ? last / 2
+                                   : last + (i < seg % base));
+  }
+  return (int)(seg / count + (i < seg % count));
+}
+
 // Time of a tile launch in us, as measured back to back on 256 compute units
 // (one entry per region size): first + step * s for s steps where the tiles
 // all run at once, and next + next_step * s for each further round of tiles.
@@ -421,44 +447,67 @@ constexpr TileTime TILE_TIMES[3][4] = {
     {{24, 4.9, 0.39, 2.4, 0.40}, {32, 6.0, 0.44, 2.8, 0.72}, {40, 8.4, 0.74, 4.9, 0.68}, {48, 10.4, 1.10, 7.2, 0.97}},
     {{24, 5.0, 0.51, 3.0, 0.48}, {32, 5.5, 0.66, 3.2, 0.87}, {40, 6.9, 1.13, 5.0, 1.40}, {48, 8.9, 1.55, 6.0, 1.85}}};
 
-// The fastest tile launch for up to n steps: region, steps per launch and its
-// time per step (1e300 where there is none). Beyond two rounds of tiles the
-// strips are faster (three rounds, 1023 x 777 FP64: 10.4 against 8.9 us a step;
-// two, 700 x 500: 5.4 against 5.8, in FP32 3.4 against 4.7); where there are
-// none, the alternative is one step per launch and more rounds still pay.
-double best_tiles(const lbm::StepConfig &c, int64_t n, int cus, bool strips, int *region,
-                  int *steps) {
-  double best = 1e300;
-  const double most_rounds = strips ? 2.0 : 8.0;
-  const int ch = c.channel ? 1 : 0;
+// Time of a tile launch of m steps in us. Beyond two rounds of tiles the strips are
+// faster (three rounds, 1023 x 777 FP64: 10.4 against 8.9 us a step; two, 700 x
+// 500: 5.4 against 5.8, in FP32 3.4 against 4.7); where there are none, the
+// alternative is one step per launch and more rounds still pay. 1e300: too many.
+double tile_time(const lbm::StepConfig &c, const TileTime &t, int m, int cus, bool strips) {
+  const int T = t.region - 2 * (m - 1 + (c.channel ? 1 : 0));
+  if (T < 4) return 1e300;
+  const int64_t tiles = (int64_t)((c.nx + T - 1) / T) * ((c.ny + T - 1) / T);
+  const double rounds = (double)((tiles + cus - 1) / cus);
+  if (rounds > (strips ? 2.0 : 8.0)) return 1e300;
+  return t.first + t.step * m + (rounds - 1) * (t.next + t.next_step * m);
+}
+
+// Time per step in us of the strips, four steps per launch in their fitted shape:
+// from 300^2 to 1400^2 cells a fixed part (a strip's rows run in sequence) and a
+// rate (measured: 512^2 FP32 4.2 and tiles 2.0, 1023 x 777 6.3 and 7.9).
+double strip_time(const lbm::StepConfig &c) {
+  static const double fixed[3] = {3.0, 2.6, 2.9}, rate[3] = {7.3e-6, 4.3e-6, 5.5e-6};
+  return fixed[c.storage] + rate[c.storage] * ((double)c.nx * c.ny);
+}
+// Time of a single step in us, with a per-cell reference (FP16 1500^2 23 us, a
+// running mean 27) or without.
+double one_time(const lbm::StepConfig &c) {
+  static const double fixed[3] = {3.4, 3.0, 3.0}, rate[3] = {2.5e-5, 1.15e-5, 8e-6};
+  const double us = fixed[c.storage] + rate[c.storage] * ((double)c.nx * c.ny);
+  return !c.qfield ? us : c.qalpha != 0.0 ? 1.25 * us : 1.1 * us;
+}
+
+// The fastest tiles for n >= 2 steps, given p.per: false where they are not faster
+// than strips, or where there are none than single steps. The latter is close
+// for short calls, so it goes by the launches that would really be made, with
+// a margin for per-cell references (FP16 1500^2, 3 steps: tiles 74 us, 62 without).
+bool plan_tiles(const lbm::StepConfig &c, int64_t n, int cus, bool strips, StepPlan &p) {
+  const double one = one_time(c), slower = c.qfield ? 1.15 : 1.0;
+  double best = (double)n * (strips ? strip_time(c) : one);
+  StepPlan q = p;
+  bool found = false;
+  q.kind = StepPlan::TILE;
   for (const TileTime &t : TILE_TIMES[c.storage]) {
     for (int s = 2; t.region && s <= lbm::TILE_MAX_STEPS && s <= n; ++s) {
-      const int T = t.region - 2 * (s - 1 + ch);
-      if (T < 4) break;
-      const int64_t tiles = (int64_t)((c.nx + T - 1) / T) * ((c.ny + T - 1) / T);
-      const double rounds = (double)((tiles + cus - 1) / cus);
-      if (rounds > most_rounds) continue;
-      const double us = (t.first + t.step * s + (rounds - 1) * (t.next + t.next_step * s)) / s;
-      if (us < best) {
-        best = us;
-        *region = t.region;
-        *steps = s;
+      const double us = tile_time(c, t, s, cus, strips);
+      if (us > 1e299) break;  // more steps, smaller tiles, more rounds
+      double total = us / s * (double)n;
+      if (total >= best) continue;
+      q.most = s;
+      const int64_t count = launch_count(n, q), m = n / count, longer = n % count;
+      if (m + (longer > 0) < 2) continue;  // all of them single steps
+      if (!strips)
+        total = slower * (double)longer * tile_time(c, t, (int)m + 1, cus, strips) +
+                (double)(count - longer) *
+                    (m < 2 ? one : slower * tile_time(c, t, (int)m, cus, strips));
+      if (total < best) {
+        best = total;
+        found = true;
+        p.kind = StepPlan::TILE;
+        p.region = t.region;
+        p.most = s;
       }
     }
   }
-  return best;
-}
-
-// The time per step in us that the tiles have to beat: the K-step strips' in
-// their fitted shape, from 300^2 to 1400^2 cells a fixed part (a strip's rows run
-// in sequence) and a rate (measured: 512^2 FP32 4.2 and tiles 2.0, 1023 x 777
-// 6.3 and 7.9), or the one-step kernel's where there are no strips.
-double other_time(const lbm::StepConfig &c, bool strips) {
-  const double cells = (double)c.nx * c.ny;
-  static const double fixed[3] = {3.0, 2.6, 2.9}, rate[3] = {7.3e-6, 4.3e-6, 5.5e-6};
-  static const double one_fixed[3] = {3.4, 3.0, 3.0}, one_rate[3] = {2.5e-5, 1.15e-5, 8e-6};
-  return strips ? fixed[c.storage] + rate[c.storage] * cells
-                : one_fixed[c.storage] + one_rate[c.storage] * cells;
+  return found;
 }
 
 // The plan for a call of n steps.
@@ -468,32 +517,42 @@ StepPlan step_plan(const lbm_handle *h, int64_t n) {
   const bool strips = lbm::multi_step_supports(h->cfg);
   const bool chosen = h->shape_set && k >= lbm::KERNEL_MULTI_MIN;
   p.per = chosen && strips ? k : 1;
+  if (n < 2) return p;
+  StepPlan st = p;
+  if (strips && (chosen || !h->shape_set)) {
+    st.kind = StepPlan::STRIP;
+    st.cfg = h->cfg;
+    const int fitted = lbm::fitted_steps(h->cfg);
+    const double cells = (double)h->user.nx * (double)h->user.ny;
+    if (h->shape_set) {
+      st.most = k == 4 && h->cfg.rows == 0 ? fitted : k;
+    } else {
+      // as created: the shape that is fastest or within 5% of it from 300^2 to 3000
+      // x 2500 cells (wide workgroups pay once the chunks are tall)
+      st.most = fitted;
+      st.cfg.kernel = 4;
+      st.cfg.rows = 0;
+      st.cfg.block = h->user.storage == LBM_STORAGE_F16     ? 64
+                     : fitted == 6 || cells >= 3e6          ? 256
+                     : h->user.storage == LBM_STORAGE_F64 ? 128
+                                                            : 64;
+    }
+    // Halving the last launch is the better way to one more where launches of all
+    // step counts cost about the same (FP64, 5 steps: 3 + 1 + 1 550 us at 2048^2 with a
+    // per-cell reference, 2 + 2 + 1 less, but 20 steps 961 against 1396 evenly); for
+    // FP32's five and six steps evenly is (2048^2, 7 steps 3 to 7%). With a set shape it pays
+    // for five steps in FP64 until the chunks are tall: a launch of five takes
+    // as long as one of four (1024^2 46 and 45 us, 20 steps 223 against 250; 2048^2 177 and 140).
+    st.halve = h->shape_set ? st.most == 5 && h->user.storage == LBM_STORAGE_F64 && cells < 2e6
+                            : st.most == 4 || h->user.storage == LBM_STORAGE_F64;
+  }
   // a channel has no strip form: any shape means the tiles for it
-  if (n >= 2 && (h->channel || !h->shape_set || (chosen && h->cfg.rows == 0)) &&
-      best_tiles(h->cfg, n, h->cus, strips, &p.region, &p.most) <
-          other_time(h->cfg, strips)) {
-    p.kind = StepPlan::TILE;
-    return p;
+  if (h->channel || !h->shape_set || (chosen && h->cfg.rows == 0)) {
+    // (a detector cuts the call at its checks)
+    const int64_t m = h->det_every ? std::max<int64_t>(2, std::min(n, h->det_every)) : n;
+    if (plan_tiles(h->cfg, m, h->cus, strips, p)) return p;
   }
-  p.most = 1;
-  if (n < 2 || !strips || (h->shape_set && !chosen)) return p;
-  p.kind = StepPlan::STRIP;
-  p.cfg = h->cfg;
-  const int fitted = lbm::fitted_steps(h->cfg);
-  if (h->shape_set) {
-    p.most = k == 4 && h->cfg.rows == 0 ? fitted : k;
-    return p;
-  }
-  // as created: the shape that is fastest or within 5% of it from 300^2 to 3000
-  // x 2500 cells (wide workgroups pay once the chunks are tall)
-  p.most = fitted;
-  p.cfg.kernel = 4;
-  p.cfg.rows = 0;
-  p.cfg.block = h->user.storage == LBM_STORAGE_F16                      ? 64
-                : fitted == 6 || (int64_t)h->user.nx * h->user.ny >= 3000000 ? 256
-                : h->user.storage == LBM_STORAGE_F64                  ? 128
-                                                                        : 64;
-  return p;
+  return st;
 }
 
 // The set shape's own launches: its strips, or one step per launch.
@@ -518,21 +577,6 @@ bool is_capturing(hipStream_t stream) {
   return true;
 }
 
-// The number of launches of `seg` >= 1 steps, of the parity that the launches of
-// `per` steps would have: as few as `most` steps each allow, or one more.
-int64_t launch_count(int64_t seg, const StepPlan &p) {
-  const int64_t before = (seg - 1) / p.per + 1, count = (seg - 1) / p.most + 1;
-  return count + ((count ^ before) & 1);
-}
-
-// The steps of launch i of `count` that take `seg` steps: evenly, except for the
-// handle's own strips: full launches and a rest.
-int launch_steps(int64_t seg, int64_t count, int64_t i, const StepPlan &p) {
-  if (p.kind == StepPlan::STRIP && p.per == p.most)
-    return (int)std::min<int64_t>(p.most, seg - i * p.most);
-  return (int)(seg / count + (i < seg % count));
-}
-
 // The steps until the next moment at which a detector's check may be made, with
 // `k` of the call's `n` steps taken: the first multiple of `per` steps from the
 // call's start at which it is due, or the call's end.
@@ -553,7 +597,7 @@ int enqueue_launch(lbm_handle *h, const StepPlan &p, int steps, const void *src,
   c.qfield = h->qf;
   c.qfield_out = h->qf2;
   *second = false;
-  if (p.kind == StepPlan::TILE) {
+  if (p.kind == StepPlan::TILE && steps > 1) {
     double source[9 * lbm::TILE_MAX_STEPS];
     if (h->channel)
       for (int j = 0; j < steps; ++j) source_dev(h, h->steps + 1 + j, source + 9 * j);
@@ -957,10 +1001,10 @@ int lbm_autotune(lbm_handle *h, int32_t reps, lbm_tuning *best, double *best_ms)
   if (reps < 1) return fail(LBM_EINVAL, "reps must be >= 1");
   std::vector<lbm_tuning> cands;
   const int blocks[4] = {64, 128, 256, 512};
-  int tile_region, tile_steps;
   const bool strips = lbm::multi_step_supports(h->cfg);
-  const bool tiles = best_tiles(h->cfg, 1 << 20, h->cus, strips, &tile_region, &tile_steps) <
-                     other_time(h->cfg, strips);
+  const int64_t many = 1 << 20;
+  StepPlan tile_plan;
+  const bool tiles = plan_tiles(h->cfg, many, h->cus, strips, tile_plan);
   if (h->channel && tiles) {
     cands.push_back(lbm_tuning{0, 256, 0, 0});  // the tiles, whatever the shape
   } else {
@@ -1043,7 +1087,7 @@ int lbm_autotune(lbm_handle *h, int32_t reps, lbm_tuning *best, double *best_ms)
     h->cfg.block = c.block;
     h->cfg.nontemporal = c.nontemporal;
     h->cfg.rows = c.kernel >= 2 ? c.rows : saved.rows;
-    const StepPlan p = step_plan(h, 1 << 20);
+    const StepPlan p = step_plan(h, many);
     for (int k = 0; k < 2 + reps && e == hipSuccess && !rc_launch; ++k) {
       bool second;
       if (k == 2) e = hipEventRecord(e0, h->stream);

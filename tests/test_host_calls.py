@@ -235,3 +235,42 @@ print(json.dumps(out))
 """ % (size,))
     assert got[0] == got[2] == ["o1"] * 9 and got[1] < 9 and got[3] == 9
     assert got[4] == -2 and got[5] == 3
+
+
+def test_mixes_of_launches(recorder):
+    """A set shape's longer launches are taken where there are at least two fewer of
+    them, else its own; a single step always takes the one-step kernel; and two steps,
+    which the parity makes two launches, are two of those."""
+    got = recorder("""
+out = {"own": [], "fewer": [], "single": [], "two": []}
+for storage in ("f32", "f64"):
+    lat = lattice(2048, 1300, storage)
+    lat.set_tuning(kernel=4, block=128, rows=0)
+    for n in (5, 6, 7, 9, 10, 12, 13, 14, 16, 20):
+        lat.step(n)
+        rest = {0: [], 1: ["o1"]}.get(n % 4, ["s%d" % (n % 4)])
+        out["own"].append(steps() == ["s4"] * (n // 4) + rest)
+    for n in (50, 100):
+        lat.step(n)
+        out["fewer"].append(-(-n // 4) - len(steps()))
+for storage in ("f64", "f32", "f16"):
+    for nx, ny in ((16, 16), (64, 70), (128, 128), (256, 200), (500, 500), (1000, 900)):
+        for kw in ({}, dict(s=(1.7,) * 9)):
+            for field in (0, 1, 2):
+                lat = lattice(nx, ny, storage, **kw)
+                one = np.ones((ny, nx))
+                if field == 1:
+                    lat.set_qref_field(one, 0 * one, 0 * one)
+                if field == 2:
+                    lat.set_line_source((1.0, 1e-3, 0.01, 0.0, 0.0, 0.0), True)
+                take()
+                for n in range(2, 18):
+                    lat.step(n)
+                    s = steps()
+                    out["single"].append("t1" in s)
+                    if n == 2:
+                        out["two"].append(s == ["o1"] * 2)
+print(json.dumps(out))
+""")
+    assert all(got["own"]) and all(k >= 2 for k in got["fewer"]), got
+    assert not any(got["single"]) and all(got["two"])
