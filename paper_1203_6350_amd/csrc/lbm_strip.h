@@ -540,17 +540,37 @@ __device__ __forceinline__ void strip_run(const StripCtx<S, VAR, CHI, K> &c, int
 #undef LBM_STRIP_ITER
 }
 
-// One strip, in the form that its part of the layer needs. In FP16 storage and in
-// FP32 beyond four steps, which are bound by VALU issue, a strip clear of the layer
-// (0.90 of the waves of 4096^2 with a 64-cell layer) runs the collision without the
-// damping's products with 0, same values: 4096^2 Type II FP16 210 -> 229 GLUPS
-// (three steps, block 64, rows 32), FP32 with six steps 257 -> 265. Four steps in
-// FP32 move memory at 4.7 TB/s whether they collide or not (265 us a launch without
-// the collision, 285 with it) and gained 2%; in FP64 the second loop's registers
-// took 9% from batches: these keep the one loop. The choice is made once per
-// strip, so each row loop stays one block; the waves of a workgroup may differ,
-// both loops pass one barrier per row.
-template <typename S, int VAR, int CHI, int K>
+// Whether strips clear of the layer run a second loop, the collision without the
+// damping's products with 0 (FREE; default parameters only, which halves the
+// instances; the undamped scheme is its own free form). It pays in FP16 storage and
+// in FP32 beyond four steps, which are bound by VALU issue (FP16 4096^2 Type II, four
+// steps, rows 32: 0.95 of the time; FP32 with six steps 257 -> 265 GLUPS), with 0.90 of
+// the waves of 4096^2 clear of a 64-cell layer. Four steps in FP32 move memory at
+// 4.7 TB/s whether they collide or not (265 us a launch without the collision,
+// 285 with it) and gained 2%; in FP64 the second loop's registers took 9% from
+// batches. In FP16 too it stays out where its registers cost a wave per SIMD or
+// more than it saves, against the one loop: single lattices with two steps (1024^2
+// 1.12 of the time), with three in Type III (1.04) or with a running mean (4096^2 1.05), with
+// four and a fixed per-cell reference in Types I and II (2048^2 and 4096^2 1.06 to 1.10,
+// 1024^2 0.95) or a running one in Type III (1.10); batches with two steps (1.10 to 1.23)
+// unless their sponges are mixed (0.91) or, being separable maxima, beside per-cell
+// references (0.90), and with three steps and mixed sponges (256 of 256^2 1.16, 64 of
+// 512^2 with fields 1.33). Without any sponge it is the only loop.
+template <typename S, int VAR, int CHI, int K, bool BATCH>
+constexpr bool strip_has_free() {
+  constexpr bool III = (VAR & V_MASK) == V_III, QF = (VAR & V_QF) != 0, QA = (VAR & V_QA) != 0;
+  if ((VAR & V_MASK) == V_NONE || (VAR & V_DEF) == 0 || CHI == CHI_FIELD) return false;
+  if (sizeof(S) == 4) return K > 4;
+  if (sizeof(S) != 2) return false;
+  if (CHI == CHI_ZERO || (BATCH && K == 4)) return true;
+  if (BATCH) return K == 3 ? CHI != CHI_RUNTIME || QF : (CHI == CHI_RUNTIME) != QF;
+  return K == 4 ? !QF || QA != III : K == 3 && !QA && (QF || !III);
+}
+
+// One strip, in the form that its part of the layer needs (strip_has_free). The
+// choice is made once per strip, so each row loop stays one block; the waves of a
+// workgroup may differ, both loops pass one barrier per row.
+template <typename S, int VAR, int CHI, int K, bool BATCH = false>
 __device__ __forceinline__ void strip_do(const S *src, S *dst, int nx, int ny, int64_t pitch,
                                          int64_t ps, int strip, bool idle, int Y0, int R, int nw,
                                          const typename Store<S>::C *chi_field,
@@ -566,10 +586,7 @@ __device__ __forceinline__ void strip_do(const S *src, S *dst, int nx, int ny, i
   StripCtx<S, VAR, CHI, K> c;
   strip_setup(c, src, dst, nx, ny, pitch, ps, strip, idle, Y0, nw, chi_field, chix, chiy,
               chi_mode, scale, inv_scale, p, qf, qps, qf_out, alpha);
-  // (default parameters only, which halves the instances; the undamped scheme
-  // is its own free form)
-  constexpr bool LAYER = (sizeof(S) == 2 || (sizeof(S) == 4 && K > 4)) && (VAR & V_MASK) != V_NONE && (VAR & V_DEF) != 0 &&
-                         CHI != CHI_FIELD;
+  constexpr bool LAYER = strip_has_free<S, VAR, CHI, K, BATCH>();
   if constexpr (LAYER) {
     if (CHI == CHI_ZERO || strip_is_free(c, R)) {
       // a fixed per-cell reference is not read where chi is 0
@@ -697,7 +714,7 @@ void batch_multi_strip(const BatchDomain *__restrict__ doms, const int4 *__restr
     set_relax_coeffs(p);
 #define LBM_BATCH_RUN(VAR, QFP)                                                              \
   {                                                                                          \
-    strip_do<S, (VAR) | (DEF ? V_DEF : 0), MAXF ? CHI_SEP_MAX : CHI_RUNTIME, K>(             \
+    strip_do<S, (VAR) | (DEF ? V_DEF : 0), MAXF ? CHI_SEP_MAX : CHI_RUNTIME, K, true>(       \
         (const S *)d.lat[par], (S *)d.lat[par ^ 1], d.nx, d.ny, d.pitch, d.ps, strip, idle,  \
         it.z, it.w, nw, (const C *)d.chi_field, (const C *)d.chi_x, (const C *)d.chi_y,      \
         d.chi_mode, scale, inv_scale, p, QFP, d.qps);                                        \
