@@ -539,7 +539,7 @@ static Two3Shape two3_shape(const Step3Config &c) {
 }
 
 int two3_depth(const Step3Config &c, double *use) {
-  if (use) *use = 0.0;
+  *use = 0.0;
   if (c.storage == 2) return 0;  // FP16 is bound by VALU issue at one step already
   const int64_t eb = c.storage == 0 ? 8 : 4;
   // a slice is addressed through one buffer range
@@ -552,7 +552,8 @@ int two3_depth(const Step3Config &c, double *use) {
   const int64_t slots = (int64_t)w.per_cu * c.cus;
   double best = 0.0;
   int depth = 0;
-  for (int64_t chunks = 1; chunks <= c.nz; ++chunks) {
+  // (each height once: some 2 sqrt(nz) of them)
+  for (int64_t chunks = 1; chunks <= c.nz;) {
     const int64_t d = (c.nz + chunks - 1) / chunks;
     const int64_t wgs = tiles * ((c.nz + d - 1) / d), rounds = (wgs + slots - 1) / slots;
     const double u = (double)c.nx * c.ny * c.nz / ((double)rounds * slots * TX * TY * (d + 2));
@@ -561,8 +562,9 @@ int two3_depth(const Step3Config &c, double *use) {
       depth = (int)d;
     }
     if (d <= 4) break;
+    chunks = (c.nz + d - 2) / (d - 1);
   }
-  if (use) *use = best;
+  *use = best;
   return depth;
 }
 
@@ -572,7 +574,7 @@ static hipError_t launch_two_v(const Step3Config &c, const void *src, void *dst,
   typedef typename Store<S>::C C;
   typedef Two3<S, RX, TWO3_RY> G;
   const int ntx = (c.nx + G::TX - 1) / G::TX, nty = (c.ny + G::TY - 1) / G::TY;
-  const int depth = two3_depth(c, nullptr);
+  const int depth = c.two_depth;
   const int64_t nwg = (int64_t)ntx * nty * ((c.nz + depth - 1) / depth), per = (nwg + 7) / 8;
   if (8 * per > 0x7fffffff) return hipErrorInvalidValue;
   const Chi3<C> X = {(const C *)c.chi_field, (const C *)c.chi_x, (const C *)c.chi_y,
@@ -596,7 +598,7 @@ static hipError_t launch_two_s(const Step3Config &c, const void *src, void *dst,
 }
 
 hipError_t launch_two3(const Step3Config &c, const void *src, void *dst, hipStream_t stream) {
-  if (two3_depth(c, nullptr) < 1) return hipErrorInvalidValue;
+  if (c.two_depth < 1) return hipErrorInvalidValue;
   switch (c.storage) {
     case 0: return launch_two_s<double, TWO3_NARROW>(c, src, dst, stream);
     case 1:

@@ -2195,8 +2195,7 @@ int check_chi3(const double *chi, size_t n, int variant) {
 // computing cells on (measured, against one step: 0.59 +20% at 96^3 FP32, 0.41
 // -8% at 64^3 FP64, 0.21 -1% at 64^3 FP32).
 bool two_steps_pay(const lbm3_handle *h) {
-  double use = 0.0;
-  return !h->shape_set && lbm::two3_depth(h->cfg, &use) > 0 && use > 0.5;
+  return !h->shape_set && h->cfg.two_depth > 0 && h->cfg.two_use > 0.5;
 }
 
 // FP64 device copy of a host array of n doubles (NULL stays NULL).
@@ -2238,6 +2237,7 @@ int lbm3_create(const lbm3_config *cfg, const double *rho, const double *ux, con
   if (hipDeviceGetAttribute(&h->cfg.cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess)
     h->cfg.cus = 256;
   fill_cfg3(h);
+  h->cfg.two_depth = lbm::two3_depth(h->cfg, &h->cfg.two_use);
   for (int k = 0; k < 2; ++k) {
     hipError_t e = hipMalloc(&h->lat[k], h->lat_bytes);
     if (e == hipSuccess) e = hipMemsetAsync(h->lat[k], 0, h->lat_bytes, h->stream);

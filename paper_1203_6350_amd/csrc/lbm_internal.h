@@ -271,11 +271,13 @@ struct Step3Config {
   int kernel;            // 0: one cell per thread; 1: two cells of a row per thread (nx even)
   int block;             // threads per workgroup, 64..512, a multiple of 64
   int cus;               // compute units of the device
+  int two_depth;         // two3_depth of the sizes, storage and device, and its use
+  double two_use;
 };
 hipError_t launch_step3(const Step3Config &c, const void *src, void *dst, hipStream_t stream);
 // Two steps in one launch (FP32 and FP64). two3_depth: planes per workgroup, or
-// 0 where the kernel does not take the lattice; *use (may be NULL): the share
-// of the launch's capacity that computes cells.
+// 0 where the kernel does not take the lattice; *use: the share of the launch's
+// capacity that computes cells.
 int two3_depth(const Step3Config &c, double *use);
 hipError_t launch_two3(const Step3Config &c, const void *src, void *dst, hipStream_t stream);
 hipError_t launch_init3(const Step3Config &c, const double *rho, const double *ux,

@@ -274,3 +274,44 @@ print(json.dumps(out))
 """)
     assert all(got["own"]) and all(k >= 2 for k in got["fewer"]), got
     assert not any(got["single"]) and all(got["two"])
+
+
+def test_planes_of_the_two_step_kernel(recorder):
+    """D3Q15's chunk height is the best of all, is found once, and a lattice of many
+    planes pays nothing for it on each call."""
+    got = recorder("""
+import time
+out = []
+for storage in ("f32", "f64"):
+    for shape in ((128, 104, 64), (129, 105, 66), (1, 500, 2000), (256, 256, 256), (64, 260, 4001), (320, 130, 999)):
+        lat = lbm.Lattice3(*shape, storage=storage)
+        take()
+        lat.step(8)
+        out.append([storage, shape, [int(l[2]) for l in take() if "step3_two" in l[1]]])
+def idle(*shape):
+    lat = lbm.Lattice3(*shape, storage="f32")
+    best = 1.0
+    for _ in range(50):
+        t = time.perf_counter()
+        for _ in range(10):
+            lat.step(0)
+        best = min(best, time.perf_counter() - t)
+    return best
+out.append([idle(8, 8, 8), idle(4, 4, 400000)])
+print(json.dumps(out))
+""")
+    small, flat = got.pop()
+    assert flat < 4 * small  # 400000 planes had cost 400 us a call
+    for storage, (nx, ny, nz), grids in got:
+        wide = storage == "f32" and 120 * nx * ny * nz > 256 << 20
+        tx, ty, slots = (64 if wide else 32), 13, 256 * (1 if wide or storage == "f64" else 2)
+        tiles, best = -(-nx // tx) * -(-ny // ty), (0, 0)
+        for chunks in range(1, nz + 1):
+            d = -(-nz // chunks)
+            wgs = tiles * -(-nz // d)
+            use = nx * ny * nz / (-(-wgs // slots) * slots * tx * ty * (d + 2))
+            if use > best[0]:
+                best = (use, wgs)
+            if d <= 4:
+                break
+        assert grids == ([8 * -(-best[1] // 8)] * 4 if best[0] > 0.5 else []), (storage, nx, ny, nz)
