@@ -11,6 +11,7 @@
 #include <cstdio>
 #include <cstdlib>
 #include <algorithm>
+#include <array>
 #include <atomic>
 #include <cstring>
 #include <initializer_list>
@@ -1268,6 +1269,10 @@ const char *lbm_last_error(void) { return g_err.c_str(); }
 
 }  // extern "C"
 
+// Tick lengths told apart in the choice of square tiles; longer ones count as this
+// (two launches of the most steps).
+constexpr int BT_TICKS = 2 * lbm::TILE_MAX_STEPS;
+
 struct lbm_batch {
   std::vector<lbm_handle *> members;
   int storage = 1;
@@ -1296,10 +1301,22 @@ struct lbm_batch {
   size_t item_cap = 0;
   int multi_form = 0;  // BATCH_DEF / BATCH_QF of the member list when the items were made
   // several steps per launch on square tiles (batches of few or small members):
-  // the table for ticks of min(tick, TILE_MAX_STEPS) = bt_for steps (0: none made)
-  int4 *d_btiles = nullptr;
-  size_t bt_cap = 0;
-  int bt_for = 0, bt_region = 0, bt_most = 0, nbt = 0;
+  // the choice for each tick length, and the table of each (region, most steps) that was
+  // ever chosen, both for the current members; the tables keep their memory
+  struct TileChoice {
+    bool made = false;
+    int region = 0, most = 0;  // region 0: no tiles
+    double gain = 0.0;         // us a tick
+  };
+  struct TileTable {
+    int4 *dev = nullptr;  // [0].x: the number of tiles, then the tiles
+    size_t cap = 0;
+    int n = 0;            // 0: not cut for these members
+  };
+  TileChoice bt_choice[BT_TICKS + 1];
+  std::map<std::pair<int, int>, TileTable> bt_tables;
+  double bt_owed = 0.0;  // what the tables that are not cut would have gained so far
+  std::vector<std::array<int64_t, 3>> sizes;  // the members' distinct (nx, ny) and how many
   // instability detector: per-member trip slots (one copy at lbm_batch_sync)
   // and the descriptors of one tick's checks, staged like the members'
   unsigned long long *d_trip = nullptr;            // [dom_cap]
@@ -1401,11 +1418,11 @@ void free_graphs(lbm_batch *b) {
 // tile launches (k = 0 .. nsingle-1; with K-step launches these take the
 // members' remainders).
 // With region > 0 instead `nmulti` tile launches of at most K steps on regions of
-// that size, one workgroup per tile.
+// that size, one workgroup per tile of the table.
 int batch_graph(lbm_batch *b, int K, int nmulti, int nsingle, int form, int region,
-                hipGraphExec_t *out) {
+                const lbm_batch::TileTable *table, hipGraphExec_t *out) {
   // (rounded up, so that most changes of the member list keep the graph)
-  const int grid = region ? (b->nbt + 255) / 256 * 256 : b->cus * b->blocks_per_cu;
+  const int grid = region ? (table->n + 255) / 256 * 256 : b->cus * b->blocks_per_cu;
   const auto key = region ? std::make_tuple(K, nmulti, -1, grid, region, 0)
                           : std::make_tuple(K, nmulti, nsingle, b->blocks_per_cu,
                                             K ? b->multi_nw : 0, K ? form : 0);
@@ -1420,8 +1437,8 @@ int batch_graph(lbm_batch *b, int K, int nmulti, int nsingle, int form, int regi
   // graph is replayed every tick)
   if (nmulti > 0 && !region) e = lbm::launch_fill_i32(b->d_nitems + 1, nmulti, 0, b->stream);
   for (int j = 0; j < nmulti && e == hipSuccess; ++j)
-    e = region ? lbm::launch_batch_tile(b->storage, region, K, b->d_doms, b->d_btiles,
-                                        b->d_ntiles + 1, grid, j, b->stream)
+    e = region ? lbm::launch_batch_tile(b->storage, region, K, b->d_doms, table->dev + 1,
+                                        (const int *)table->dev, grid, j, b->stream)
                : lbm::launch_batch_multi(b->storage, K, b->multi_nw, form, b->d_doms,
                                          b->d_items, b->d_nitems, b->multi_grid, j, b->stream);
   for (int k = 0; k < nsingle && e == hipSuccess; ++k)
@@ -1454,7 +1471,7 @@ void lbm_batch_destroy(lbm_batch *b) {
   if (b->d_ntiles) (void)hipFree(b->d_ntiles);
   if (b->d_items) (void)hipFree(b->d_items);
   if (b->d_nitems) (void)hipFree(b->d_nitems);
-  if (b->d_btiles) (void)hipFree(b->d_btiles);
+  for (auto &kv : b->bt_tables) (void)hipFree(kv.second.dev);
   if (b->d_trip) (void)hipFree(b->d_trip);
   if (b->d_chk) (void)hipFree(b->d_chk);
   for (int k = 0; k < 2; ++k) {
@@ -1533,60 +1550,83 @@ double batch_other_time(int storage, double cells, bool strips) {
   return t[0] + t[1] * cells;
 }
 
-// The square tiles for ticks of n steps: region and steps per launch by the tiles'
-// times, and their table. No tiles (bt_region = 0) where the launches that the
-// batch has otherwise are faster, which they are beyond some 3 million cells.
-// (Tiles against those, FP32: 2 of 64^2 1.05 and 3.3 us a step, 8 of 256^2 4.3 and
-// 12.7, 50 of 128^2 7.9 and 14.0.)
-int choose_batch_tiles(lbm_batch *b, int n, bool strips) {
+// The square tiles for ticks of n steps, by the launches that a member would make
+// (region 0: none, where the launches that the batch has otherwise are faster,
+// which they are beyond some 3 million cells, and for ticks of two steps, which the
+// parity would make two launches of one). The tiles' times are of single launches; in
+// a tick's graph they take about a tenth less. (Tiles against those, FP32: 2 of 64^2
+// 1.05 and 3.3 us a step, 8 of 256^2 4.3 and 12.7, 50 of 128^2 7.9 and 14.0.)
+lbm_batch::TileChoice choose_batch_tiles(const lbm_batch *b, int n, bool strips) {
+  lbm_batch::TileChoice c;
+  c.made = true;
   double cells = 0;
-  for (const lbm_handle *h : b->members) cells += (double)h->user.nx * h->user.ny;
-  double best = batch_other_time(b->storage, cells, strips);
-  int region = 0, most = 0;
+  for (const auto &m : b->sizes) cells += (double)m[0] * m[1] * m[2];
+  const double other = n * batch_other_time(b->storage, cells, strips);
+  double best = 1.12 * other;
   for (const TileTime &t : TILE_TIMES[b->storage])
-    for (int s = 2; t.region && s <= n; ++s) {
-      const int T = t.region - 2 * (s - 1);
+    for (int s = 2; t.region && s <= std::min(n, lbm::TILE_MAX_STEPS); ++s) {
+      const int T = t.region - 2 * (s - 1), launches = lbm::batch_tile_launches(n, s);
       if (T < 4 || cells / ((double)T * T) > 16.0 * b->cus) break;
+      if (launches == n) continue;
+      auto total = [&](double tiles) {
+        const double more = std::ceil(tiles / b->cus) - 1;
+        return launches * (t.first + more * t.next) + n * (t.step + more * t.next_step);
+      };
+      if (total(cells / ((double)T * T)) >= best) continue;  // at least as many tiles
       int64_t tiles = 0;
-      for (const lbm_handle *h : b->members)
-        tiles += ((h->user.nx + T - 1) / T) * ((h->user.ny + T - 1) / T);
-      const double rounds = (double)((tiles + b->cus - 1) / b->cus);
-      const double us = (t.first + t.step * s + (rounds - 1) * (t.next + t.next_step * s)) / s;
+      for (const auto &m : b->sizes) tiles += (m[0] + T - 1) / T * ((m[1] + T - 1) / T) * m[2];
+      const double us = total((double)tiles);
       if (us < best) {
         best = us;
-        region = t.region;
-        most = s;
+        c.region = t.region;
+        c.most = s;
+        c.gain = other - us / 1.12;
       }
     }
-  if (region && (region != b->bt_region || most != b->bt_most || !b->bt_for)) {
-    const int T = region - 2 * (most - 1);
-    std::vector<int4> tiles;
-    for (size_t i = 0; i < b->members.size(); ++i)
-      for (int64_t y = 0; y < b->members[i]->user.ny; y += T)
-        for (int64_t x = 0; x < b->members[i]->user.nx; x += T)
-          tiles.push_back(make_int4((int)i, (int)x, (int)y, 0));
-    if (tiles.size() > b->bt_cap) {
-      HIP_TRY(hipStreamSynchronize(b->stream), "hipStreamSynchronize");
-      free_graphs(b);
-      if (b->d_btiles) (void)hipFree(b->d_btiles);
-      b->d_btiles = nullptr;
-      b->bt_cap = b->bt_for = 0;
-      const size_t cap = (size_t)(1.5 * tiles.size());
-      HIP_TRY(hipMalloc((void **)&b->d_btiles, sizeof(int4) * cap), "batch tiles");
-      b->bt_cap = cap;
-    }
-    b->nbt = (int)tiles.size();
-    int rc = upload_tables(b, {{b->d_btiles, tiles.data(), sizeof(int4) * tiles.size()},
-                               {b->d_ntiles + 1, &b->nbt, sizeof(int)}});
-    if (rc) {
-      b->bt_for = 0;
-      return rc;
-    }
+  return c;
+}
+
+// The table of a choice for the current members, cut and copied behind the work
+// enqueued so far unless it is there; NULL while the ticks of these members would not
+// have gained what that costs (a server's short ticks between changes of its members).
+constexpr double BT_CUT_US = 8.0;
+int cut_batch_tiles(lbm_batch *b, const lbm_batch::TileChoice &c, lbm_batch::TileTable **out) {
+  lbm_batch::TileTable &t = b->bt_tables[{c.region, c.most}];
+  *out = &t;
+  if (t.n) return LBM_OK;
+  b->bt_owed += c.gain;
+  if (b->bt_owed < BT_CUT_US) {
+    *out = nullptr;
+    return LBM_OK;
   }
-  b->bt_region = region;
-  b->bt_most = most;
-  b->bt_for = n;
-  return LBM_OK;
+  const int T = c.region - 2 * (c.most - 1);
+  std::vector<int4> tiles(1);
+  for (size_t i = 0; i < b->members.size(); ++i)
+    for (int64_t y = 0; y < b->members[i]->user.ny; y += T)
+      for (int64_t x = 0; x < b->members[i]->user.nx; x += T)
+        tiles.push_back(make_int4((int)i, (int)x, (int)y, 0));
+  const int n = (int)tiles.size() - 1;
+  tiles[0] = make_int4(n, 0, 0, 0);
+  if (tiles.size() > t.cap) {
+    HIP_TRY(hipStreamSynchronize(b->stream), "hipStreamSynchronize");
+    free_graphs(b);
+    if (t.dev) (void)hipFree(t.dev);
+    t.dev = nullptr;
+    t.cap = 0;
+    const size_t cap = (size_t)(1.5 * tiles.size());
+    HIP_TRY(hipMalloc((void **)&t.dev, sizeof(int4) * cap), "batch tiles");
+    t.cap = cap;
+  }
+  int rc = upload_tables(b, {{t.dev, tiles.data(), sizeof(int4) * tiles.size()}});
+  if (!rc) t.n = n;
+  return rc;
+}
+
+// New members or settings: the choices and tables are no longer theirs.
+void forget_batch_tiles(lbm_batch *b) {
+  for (auto &c : b->bt_choice) c.made = false;
+  for (auto &kv : b->bt_tables) kv.second.n = 0;
+  b->bt_owed = 0.0;
 }
 
 // The strip work-item table for the batch's members and K-step shape
@@ -1705,13 +1745,24 @@ int batch_set_members_impl(lbm_batch *b, lbm_handle *const *members, int32_t cou
   b->ntiles = (int)tiles.size();
   b->members.assign(members, members + count);
   b->storage = members[0]->user.storage;
+  forget_batch_tiles(b);
+  b->sizes.clear();
+  for (int32_t i = 0; i < count; ++i) b->sizes.push_back({members[i]->user.nx, members[i]->user.ny, 1});
+  std::sort(b->sizes.begin(), b->sizes.end());
+  size_t last = 0;
+  for (size_t i = 1; i < b->sizes.size(); ++i) {
+    if (b->sizes[i][0] == b->sizes[last][0] && b->sizes[i][1] == b->sizes[last][1])
+      ++b->sizes[last][2];
+    else
+      b->sizes[++last] = b->sizes[i];
+  }
+  b->sizes.resize(last + 1);
   // fresh trip slots for the new member list (stream-ordered)
   HIP_TRY(lbm::launch_fill_u64(b->d_trip, count, lbm::TRIP_NONE, b->stream), "detector slots");
   b->any_detector = false;
   std::vector<int4> items;
   rc = make_items(b, items);
   if (rc) return rc;
-  b->bt_for = 0;  // the next tick cuts its own
   return upload_tables(b, {{b->d_tiles, tiles.data(), sizeof(int2) * tiles.size()},
                            {b->d_ntiles, &b->ntiles, sizeof(int)},
                            {b->d_items, items.data(), sizeof(int4) * items.size()},
@@ -1776,7 +1827,7 @@ int lbm_batch_create(lbm_handle *const *members, int32_t count, void *stream,
   int dev = 0;
   if (e == hipSuccess) e = hipGetDevice(&dev);
   if (e == hipSuccess) e = hipDeviceGetAttribute(&b->cus, hipDeviceAttributeMultiprocessorCount, dev);
-  if (e == hipSuccess) e = hipMalloc((void **)&b->d_ntiles, 2 * sizeof(int));  // and of square tiles
+  if (e == hipSuccess) e = hipMalloc((void **)&b->d_ntiles, sizeof(int));
   // item count and one ticket per strip launch of a tick (at most 4096 / 2)
   if (e == hipSuccess) e = hipMalloc((void **)&b->d_nitems, sizeof(int) * (1 + 4096 / 2));
   // default shape: K-step strip launches (K = 4 for FP32, 3 for FP64 and FP16)
@@ -1833,7 +1884,7 @@ int lbm_batch_set_tuning(lbm_batch *b, const lbm_tuning *t) {
     b->multi_nw = t->block / 64;
     b->multi_rows = t->rows;
   }
-  b->bt_for = 0;
+  forget_batch_tiles(b);
   return build_items(b);
 }
 
@@ -1841,7 +1892,7 @@ int lbm_batch_set_min_items(lbm_batch *b, int32_t min_items) {
   if (!b) return fail(LBM_EINVAL, "batch is NULL");
   if (min_items < -1) return fail(LBM_EINVAL, "min_items must be -1 or >= 0");
   b->min_items = min_items;
-  b->bt_for = 0;  // strips or single steps: the tiles' alternative may be another
+  forget_batch_tiles(b);  // strips or single steps: the tiles' alternative may be another
   return LBM_OK;
 }
 
@@ -1895,21 +1946,31 @@ int lbm_batch_tick(lbm_batch *b, int32_t tick, const int32_t *member_steps) {
   // tick length needs at most K graphs whatever the members' step counts.
   const int need = b->min_items >= 0 ? b->min_items : b->multi_grid;
   int K = b->multi_k && b->nitems >= need ? b->multi_k : 0;
-  int nmulti = 0, nsingle = tick, region = 0;
+  int nmulti = 0, nsingle = tick, region = 0, most = 0;
+  lbm_batch::TileTable *table = nullptr;
   if (b->multi_k && (!K || (!b->shape_set && b->min_items < 0)) && tick >= 2 &&
       (form & lbm::BATCH_DEF) && !(form & lbm::BATCH_QF)) {
-    const int bt = std::min(tick, lbm::TILE_MAX_STEPS);
-    if (bt != b->bt_for) {
-      int rc = choose_batch_tiles(b, bt, K != 0);
-      if (rc) return rc;
+    lbm_batch::TileChoice &c = b->bt_choice[std::min(tick, BT_TICKS)];
+    if (!c.made) c = choose_batch_tiles(b, std::min(tick, BT_TICKS), K != 0);
+    if (c.region) {
+      int rc = LBM_ENOMEM;
+      try {
+        rc = cut_batch_tiles(b, c, &table);
+      } catch (const std::bad_alloc &) {
+      }
+      if (rc == LBM_ENOMEM)  // the launches that the batch has otherwise need no table
+        c.region = 0;
+      else if (rc)
+        return rc;
     }
-    region = b->bt_region;
+    region = table ? c.region : 0;
+    most = c.most;
   }
   if (region) {
     K = 0;
+    nsingle = 0;
     for (size_t i = 0; i < n; ++i)
-      nmulti = std::max(nmulti, lbm::batch_tile_launches(member_steps ? member_steps[i] : tick,
-                                                         b->bt_most));
+      nmulti = std::max(nmulti, lbm::batch_tile_launches(member_steps ? member_steps[i] : tick, most));
   } else if (K) {
     nmulti = tick / K;
     nsingle = 0;
@@ -1919,8 +1980,8 @@ int lbm_batch_tick(lbm_batch *b, int32_t tick, const int32_t *member_steps) {
     }
   }
   hipGraphExec_t ex = nullptr;
-  int rc = region ? batch_graph(b, b->bt_most, nmulti, 0, 0, region, &ex)
-                  : batch_graph(b, K, nmulti, nsingle, form, 0, &ex);
+  int rc = region ? batch_graph(b, most, nmulti, 0, 0, region, table, &ex)
+                  : batch_graph(b, K, nmulti, nsingle, form, 0, nullptr, &ex);
   if (rc) return rc;
   HIP_TRY(hipGraphLaunch(ex, b->stream), "hipGraphLaunch");
   for (size_t i = 0; i < n; ++i) {

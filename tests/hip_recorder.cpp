@@ -27,7 +27,7 @@ State &state() {
   static State *s = new State;  // outlives the library's own static objects
   return *s;
 }
-std::atomic<int> capturing{0}, async_left{-1}, launches_left{-1}, error{hipSuccess};
+std::atomic<int> capturing{0}, mallocs_left{-1}, async_left{-1}, launches_left{-1}, error{hipSuccess};
 thread_local int news_left = -1;  // this thread's operator new: -1 never fails, else counts down
 struct Config {
   dim3 grid, block;
@@ -73,6 +73,7 @@ size_t recorder_take(char *out, size_t n) {  // the log so far, then empty
   return len;
 }
 void recorder_capturing(int on) { capturing = on; }
+void recorder_mallocs_left(int n) { mallocs_left = n; }  // hipMalloc calls that succeed, -1: all
 void recorder_async_left(int n) { async_left = n; }  // hipMallocAsync calls that succeed, -1: all
 void recorder_launches_left(int n) { launches_left = n; }  // kernel launches that succeed, -1: all
 void recorder_news_left(int n) { news_left = n; }    // this thread's allocations that succeed
@@ -117,18 +118,25 @@ hipError_t hipOccupancyMaxActiveBlocksPerMultiprocessor(int *n, const void *, in
 }
 
 // ---- memory
-hipError_t hipMalloc(void **p, size_t n) {
+static hipError_t take_memory(void **p, size_t n) {
   *p = std::aligned_alloc(4096, (n + 4095) / 4096 * 4096);  // untouched pages cost nothing
   return *p ? hipSuccess : hipErrorOutOfMemory;
+}
+hipError_t hipMalloc(void **p, size_t n) {
+  if (mallocs_left >= 0 && mallocs_left-- == 0) {
+    mallocs_left = 0;
+    return hipErrorOutOfMemory;
+  }
+  return take_memory(p, n);
 }
 hipError_t hipMallocAsync(void **p, size_t n, hipStream_t) {
   if (async_left >= 0 && async_left-- == 0) {
     async_left = 0;
     return hipErrorOutOfMemory;
   }
-  return hipMalloc(p, n);
+  return take_memory(p, n);
 }
-hipError_t hipHostMalloc(void **p, size_t n, unsigned) { return hipMalloc(p, n); }
+hipError_t hipHostMalloc(void **p, size_t n, unsigned) { return take_memory(p, n); }
 hipError_t hipFree(void *p) { return std::free(p), hipSuccess; }
 hipError_t hipFreeAsync(void *p, hipStream_t) { return std::free(p), hipSuccess; }
 hipError_t hipHostFree(void *p) { return std::free(p), hipSuccess; }
@@ -147,7 +155,7 @@ hipError_t hipPointerGetAttributes(hipPointerAttribute_t *a, const void *) {
   a->type = hipMemoryTypeUnregistered;
   return hipSuccess;
 }
-hipError_t hipGetSymbolAddress(void **p, const void *) { return hipMalloc(p, 1 << 20); }
+hipError_t hipGetSymbolAddress(void **p, const void *) { return take_memory(p, 1 << 20); }
 
 // ---- device, streams, events, graphs
 hipError_t hipGetDevice(int *d) { return *d = 0, hipSuccess; }

@@ -315,3 +315,56 @@ print(json.dumps(out))
             if d <= 4:
                 break
         assert grids == ([8 * -(-best[1] // 8)] * 4 if best[0] > 0.5 else []), (storage, nx, ny, nz)
+
+
+BATCH = """
+def kinds(log):
+    return ["tile" if "batch_tile" in l[1] else "strip" if "batch_multi" in l[1] else "one"
+            for l in log if l[0] == "launch" and l[1] != "graph" and "fill" not in l[1] and "check" not in l[1]]
+lats = [lbm.Lattice(64 + i %% 3, 60, storage=%r) for i in range(24)]
+b = lbm.Batch(lats)
+take()
+"""
+
+
+@pytest.mark.parametrize("storage", ["f32", "f64", "f16"])
+def test_ticks_of_a_small_batch(recorder, storage):
+    """Ticks of changing lengths cut no table twice and choose nothing again; a tick of two
+    steps takes single steps; a changed member list is cut anew; without memory for
+    a table the batch steps one by one."""
+    got = recorder(BATCH % storage + """
+out = {"kinds": {}, "copies": [], "members": []}
+for n in (2, 3, 4, 9, 14, 40):
+    for _ in range(4):  # a table is cut once ticks would have gained what it costs
+        b.step(n)
+        out["kinds"][n] = kinds(take()) or out["kinds"][n]  # (a graph is captured once)
+for n in (3, 9, 2, 4, 9, 3, 40, 14, 4):
+    b.step(n)
+    out["copies"].append(sum(l[0] == "copy" for l in take()))
+for who in (lats[:20], lats):
+    b.set_members(who)
+    take()
+    b.step(14)
+    out["members"].append(sum(l[0] == "copy" for l in take()))
+    b.step(14)
+    out["members"].append(sum(l[0] == "copy" for l in take()))
+    b.set_members(who)
+    take()
+    b.step(3)
+    out["members"].append(sum(l[0] == "copy" for l in take()))
+b = lbm.Batch(lats)
+take()
+R.recorder_mallocs_left(0)
+b.step(14)
+R.recorder_mallocs_left(-1)
+out["poor"] = kinds(take())
+b.step(16)
+out["later"] = kinds(take())
+print(json.dumps(out))
+""")
+    assert got["kinds"]["2"] == ["one"] * 2
+    assert all(set(got["kinds"][n]) == {"tile"} for n in ("4", "9", "14", "40")), got["kinds"]
+    assert all(len(got["kinds"][n]) % 2 == int(n) % 2 for n in got["kinds"])
+    assert got["copies"] == [1] * 9  # the members' descriptors
+    assert got["members"] == [2, 1, 1] * 2
+    assert got["poor"] == ["one"] * 14 and set(got["later"]) == {"tile"}
