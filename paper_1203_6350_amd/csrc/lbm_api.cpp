@@ -1979,11 +1979,13 @@ int lbm_batch_tick(lbm_batch *b, int32_t tick, const int32_t *member_steps) {
       nsingle = std::max(nsingle, st % K);
     }
   }
-  hipGraphExec_t ex = nullptr;
-  int rc = region ? batch_graph(b, most, nmulti, 0, 0, region, table, &ex)
-                  : batch_graph(b, K, nmulti, nsingle, form, 0, nullptr, &ex);
-  if (rc) return rc;
-  HIP_TRY(hipGraphLaunch(ex, b->stream), "hipGraphLaunch");
+  if (nmulti + nsingle > 0) {  // (no member steps: no graph of no launches)
+    hipGraphExec_t ex = nullptr;
+    int rc = region ? batch_graph(b, most, nmulti, 0, 0, region, table, &ex)
+                    : batch_graph(b, K, nmulti, nsingle, form, 0, nullptr, &ex);
+    if (rc) return rc;
+    HIP_TRY(hipGraphLaunch(ex, b->stream), "hipGraphLaunch");
+  }
   for (size_t i = 0; i < n; ++i) {
     const int st = member_steps ? member_steps[i] : tick;
     const int launches = K ? st / K + st % K : st;  // (tiles: of the same parity)

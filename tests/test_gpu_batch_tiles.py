@@ -86,3 +86,16 @@ def test_members_of_the_general_form():
         r.step(11)
         assert same(a, r)
     b.close()
+
+
+def test_a_tick_in_which_no_member_steps():
+    lats = [member(i, "f32", False) for i in range(6)]
+    ref = [member(i, "f32", True) for i in range(6)]
+    b = lbm.Batch(lats)
+    for n in (14, 0, 14, 0):
+        b.tick(14, [n] * 6)
+    b.sync()
+    for a, r in zip(lats, ref):
+        r.step(28)
+        assert same(a, r)
+    b.close()

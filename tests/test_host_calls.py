@@ -368,3 +368,18 @@ print(json.dumps(out))
     assert got["copies"] == [1] * 9  # the members' descriptors
     assert got["members"] == [2, 1, 1] * 2
     assert got["poor"] == ["one"] * 14 and set(got["later"]) == {"tile"}
+
+
+def test_a_tick_in_which_no_member_steps(recorder):
+    """It launches nothing where several steps per launch would leave an empty graph."""
+    got = recorder(BATCH % "f32" + """
+out = []
+for n in (14, 20):
+    b.step(n)
+    take()
+    b.tick(n, [0] * 24)
+    out.append(sum(l[:2] == ["launch", "graph"] for l in take()))
+out.append([l.info().steps_done for l in lats] == [34] * 24)
+print(json.dumps(out))
+""")
+    assert got == [0, 0, True]
