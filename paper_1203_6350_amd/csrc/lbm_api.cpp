@@ -1024,17 +1024,14 @@ int lbm_autotune(lbm_handle *h, int32_t reps, lbm_tuning *best, double *best_ms)
               if (r || !tiles) cands.push_back(lbm_tuning{kk, b, 0, r});
     // Fitted rows mean more than four steps where the kernel has them; four may still
     // be faster on a lattice whose width suits their strips (1163 x 2153 FP32: 210
-    // GLUPS against six steps' 204), in the height that would be fitted to them: all
-    // blocks resident at the 12 (FP64: 8) waves per compute unit that their
-    // registers allow.
+    // GLUPS against six steps' 204), in the height that is fitted to them.
     if (strips && !tiles && lbm::fitted_steps(h->cfg) > 4)
       for (int b : blocks)
         if (b <= lbm::multi_step_max_block(h->user.storage, 4)) {
-          const int64_t nw = b / 64, strip_groups = ((h->user.nx + 55) / 56 + nw - 1) / nw;
-          const int64_t fit = (int64_t)h->cus * ((h->user.storage == LBM_STORAGE_F64 ? 8 : 12) / nw);
-          const int64_t chunks = std::max<int64_t>(1, fit / strip_groups);
-          const int64_t r = (h->user.ny + chunks - 1) / chunks;
-          if (r <= 4096) cands.push_back(lbm_tuning{4, b, 0, (int32_t)r});
+          lbm::StepConfig four = h->cfg;
+          four.block = b;
+          const int r = lbm::fitted_rows(four, 4);
+          if (r >= 1 && r <= 4096) cands.push_back(lbm_tuning{4, b, 0, r});
         }
   }
   hipEvent_t e0, e1;

@@ -29,6 +29,7 @@ struct StepConfig {
   int block;             // threads per block: 64, 128, 256 or 512
   int nontemporal;       // 1: streaming (non-temporal) stores (vector kernel)
   int rows;              // rows per chunk of the multi-step kernel (0: fit the device)
+  int *fit_rows = nullptr; // set: write the rows per chunk here and launch nothing
   // per-cell reference state: three planes [3][qps] of (d rho^f, d j^f_x,
   // d j^f_y), each [ny][pitch], compute type; NULL: uniform dcf above
   void *qfield;
@@ -98,6 +99,8 @@ inline int fitted_steps(const StepConfig &c) {
 // fitted_steps.
 hipError_t launch_multi_steps(const StepConfig &c, int k, const void *src, void *dst,
                               hipStream_t stream);
+// The rows per chunk that a launch of k steps with fitted rows takes, 0 if it fails.
+int fitted_rows(StepConfig c, int k);
 // Tile kernel (lbm_tile_f64/f32/f16.hip): 1..TILE_MAX_STEPS steps in one
 // launch on regions of `region` cells a side (24 or 32, and in FP32 and FP16
 // 40 or 48). source: for a channel, the source column's deviations

@@ -431,6 +431,13 @@ hipError_t launch_multi_steps(const StepConfig &c, int k, const void *src, void 
   return hipErrorInvalidValue;
 }
 
+int fitted_rows(StepConfig c, int k) {
+  int rows = 0;
+  c.rows = 0;
+  c.fit_rows = &rows;
+  return launch_multi_steps(c, k, nullptr, nullptr, nullptr) == hipSuccess ? rows : 0;
+}
+
 int elem_bytes_of(int storage) {
   return storage == 0 ? 8 : (storage == 1 ? 4 : 2);
 }

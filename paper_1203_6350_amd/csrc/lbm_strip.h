@@ -783,6 +783,10 @@ static hipError_t launch_multi_t(const StepConfig &c, const void *src, void *dst
     const int64_t chunks = cap > ngroups ? cap / ngroups : 1;
     rows = (int)((c.ny + chunks - 1) / chunks);
   }
+  if (c.fit_rows) {
+    *c.fit_rows = rows;
+    return hipSuccess;
+  }
   const int nchunks = (c.ny + rows - 1) / rows;
   const int64_t nwg = (int64_t)ngroups * nchunks;
   const int64_t per_xcd = (nwg + 7) / 8;

@@ -383,3 +383,20 @@ out.append([l.info().steps_done for l in lats] == [34] * 24)
 print(json.dumps(out))
 """)
     assert got == [0, 0, True]
+
+
+@pytest.mark.parametrize("storage", ["f32", "f64"])
+def test_autotuner_fits_four_steps_by_occupancy(recorder, storage):
+    """Among the candidates are four steps per launch in the height at which the
+    workgroups that the device says it can hold are all resident."""
+    nx, ny = 2100, 1500
+    got = recorder("""
+lat = lattice(%d, %d, %r)
+lat.autotune(reps=1)
+print(json.dumps([[int(l[2]), int(l[3])] for l in take() if re.search("step_multi_strip.*ELi4EEE", l[1])]))
+""" % (nx, ny, storage))
+    for block in (64, 128, 256, 512) if storage == "f32" else (64, 128, 256):
+        groups = -(-(-(-nx // 56)) // (block // 64))
+        chunks = max(1, 256 * (512 // block) // groups)  # what the recorder says
+        rows = -(-ny // chunks)
+        assert [8 * -(-(groups * -(-ny // rows)) // 8), block] in got, block
