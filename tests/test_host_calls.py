@@ -400,3 +400,23 @@ print(json.dumps([[int(l[2]), int(l[3])] for l in take() if re.search("step_mult
         chunks = max(1, 256 * (512 // block) // groups)  # what the recorder says
         rows = -(-ny // chunks)
         assert [8 * -(-(groups * -(-ny // rows)) // 8), block] in got, block
+
+
+def test_strips_of_a_set_height(recorder):
+    """The handles of the tests of the four-step strips reach them: a set height on
+    small lattices, and large lattices of the general form as created."""
+    got = recorder("""
+out = []
+for storage in ("f64", "f32", "f16"):
+    for nx, ny, kw in ((133, 29, {}), (97, 23, dict(s=(1.7,) * 9)), (97, 23, dict(shift_n=0.3, shift_m=0.8))):
+        lat = lattice(nx, ny, storage, **kw)
+        lat.set_tuning(kernel=4, block=64, rows=5)
+        lat.step(8)
+        out.append(steps() == ["s4"] * 2)
+    for kw in (dict(s=(1.7,) * 9), dict(shift_n=0.3, shift_m=0.8)):
+        lat = lattice(1003, 1009, storage, **kw)
+        lat.step(11)
+        out.append("s4" in steps())
+print(json.dumps(out))
+""")
+    assert got == [True] * 15
