@@ -299,7 +299,10 @@ int lbm_set_line_source(lbm_handle *h, const lbm_line_source *src, int32_t outfl
 
 /* ---- kernel tuning ----------------------------------------------------
  * Launch shape of the step kernel. Every choice computes the same per-cell
- * arithmetic, so results are bit-identical across tunings.
+ * arithmetic, so results are bit-identical across tunings, up to the sign of
+ * zeros: outside the layer some kernels leave out the damping's products with
+ * 0, which can make -0 of what the others make +0 (so a reference state whose
+ * moments overflow the compute precision is felt there in the others only).
  * A handle whose shape has not been set (lbm_set_tuning, lbm_autotune) leaves
  * the choice to lbm_step, by size, storage and number of steps: the tile
  * kernel on lattices too small to fill the device with strips, else strips of
@@ -371,8 +374,8 @@ const char *lbm_last_error(void);
  * mean reference (lbm_set_qref_average with alpha != 0), a line source or
  * rows of 2^32 bytes or more are refused (LBM_EINVAL), at creation and,
  * for the first two, which can be set on a member later, at every tick
- * before it enqueues anything. Each member's result is bit-identical to
- * stepping it alone with lbm_step.
+ * before it enqueues anything. Each member's result is bit-identical (as above)
+ * to stepping it alone with lbm_step.
  * While a batch has work in flight its members must not be used on their
  * own; lbm_batch_sync makes them usable again. Member parameters (sponge,
  * q_ref and its per-cell field, tuning) are read at every tick, so they may

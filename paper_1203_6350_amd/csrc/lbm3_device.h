@@ -80,7 +80,7 @@ __device__ __forceinline__ void ref_moments3(const CollideParams3<C> &p, C mref[
 }
 
 // A product with a power of two is exact, so fused into the sum that takes it
-// it gives the same bits in one operation less.
+// it gives the same bits in one operation less (unless the product alone overflows).
 // One D3Q15 collision in deviation form; g: pre-collision deviations in,
 // post-collision deviations out. mref from ref_moments3 (Types I and II).
 template <typename C, int VAR>

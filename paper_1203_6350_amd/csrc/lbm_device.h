@@ -181,7 +181,8 @@ __device__ __forceinline__ void ref_moments(const CollideParams<C> &p, C mref[9]
 // to a value that is not finite is kept (0 * inf is a NaN): the terms 0 * m
 // below stand for the factors that the damped form multiplies by chi, so
 // that a run past its stability limit overflows to the same values in every
-// kernel. Only the sign of a zero may differ.
+// kernel. The sign of a zero may differ, and a reference state whose moments
+// overflow C (the damped form then makes every cell a NaN) is not felt here.
 template <typename C, int VAR, bool DEF = false, bool FREE = false>
 __device__ __forceinline__ void collide(C g[9], C chi, const CollideParams<C> &p,
                                         const C mref[9]) {

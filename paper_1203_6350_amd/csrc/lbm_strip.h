@@ -31,7 +31,8 @@ namespace lbm {
 //
 // Every intermediate result is rounded through the storage format before
 // the next step reads it, exactly as a stored and reloaded value would be,
-// so the result is bit-identical to K launches of the one-step kernels.
+// so the result is bit-identical to K launches of the one-step kernels (up to
+// the sign of zeros where strips run the collision's FREE form).
 //
 // Everything that indexes rows is uniform across the wave (scalar
 // registers); per lane only the column offset differs. The row loop is

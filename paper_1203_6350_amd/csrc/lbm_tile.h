@@ -28,7 +28,8 @@
 // The eight moving populations live in LDS in two copies (step j writes copy
 // j mod 2 and reads it after one barrier); the resting one stays in its
 // thread's register. Every intermediate result is rounded through the storage
-// format, so the result is bit-identical to that many one-step launches.
+// format, so the result is bit-identical to that many one-step launches, up to the
+// sign of zeros (waves clear of the layer run the collision's FREE form).
 #pragma once
 
 #include "lbm_device.h"
