@@ -97,6 +97,20 @@ def launch_steps(tuning, storage="f32"):
     return k if k >= 2 else 1
 
 
+def launches_made(tuning, per, steps):
+    """The launches that one call of `steps` steps makes with a set shape that takes up
+    to `per` per launch: of the same parity as the shape's own launches."""
+    own = -(-steps // max(1, min(tuning["kernel"], per)))
+    count = -(-steps // per)
+    return count + (count + own) % 2
+
+
+def launch_group(tuning, per, steps):
+    """The largest n for which a call of n * per <= steps steps makes n launches (1 if there is none)."""
+    fits = [n for n in range(1, steps // per + 1) if launches_made(tuning, per, n * per) == n]
+    return fits[-1] if fits else 1
+
+
 def counter_traffic(tuning):
     """HBM bytes per launch of the given launch shape from the committed
     rocprofv3 --pmc summary, or None when the kernel source changed since the
@@ -158,8 +172,9 @@ def time_variant(lbm, wl, torch, spec, fields, steps, warmup, diag_every=100, fi
     # launches run in groups between two diagnostics; a pair of events
     # brackets each group, so the mean launch duration includes the gaps
     # between launches but neither the diagnostics nor an event per launch
-    # (one after every launch cost about 1% of the rate)
-    group = max(1, diag_every // per) if diag_every else max(1, launches)
+    # (one after every launch cost about 1% of the rate); a group is a call of which
+    # the library makes so many launches
+    group = launch_group(tuning, per, diag_every if diag_every else launches * per)
     marks = []
     t0 = time.perf_counter()
     done_launches = 0
@@ -167,9 +182,9 @@ def time_variant(lbm, wl, torch, spec, fields, steps, warmup, diag_every=100, fi
         n = min(group, launches - done_launches)
         ea, eb = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
         ea.record(stream)
-        lat.step(n * per)  # n launches of `per` steps
+        lat.step(n * per)  # n launches of `per` steps, or as many as launches_made says
         eb.record(stream)
-        marks.append((ea, eb, n))
+        marks.append((ea, eb, n, launches_made(tuning, per, n * per)))
         done_launches += n
         if diag_every and n == group:
             lbm.lbm_diagnostics_dev(lat.h, diag)
@@ -177,7 +192,8 @@ def time_variant(lbm, wl, torch, spec, fields, steps, warmup, diag_every=100, fi
         lat.step(rest)  # the remaining steps as one shorter launch, so exactly `steps` run
     torch.cuda.synchronize()
     t1 = time.perf_counter()
-    group_ms = sum(ea.elapsed_time(eb) for ea, eb, _ in marks)
+    whole = [m for m in marks if m[2] == m[3]] or marks
+    group_ms = sum(ea.elapsed_time(eb) for ea, eb, _, _ in whole)
     d = diag.cpu().numpy()
     lat.close()
     wall = t1 - t0
@@ -185,7 +201,7 @@ def time_variant(lbm, wl, torch, spec, fields, steps, warmup, diag_every=100, fi
     done = launches * per + rest
     return dict(wall_s=wall, ms_per_step=1e3 * wall / done, steps=done,
                 mlups=cells * done / wall / 1e6, steps_per_launch=per,
-                kernel_ms=group_ms / launches if launches else float("nan"),
+                kernel_ms=group_ms / sum(m[3] for m in whole) if whole else float("nan"),
                 diag=[float(x) for x in d], tuning=tuning)
 
 
@@ -561,6 +577,7 @@ def qref_leg(lbm, wl, torch, n=4096, steps=400, warmup=20, alpha=1e-3):
             lat.autotune(reps=5)
         t = lat.tuning()
         per = min(5 if a else 6, launch_steps(t))
+        per = steps / launches_made(t, per, steps)  # the mean of the call below
         lat.step(warmup)
         e0 = torch.cuda.Event(enable_timing=True)
         e1 = torch.cuda.Event(enable_timing=True)

@@ -420,3 +420,26 @@ for storage in ("f64", "f32", "f16"):
 print(json.dumps(out))
 """)
     assert got == [True] * 15
+
+
+@pytest.mark.parametrize("storage", ["f32", "f64", "f16"])
+def test_launches_that_the_benchmark_counts(recorder, storage):
+    """Its group of launches is one that the library makes, of the steps it says."""
+    bench = pytest.importorskip("bench")
+    shapes = [dict(kernel=4, block=128, rows=0), dict(kernel=4, block=128, rows=32),
+              dict(kernel=3, block=64, rows=0), dict(kernel=1, block=256, rows=0)]
+    groups = []
+    for t in shapes:
+        per = bench.launch_steps(t, storage)
+        groups.append((per, bench.launch_group(t, per, 100)))
+    got = recorder("""
+out = []
+for t, (per, n) in zip(%r, %r):
+    lat = lattice(2048, 2048, %r)
+    lat.set_tuning(**t)
+    lat.step(n * per)
+    out.append(steps())
+print(json.dumps(out))
+""" % (shapes, groups, storage))
+    for log, (per, n) in zip(got, groups):
+        assert n * per >= 80 and len(log) == n and {int(l[1:]) for l in log} == {per}
