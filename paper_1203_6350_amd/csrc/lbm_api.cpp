@@ -411,12 +411,15 @@ struct StepPlan {
   lbm::StepConfig cfg;
 };
 
-// The number of launches of `seg` >= 1 steps, of the parity that the launches of
-// `per` steps would have: as few as `most` steps each allow, or one more.
-int64_t launch_count(int64_t seg, const StepPlan &p) {
+// The number of launches of `seg` >= 1 steps: as few as `most` steps each allow, and
+// one more where that is of the wrong parity (`odd`: against that of the launches of
+// `per` steps) and there are two steps to part.
+int64_t launch_count(int64_t seg, const StepPlan &p, bool odd = false) {
   const int64_t before = (seg - 1) / p.per + 1, count = (seg - 1) / p.most + 1;
-  return count + ((count ^ before) & 1);
+  return count + (((count ^ before) & 1) != (odd ? 1 : 0) && count < seg);
 }
+// The same without an eye to the parity, where more launches of the call follow.
+int64_t fewest_launches(int64_t seg, const StepPlan &p) { return (seg - 1) / p.most + 1; }
 
 // The steps of launch i of `count` that take `seg` steps: evenly. With as many
 // launches as the set shape would make, they are its own: other step counts move
@@ -480,7 +483,8 @@ double one_time(const lbm::StepConfig &c) {
 // than strips, or where there are none than single steps. The latter is close
 // for short calls, so it goes by the launches that would really be made, with
 // a margin for per-cell references (FP16 1500^2, 3 steps: tiles 74 us, 62 without).
-bool plan_tiles(const lbm::StepConfig &c, int64_t n, int cus, bool strips, StepPlan &p) {
+// `free`: more launches of the call follow, so that the parity does not bind.
+bool plan_tiles(const lbm::StepConfig &c, int64_t n, int cus, bool strips, bool free, StepPlan &p) {
   const double one = one_time(c), slower = c.qfield ? 1.15 : 1.0;
   double best = (double)n * (strips ? strip_time(c) : one);
   StepPlan q = p;
@@ -493,7 +497,8 @@ bool plan_tiles(const lbm::StepConfig &c, int64_t n, int cus, bool strips, StepP
       double total = us / s * (double)n;
       if (total >= best) continue;
       q.most = s;
-      const int64_t count = launch_count(n, q), m = n / count, longer = n % count;
+      const int64_t count = free ? fewest_launches(n, q) : launch_count(n, q);
+      const int64_t m = n / count, longer = n % count;
       if (m + (longer > 0) < 2) continue;  // all of them single steps
       if (!strips)
         total = slower * (double)longer * tile_time(c, t, (int)m + 1, cus, strips) +
@@ -550,8 +555,10 @@ StepPlan step_plan(const lbm_handle *h, int64_t n) {
   // a channel has no strip form: any shape means the tiles for it
   if (h->channel || !h->shape_set || (chosen && h->cfg.rows == 0)) {
     // (a detector cuts the call at its checks)
-    const int64_t m = h->det_every ? std::max<int64_t>(2, std::min(n, h->det_every)) : n;
-    if (plan_tiles(h->cfg, m, h->cus, strips, p)) return p;
+    int64_t m = n;
+    if (h->det_every && h->det_every < n) m = std::min(n, (h->det_every - 1) / p.per * p.per + p.per);
+    m = std::max<int64_t>(2, m);
+    if (plan_tiles(h->cfg, m, h->cus, strips, m < n, p)) return p;
   }
   return st;
 }
@@ -780,15 +787,22 @@ int lbm_step(lbm_handle *h, int64_t n) {
     }
   }
   // nothing is kept per launch: a call may be of any length
+  bool odd = false;  // the launches so far are of the other parity than the set shape's
   for (int64_t k = 0; k < n;) {
-    const int64_t seg = segment(h, k, n, p), count = launch_count(seg, p);
+    const int64_t seg = segment(h, k, n, p);
+    const int64_t count = seg < n - k ? fewest_launches(seg, p) : launch_count(seg, p, odd);
     for (int64_t i = 0; i < count; ++i) {
       int rc = run_launch(h, p, launch_steps(seg, count, i, p));
       if (rc) return rc;
     }
+    odd ^= ((count ^ ((seg - 1) / p.per + 1)) & 1) != 0;
     int rc = detector_after_launch(h, h->stream, nullptr);
     if (rc) return rc;
     k += seg;
+  }
+  if (odd) {  // (the last check was one step before the end)
+    HIP_TRY(lbm::launch_copy(h->lat[1 - h->cur], h->lat[h->cur], h->lat_bytes, h->stream), "lattice copy");
+    h->cur = 1 - h->cur;
   }
   if (h->mean_captured && qa && (mean != h->qf) != (own_swaps & 1)) {
     const size_t eb = h->user.storage == LBM_STORAGE_F64 ? 8 : 4;
@@ -1005,7 +1019,7 @@ int lbm_autotune(lbm_handle *h, int32_t reps, lbm_tuning *best, double *best_ms)
   const bool strips = lbm::multi_step_supports(h->cfg);
   const int64_t many = 1 << 20;
   StepPlan tile_plan;
-  const bool tiles = plan_tiles(h->cfg, many, h->cus, strips, tile_plan);
+  const bool tiles = plan_tiles(h->cfg, many, h->cus, strips, false, tile_plan);
   if (h->channel && tiles) {
     cands.push_back(lbm_tuning{0, 256, 0, 0});  // the tiles, whatever the shape
   } else {

@@ -133,7 +133,8 @@ HANDLES = {
 @pytest.mark.parametrize("name", list(HANDLES))
 def test_launches_of_a_call(recorder, name):
     """The launches of a call take its steps, as many as the set shape's own
-    launches in parity, and a detector's checks fall on the first multiples of
+    launches in parity (a copy of the lattice counts as one, where the last check
+    leaves a single step), and a detector's checks fall on the first multiples of
     the shape's steps, from the call's start, at or after each period."""
     per = 4 if "four" in name else 3 if "three" in name else 1
     got = recorder("""
@@ -151,15 +152,16 @@ for every in (0, 7, 16):
         for l in log:
             s = steps([l])
             k += int(s[0][1:]) if s else 0
-            if not s:
+            if "check" in l[1]:
                 at.append(k)
-        out.append([every, n, steps(log), at])
+        out.append([every, n, steps(log), at, sum("copy_kernel" in l[1] for l in log)])
 print(json.dumps(out))
 """ % HANDLES[name])
     done = {}
-    for every, n, launches, checks in got:
+    for every, n, launches, checks, copies in got:
         assert sum(int(l[1:]) for l in launches) == n
-        assert (len(launches) - (-(-n // per))) % 2 == 0, (n, launches)
+        assert (len(launches) + copies - (-(-n // per))) % 2 == 0, (n, launches)
+        assert copies == 0 or every and launches[-1][1:] == "1"
         if every:
             at, k = [], 0
             t0, due = done.get(every, (0, every))
@@ -170,6 +172,8 @@ print(json.dumps(out))
                     due = ((t0 + k) // every + 1) * every
             done[every] = t0 + n, due
             assert checks == at, (every, n, launches)
+            # between checks no more launches than the shape's own
+            assert len(launches) <= -(-n // per) + 1
 
 
 @pytest.mark.parametrize("shape,n", [(None, (4, 3, 6)), ((4, 0), (9, 1, 8)), ((4, 0), (8, 5, 9)),
