@@ -104,6 +104,9 @@ struct lbm_handle {
   int device = 0;
   int cus = 256;              // compute units of the device
   bool shape_set = false;     // lbm_set_tuning or lbm_autotune chose the launch shape
+  // lbm_autotune chose fitted rows with more than four steps: the block and rows in which four
+  // steps were fastest, for launches of up to four (block 0: those of the set shape)
+  int four_block = 0, four_rows = 0;
   // instability detector (lbm_set_detector)
   int64_t det_every = 0;      // 0: off
   double det_max = 0.0;
@@ -423,8 +426,8 @@ int64_t fewest_launches(int64_t seg, const StepPlan &p) { return (seg - 1) / p.m
 
 // The steps of launch i of `count` that take `seg` steps: evenly. With as many
 // launches as the set shape would make, they are its own: other step counts move
-// as much memory and cost more (FP32 4096^2, 9 steps as 4 + 4 + 1 787 us, as 3 + 3 + 3 or
-// 5 + 2 + 2 880 to 896).
+// as much memory and cost more (FP32 4096^2, 9 steps as 4 + 4 + 1 789 us, as
+// 5 + 2 + 2 898).
 int launch_steps(int64_t seg, int64_t count, int64_t i, const StepPlan &p) {
   if (p.kind == StepPlan::STRIP) {
     if (count == (seg - 1) / p.per + 1 && (p.per == p.most || !p.halve))
@@ -543,12 +546,12 @@ StepPlan step_plan(const lbm_handle *h, int64_t n) {
                      : h->user.storage == LBM_STORAGE_F64 ? 128
                                                             : 64;
     }
-    // Halving the last launch is the better way to one more where launches of all
-    // step counts cost about the same (FP64, 5 steps: 3 + 1 + 1 550 us at 2048^2 with a
-    // per-cell reference, 2 + 2 + 1 less, but 20 steps 961 against 1396 evenly); for
-    // FP32's five and six steps evenly is (2048^2, 7 steps 3 to 7%). With a set shape it pays
-    // for five steps in FP64 until the chunks are tall: a launch of five takes
-    // as long as one of four (1024^2 46 and 45 us, 20 steps 223 against 250; 2048^2 177 and 140).
+    // Halving the last launch is the better way to one more where launches of two to
+    // four steps cost nearly the same (FP64 2048^2 with a per-cell reference, 20 steps
+    // 961 us, evenly 1396), evenly for five and six steps in FP32 (1000^2 and 1500^2, 7 steps
+    // 0.95). With a set shape halving pays for five steps in FP64 until the chunks are
+    // tall: a launch of five takes about as long as one of four (20 steps at 1024^2 224
+    // us, its own launches 250; at 2048^2 768 and 749).
     st.halve = h->shape_set ? st.most == 5 && h->user.storage == LBM_STORAGE_F64 && cells < 2e6
                             : st.most == 4 || h->user.storage == LBM_STORAGE_F64;
   }
@@ -602,6 +605,10 @@ int enqueue_launch(lbm_handle *h, const StepPlan &p, int steps, const void *src,
                    bool *second) {
   hipError_t e;
   lbm::StepConfig c = p.kind == StepPlan::STRIP && steps > 1 ? p.cfg : h->cfg;
+  if (p.kind == StepPlan::STRIP && steps > 1 && steps <= 4 && h->four_block) {
+    c.block = h->four_block;
+    c.rows = h->four_rows;
+  }
   c.qfield = h->qf;
   c.qfield_out = h->qf2;
   *second = false;
@@ -996,6 +1003,7 @@ int lbm_set_tuning(lbm_handle *h, const lbm_tuning *t) {
   h->cfg.nontemporal = t->kernel == 1 ? t->nontemporal : 0;
   if (t->kernel >= 2) h->cfg.rows = t->rows;
   h->shape_set = true;
+  h->four_block = 0;
   return LBM_OK;
 }
 
@@ -1090,10 +1098,12 @@ int lbm_autotune(lbm_handle *h, int32_t reps, lbm_tuning *best, double *best_ms)
   void *to = h->lat[1 - h->cur];
   const lbm::StepConfig saved = h->cfg;
   const bool saved_set = h->shape_set;
-  double best_t = 1e300;
-  lbm_tuning best_c = cands[0];
-  int rc_launch = LBM_OK;
+  double best_t = 1e300, four_t = 1e300;
+  lbm_tuning best_c = cands[0], four_c = {0, 0, 0, 0};
+  int best_most = 1, rc_launch = LBM_OK;
   h->shape_set = true;
+  const int saved_four = h->four_block;
+  h->four_block = 0;
   for (const lbm_tuning &c : cands) {
     h->cfg.kernel = c.kernel;
     h->cfg.block = c.block;
@@ -1118,8 +1128,13 @@ int lbm_autotune(lbm_handle *h, int32_t reps, lbm_tuning *best, double *best_ms)
     if (e == hipSuccess) e = hipEventElapsedTime(&ms, e0, e1);
     if (e != hipSuccess) break;
     const double per = ms / reps / (double)p.most;  // per time step
+    if (c.kernel == 4 && c.rows && per < four_t) {
+      four_t = per;
+      four_c = c;
+    }
     if (per < best_t) {
       best_t = per;
+      best_most = p.kind == StepPlan::STRIP ? p.most : 1;
       best_c = c;
     }
   }
@@ -1127,6 +1142,7 @@ int lbm_autotune(lbm_handle *h, int32_t reps, lbm_tuning *best, double *best_ms)
   (void)hipEventDestroy(e1);
   h->cfg = saved;
   h->shape_set = saved_set;
+  h->four_block = saved_four;
   if (scratch) (void)hipFreeAsync(scratch, h->stream);
   if (qf_keep) {
     const hipError_t e2 = hipMemcpyAsync(h->qf, qf_keep, qf_bytes, hipMemcpyDeviceToDevice, h->stream);
@@ -1136,6 +1152,11 @@ int lbm_autotune(lbm_handle *h, int32_t reps, lbm_tuning *best, double *best_ms)
   if (rc_launch) return rc_launch;
   if (e != hipSuccess) return hip_fail(e, "autotune");
   h->shape_set = true;
+  // six steps may like another block than four (FP32 4096^2 64 and 256, where calls of
+  // 9 and 20 steps, which take four, took 950 and 1694 us in the one and 800 and
+  // 1451 in the other)
+  h->four_block = best_most > 4 ? four_c.block : 0;
+  h->four_rows = four_c.rows;
   h->cfg.kernel = best_c.kernel;
   h->cfg.block = best_c.block;
   h->cfg.nontemporal = best_c.nontemporal;

@@ -75,16 +75,15 @@ inline bool multi_step_supports(const StepConfig &c) {
   return (float)c.s[0] == 0.0f && (float)c.s[1] == 0.0f && (float)c.s[2] == 0.0f &&
          (float)c.n == (float)c.m;
 }
-// Steps per launch of the four-step shape with fitted rows: six in FP32 and five in
-// FP64, in the default form (FP64: without a per-cell reference).
-// A launch costs its memory traffic whether it collides four or six times. FP32,
-// from four to six steps: 4096^2 from 235 to 265 GLUPS, 2048^2 from 204 to 229,
-// 1024^2 from 135 to 146 (each in its best block of fitted rows), 2048^2 with a
-// per-cell reference from 191 to 211; with a running mean five steps (six do not fit
-// the registers, 2048^2 164 -> 151), from 2 million cells on (4096^2 188 -> 195, 2048^2
-// 167 -> 176, but 1200^2 147 -> 145). FP64, from four to five: 4096^2 from 124 to 130,
-// 2048^2 from 110 to 123, 1300 x 1200 from 94 to 105 (six: 129, 122, 104). FP16 is
-// bound by VALU issue already (five steps: 227 -> 208).
+// Most steps per launch of the four-step shape with fitted rows: six in FP32 and five
+// in FP64, in the default form (FP64: without a per-cell reference).
+// A launch costs its memory traffic whether it collides four or six times. Calls of 100
+// steps, block 256, layers a sixteenth of the side, four steps against up to that many,
+// GLUPS: FP32 4096^2 235 and 261, 2048^2 218 and 229, 1024^2 145 and 152; with a running
+// mean five steps from 2 million cells on (six do not fit the registers), 4096^2 184 and
+// 192, 2048^2 168 and 172, but 1200^2 147 and 145. FP64 4096^2 124 and 130, 2048^2 113 and
+// 120, 1024^2 87 and 105 (six were no faster). FP16 is bound by VALU issue already (five
+// steps were slower by a twelfth).
 inline int fitted_steps(const StepConfig &c) {
   if (!multi_step_supports(c) || c.storage == 2) return 4;
   if (c.storage == 0)

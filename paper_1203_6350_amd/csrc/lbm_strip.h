@@ -545,7 +545,7 @@ __device__ __forceinline__ void strip_run(const StripCtx<S, VAR, CHI, K> &c, int
 // damping's products with 0 (FREE; default parameters only, which halves the
 // instances; the undamped scheme is its own free form). It pays in FP16 storage and
 // in FP32 beyond four steps, which are bound by VALU issue (FP16 4096^2 Type II, four
-// steps, rows 32: 0.95 of the time; FP32 with six steps 257 -> 265 GLUPS), with 0.90 of
+// steps, rows 32: 0.95 of the time; FP32 with six steps 0.97), with 0.90 of
 // the waves of 4096^2 clear of a 64-cell layer. Four steps in FP32 move memory at
 // 4.7 TB/s whether they collide or not (265 us a launch without the collision,
 // 285 with it) and gained 2%; in FP64 the second loop's registers took 9% from

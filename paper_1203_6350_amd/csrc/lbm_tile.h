@@ -15,11 +15,13 @@
 //
 // Per step, one step per launch -> tiles (Type II): 128^2 FP64 3.6 -> 1.2 us, 128^2
 // FP32 4.5 -> 0.9, 256^2 FP32 4.8 -> 1.1, 512^2 FP32 9.8 -> 2.4 (107 G updates/s),
-// 512^2 FP16 7.3 -> 2.7, the 800 x 200 FP64 channel 7.9 -> 3.2. A launch costs
-// about 5 us plus 0.4 (24^2) to 1.1 us (48^2) a step where its tiles run at
-// once: the small regions are bound by latency (launch, first loads, one barrier
+// 512^2 FP16 7.3 -> 2.7, the 800 x 200 FP64 channel 7.9 -> 3.2. Traced launches of eight
+// steps take some 10 us (24^2 FP64 and 32^2 FP32) and 19 (48^2 FP32) where their tiles run
+// at once: 5 to 10 us for the first loads, the last stores and a wave's start, and
+// 0.4 to 1.1 a step. VALU issue is busy 0.27, 0.63 and 0.82 of the time that waves are on
+// the chip: the small regions are bound by latency (first loads, one barrier
 // and one LDS round trip a step), the 48^2 one by VALU issue, half of it on the
-// shrinking halo.
+// shrinking halo. LDS has no bank conflicts.
 //
 // The same tiles of many small lattices make one launch of a batch (us a step,
 // FP32): 2 of 64^2 3.3 -> 1.05, 8 of 256^2 12.7 -> 4.3, 50 of 128^2 14.0 -> 7.7, 36 of

@@ -38,7 +38,7 @@
 //
 // 64 sets x 256^2 wavenumbers: 15.7 ms (268 M eigenproblems/s) with one window 0..8
 // in every sweep and the entries at a lane's own bottom selected over all
-// positions, now 11.9 ms (353 M/s).
+// positions, now 12 to 13 ms (traced launches 11.9 to 13.3, 334 M/s on average).
 #include "lbm_device.h"
 #include "lbm_internal.h"
 

@@ -35,6 +35,7 @@ struct Config {
   hipStream_t stream;
 };
 thread_local Config pushed;
+float last_ms = 1.0f;  // what events say about the last launch
 
 void line(const char *fmt, const char *what, unsigned a, unsigned b, int c, hipStream_t s) {
   char buf[1024];
@@ -107,6 +108,9 @@ hipError_t hipLaunchKernel(const void *fn, dim3 g, dim3 b, void **args, size_t, 
     return hipErrorLaunchFailure;
   }
   const std::string &name = state().kernels[fn];
+  // strips of five and six steps are fastest in small workgroups, the others in large ones
+  const bool more = name.find("ELi5EEE") != std::string::npos || name.find("ELi6EEE") != std::string::npos;
+  last_ms = 1.0f + 0.001f * (more ? b.x : 512 - (b.x < 512 ? b.x : 512));
   // the tile kernel's third argument is its number of steps
   const int steps = name.find("11tile_kernel") != std::string::npos ? *(int *)args[2] : 0;
   line("launch %s %u %u %d %llx %s\n", name.c_str(), g.x, b.x, steps, s);
@@ -194,6 +198,6 @@ hipError_t hipEventCreateWithFlags(hipEvent_t *e, unsigned) { return hipEventCre
 hipError_t hipEventDestroy(hipEvent_t) { return hipSuccess; }
 hipError_t hipEventRecord(hipEvent_t, hipStream_t) { return hipSuccess; }
 hipError_t hipEventSynchronize(hipEvent_t) { return hipSuccess; }
-hipError_t hipEventElapsedTime(float *ms, hipEvent_t, hipEvent_t) { return *ms = 1.0f, hipSuccess; }
+hipError_t hipEventElapsedTime(float *ms, hipEvent_t, hipEvent_t) { return *ms = last_ms, hipSuccess; }
 
 }  // extern "C"

@@ -447,3 +447,29 @@ print(json.dumps(out))
 """ % (shapes, groups, storage))
     for log, (per, n) in zip(got, groups):
         assert n * per >= 80 and len(log) == n and {int(l[1:]) for l in log} == {per}
+
+
+@pytest.mark.parametrize("storage", ["f32", "f64"])
+def test_autotuned_calls_of_four_steps_per_launch(recorder, storage):
+    """Where the autotuner takes more than four steps per launch, the launches of
+    up to four run in the block that was fastest for them; a shape set by hand keeps its block."""
+    got = recorder("""
+lat = lattice(2100, 1500, %r)
+lat.autotune(reps=1)
+take()
+out = [lat.tuning()]
+for n in (20, 18 if %r == "f32" else 100):
+    lat.step(n)
+    log = take()
+    out.append([steps(log), [int(l[3]) for l in log]])
+lat.set_tuning(kernel=4, block=128, rows=0)
+lat.step(20)
+log = take()
+out.append([steps(log), [int(l[3]) for l in log]])
+print(json.dumps(out))
+""" % (storage, storage))
+    big, n, most = (512, 3, "s6") if storage == "f32" else (256, 0, "s5")
+    assert got[0] == dict(kernel=4, block=64, nontemporal=0, rows=0)
+    assert got[1] == [["s4"] * 5, [big] * 5]
+    assert all(b == (64 if s in ("s5", "s6") else big) for s, b in zip(*got[2])) and most in got[2][0]
+    assert got[3] == [["s4"] * 5, [128] * 5]
