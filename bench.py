@@ -52,6 +52,7 @@ KERNEL_SOURCES["d3q15"] = [os.path.join(CSRC, f) for f in ("lbm3_kernels.hip", "
                                                             "lbm_device.h")]
 PMC_SUMMARY3 = os.path.join(ROOT, "profiles", "step3_d3q15_typeII_256cube.txt")
 KERNEL_SOURCES["vn"] = [os.path.join(CSRC, "lbm_vn.hip")]
+KERNEL_SOURCES["tile"] = [os.path.join(CSRC, f) for f in ("lbm_tile.h", "lbm_launch.h", "lbm_device.h")]
 
 
 def kernel_hash(family):
@@ -162,46 +163,46 @@ def time_variant(lbm, wl, torch, spec, fields, steps, warmup, diag_every=100, fi
     else:
         lat.set_tuning(**fixed)
         tuning = lat.tuning()
-    per = launch_steps(tuning, spec.storage)
-    launches, rest = divmod(steps, per)
-    if not launches:  # fewer steps than a launch holds: one shorter launch
-        per, launches, rest = steps, 1, 0
+    per = min(launch_steps(tuning, spec.storage), steps)
     diag = torch.empty(7, dtype=torch.float64, device="cuda")
     lat.step(warmup)
     torch.cuda.synchronize()
-    # launches run in groups between two diagnostics; a pair of events
-    # brackets each group, so the mean launch duration includes the gaps
-    # between launches but neither the diagnostics nor an event per launch
-    # (one after every launch cost about 1% of the rate); a group is a call of which
-    # the library makes so many launches
-    group = launch_group(tuning, per, diag_every if diag_every else launches * per)
+    # launches run in groups between two diagnostics, each group a call of which the
+    # library makes so many launches of `per` steps, and what is left (or fewer steps
+    # than that) in one call, which the library divides as it does for a program; a pair of
+    # events brackets each, so the mean launch duration includes the gaps between
+    # launches but neither the diagnostics nor an event per launch (one after every
+    # launch cost about 1% of the rate)
+    grouped = bool(diag_every) and steps >= diag_every
+    whole = per * launch_group(tuning, per, diag_every) if grouped else steps
     marks = []
     t0 = time.perf_counter()
-    done_launches = 0
-    while done_launches < launches:
-        n = min(group, launches - done_launches)
+    done = 0
+    while done < steps:
+        n = min(whole, steps - done)
         ea, eb = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
         ea.record(stream)
-        lat.step(n * per)  # n launches of `per` steps, or as many as launches_made says
+        lat.step(n)
         eb.record(stream)
-        marks.append((ea, eb, n, launches_made(tuning, per, n * per)))
-        done_launches += n
-        if diag_every and n == group:
+        marks.append((ea, eb, n, launches_made(tuning, per, n)))
+        done += n
+        if grouped and n == whole:
             lbm.lbm_diagnostics_dev(lat.h, diag)
-    if rest:
-        lat.step(rest)  # the remaining steps as one shorter launch, so exactly `steps` run
     torch.cuda.synchronize()
     t1 = time.perf_counter()
-    whole = [m for m in marks if m[2] == m[3]] or marks
-    group_ms = sum(ea.elapsed_time(eb) for ea, eb, _, _ in whole)
+    if not grouped:
+        lbm.lbm_diagnostics_dev(lat.h, diag)
+    timed = [m for m in marks if m[2] == whole and m[2] == per * m[3]] or marks
+    launches = sum(m[3] for m in timed)
+    per = per if timed is not marks else sum(m[2] for m in timed) / launches
+    group_ms = sum(m[0].elapsed_time(m[1]) for m in timed)
     d = diag.cpu().numpy()
     lat.close()
     wall = t1 - t0
     cells = spec.nx * spec.ny
-    done = launches * per + rest
     return dict(wall_s=wall, ms_per_step=1e3 * wall / done, steps=done,
                 mlups=cells * done / wall / 1e6, steps_per_launch=per,
-                kernel_ms=group_ms / sum(m[3] for m in whole) if whole else float("nan"),
+                kernel_ms=group_ms / launches,
                 diag=[float(x) for x in d], tuning=tuning)
 
 
@@ -778,8 +779,9 @@ def main():
     hbm_gbps = bytes_per_cell * cells / launch_s / 1e9
     alu_tflops = FLOPS_PER_UPDATE[head] * cells * per / launch_s / 1e12
     copy_gbps = None if args.no_copy else copy_bandwidth(lbm, torch)
-    traffic = (counter_traffic(r["tuning"]) if args.storage == "f32" and args.n == 4096
-               and head == "II" else None)
+    profiled = (args.storage == "f32" and args.n == 4096 and head == "II"
+                and per == launch_steps(r["tuning"]))  # the counters are of such launches
+    traffic = counter_traffic(r["tuning"]) if profiled else None
     common = {"traffic": traffic,
               "algorithmic_bytes_per_launch": bytes_per_cell * cells,
               "algorithmic_flops_per_launch": FLOPS_PER_UPDATE[head] * cells * per,
@@ -792,8 +794,7 @@ def main():
         # the SQ counters give the issue utilisation the flop rate understates
         roofline = dict({"bound": "alu", "achieved": alu_tflops, "peak": PEAK_VALU_TFLOPS,
                          "unit": "TFLOP/s", "frac": alu_tflops / PEAK_VALU_TFLOPS}, **common)
-        issue = (valu_issue(r["tuning"]) if args.storage == "f32" and args.n == 4096
-                 and head == "II" else None)
+        issue = valu_issue(r["tuning"]) if profiled else None
         if issue:
             roofline.update(issue)
     else:

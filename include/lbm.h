@@ -333,7 +333,8 @@ typedef struct lbm_tuning {
                           the launch to the device: the height at which all
                           blocks are resident at once (kernel 4 then takes up
                           to six steps per launch in FP32 and five in FP64
-                          with s0 = s1 = s2 = 0 and shift_n = shift_m), or, on a
+                          with s0 = s1 = s2 = 0 and shift_n = shift_m, in calls
+                          that have fewer launches for it), or, on a
                           lattice too small for that to pay, the tile kernel
                           with up to 14 steps per launch; ignored by kernels
                           0 and 1                                            */
@@ -348,7 +349,10 @@ int lbm_get_tuning(lbm_handle *h, lbm_tuning *t);
  * best and best_ms may be NULL. Synchronises. The timings depend on the
  * current state: a field whose deviations are still mostly exact zeros
  * (just initialised from localised pulses) runs faster and can rank the
- * shapes differently from the developed field, so tune after some steps. */
+ * shapes differently from the developed field, so tune after some steps.
+ * Where that is fitted rows with more than four steps per launch, the handle
+ * also keeps the block and rows in which four were fastest, for its launches
+ * of up to four (lbm_set_tuning forgets them). */
 int lbm_autotune(lbm_handle *h, int32_t reps, lbm_tuning *best, double *best_ms);
 
 /* Release all resources of the handle; NULL is accepted. */
