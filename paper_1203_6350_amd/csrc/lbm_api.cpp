@@ -1338,7 +1338,7 @@ struct lbm_batch {
   struct TileChoice {
     bool made = false;
     int region = 0, most = 0;  // region 0: no tiles
-    double gain = 0.0;         // us a tick
+    double gain = 0.0;         // us a step
   };
   struct TileTable {
     int4 *dev = nullptr;  // [0].x: the number of tiles, then the tiles
@@ -1582,39 +1582,42 @@ double batch_other_time(int storage, double cells, bool strips) {
   return t[0] + t[1] * cells;
 }
 
-// The square tiles for ticks of n steps, by the launches that a member would make
-// (region 0: none, where the launches that the batch has otherwise are faster,
-// which they are beyond some 3 million cells, and for ticks of two steps, which the
-// parity would make two launches of one). The tiles' times are of single launches; in
-// a tick's graph they take about a tenth less. (Tiles against those, FP32: 2 of 64^2
-// 1.05 and 3.3 us a step, 8 of 256^2 4.3 and 12.7, 50 of 128^2 7.9 and 14.0.)
+// The square tiles for ticks of n steps, the fastest per step by the tiles' times;
+// none (region 0) where the launches that the batch has otherwise are faster,
+// which they are beyond some 3 million cells, or where the launches that a member would
+// really make are no gain: for ticks of two steps the parity makes them two of one. (The
+// times are of single launches; in a tick's graph they take about a tenth less.
+// Tiles against the others, FP32: 2 of 64^2 1.05 and 3.3 us a step, 8 of 256^2 4.3 and
+// 12.7, 50 of 128^2 7.9 and 14.0.)
 lbm_batch::TileChoice choose_batch_tiles(const lbm_batch *b, int n, bool strips) {
   lbm_batch::TileChoice c;
   c.made = true;
   double cells = 0;
   for (const auto &m : b->sizes) cells += (double)m[0] * m[1] * m[2];
-  const double other = n * batch_other_time(b->storage, cells, strips);
-  double best = 1.12 * other;
+  const double other = batch_other_time(b->storage, cells, strips);
+  double best = other, made = 0.0;  // a step: of full launches, and of those of the tick
   for (const TileTime &t : TILE_TIMES[b->storage])
     for (int s = 2; t.region && s <= std::min(n, lbm::TILE_MAX_STEPS); ++s) {
       const int T = t.region - 2 * (s - 1), launches = lbm::batch_tile_launches(n, s);
       if (T < 4 || cells / ((double)T * T) > 16.0 * b->cus) break;
       if (launches == n) continue;
-      auto total = [&](double tiles) {
+      auto per_step = [&](double tiles, double steps) {
         const double more = std::ceil(tiles / b->cus) - 1;
-        return launches * (t.first + more * t.next) + n * (t.step + more * t.next_step);
+        return (t.first + more * t.next) / steps + t.step + more * t.next_step;
       };
-      if (total(cells / ((double)T * T)) >= best) continue;  // at least as many tiles
+      if (per_step(cells / ((double)T * T), s) >= best) continue;  // at least as many tiles
       int64_t tiles = 0;
       for (const auto &m : b->sizes) tiles += (m[0] + T - 1) / T * ((m[1] + T - 1) / T) * m[2];
-      const double us = total((double)tiles);
+      const double us = per_step((double)tiles, s);
       if (us < best) {
         best = us;
+        made = per_step((double)tiles, n < BT_TICKS ? (double)n / launches : s);
         c.region = t.region;
         c.most = s;
-        c.gain = other - us / 1.12;
       }
     }
+  if (made >= 1.12 * other) c.region = 0;
+  c.gain = other - made / 1.12;
   return c;
 }
 
@@ -1622,11 +1625,11 @@ lbm_batch::TileChoice choose_batch_tiles(const lbm_batch *b, int n, bool strips)
 // enqueued so far unless it is there; NULL while the ticks of these members would not
 // have gained what that costs (a server's short ticks between changes of its members).
 constexpr double BT_CUT_US = 8.0;
-int cut_batch_tiles(lbm_batch *b, const lbm_batch::TileChoice &c, lbm_batch::TileTable **out) {
+int cut_batch_tiles(lbm_batch *b, const lbm_batch::TileChoice &c, int tick, lbm_batch::TileTable **out) {
   lbm_batch::TileTable &t = b->bt_tables[{c.region, c.most}];
   *out = &t;
   if (t.n) return LBM_OK;
-  b->bt_owed += c.gain;
+  b->bt_owed += c.gain * tick;
   if (b->bt_owed < BT_CUT_US) {
     *out = nullptr;
     return LBM_OK;
@@ -1640,12 +1643,15 @@ int cut_batch_tiles(lbm_batch *b, const lbm_batch::TileChoice &c, lbm_batch::Til
   const int n = (int)tiles.size() - 1;
   tiles[0] = make_int4(n, 0, 0, 0);
   if (tiles.size() > t.cap) {
-    HIP_TRY(hipStreamSynchronize(b->stream), "hipStreamSynchronize");
-    free_graphs(b);
-    if (t.dev) (void)hipFree(t.dev);
+    if (t.dev) {  // the old table and every graph that points at it go away
+      HIP_TRY(hipStreamSynchronize(b->stream), "hipStreamSynchronize");
+      free_graphs(b);
+      (void)hipFree(t.dev);
+    }
     t.dev = nullptr;
     t.cap = 0;
-    const size_t cap = (size_t)(1.5 * tiles.size());
+    // (16 rounds of tiles, more than pay: 64 KB on 256 compute units)
+    const size_t cap = std::max((size_t)(1.5 * tiles.size()), (size_t)16 * b->cus);
     HIP_TRY(hipMalloc((void **)&t.dev, sizeof(int4) * cap), "batch tiles");
     t.cap = cap;
   }
@@ -1987,7 +1993,7 @@ int lbm_batch_tick(lbm_batch *b, int32_t tick, const int32_t *member_steps) {
     if (c.region) {
       int rc = LBM_ENOMEM;
       try {
-        rc = cut_batch_tiles(b, c, &table);
+        rc = cut_batch_tiles(b, c, tick, &table);
       } catch (const std::bad_alloc &) {
       }
       if (rc == LBM_ENOMEM)  // the launches that the batch has otherwise need no table
